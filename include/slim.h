@@ -83,10 +83,13 @@ typedef enum { SLIM_PHASE_FWD = 0, SLIM_PHASE_BWD = 1 } slim_phase;
  *                          row grows with C (bf16 problems with M of 128 or
  *                          256, FAVOR+ or ReLU)
  *   SLIM_WITHIN_PS         the explicit prefix sum the paper benchmarks as
- *                          "PS": the state after every row of a slice is
- *                          written out (C M (d + 1) floats per head, twice in
- *                          the backward, in the workspace), then used; slices
- *                          one after another.  Memory grows with C.  Any
+ *                          "PS": prefix sums written out, then used, here at
+ *                          the boundaries of 64-row chunks (the rows of a
+ *                          chunk as one masked quadratic form), the chunks of
+ *                          a run in parallel, runs one after another.  The
+ *                          workspace holds C states of M (d + 1) floats per
+ *                          head (twice in the backward): it grows with C, and
+ *                          a run takes as many chunks as it holds.  Any
  *                          dtype, map and shape (float32 with d M up to 16384
  *                          included); no dropout (SLIM_EUNSUPPORTED) */
 typedef enum { SLIM_WITHIN_ITER = 0, SLIM_WITHIN_QUADRATIC = 1, SLIM_WITHIN_PS = 2 } slim_within;

@@ -515,54 +515,90 @@ size_t context_bytes(const slim_problem* p) {
   return (size_t)p->B * p->H * (bwd_parts(p) + 1) * state_elems(p) * sizeof(float);
 }
 
-// ---- the explicit prefix-sum within-slice mode: slices one after another;
-// the row kernels run ps_workgroups per head (rows dealt round-robin), the
-// backward restarts from exact states at ps_parts part boundaries (whole
-// slices) and downdates inside a part (eq. 17)
-int ps_slices(const slim_problem* p) { return (int)((p->L + clamp_C(p) - 1) / clamp_C(p)); }
-int ps_workgroups(const slim_problem* p) {
-  const int64_t BH = p->B * p->H;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(64, (1024 + BH - 1) / BH));
+// ---- the explicit prefix-sum mode: states at the boundaries of 64-row
+// chunks, the chunks of a run in parallel, runs one after another.  The
+// workspace grows with C: it is C states per head (twice in the backward),
+// plus parts of fixed size, and a run takes as many chunks as it holds.
+size_t ps_budget(const slim_problem* p, int phase) {
+  const size_t BH = (size_t)p->B * p->H, SZ = state_elems(p);
+  const size_t NW = (size_t)std::max<int64_t>(1, std::min<int64_t>(64, (1024 + (int64_t)BH - 1) / (int64_t)BH));
+  const int C = clamp_C(p);
+  const size_t rows = align256((size_t)C * BH * SZ * sizeof(float)), state = align256(BH * SZ * sizeof(float));
+  if (phase == SLIM_PHASE_FWD) return rows + 2 * state + align256(BH * NW * sizeof(float));
+  const size_t P2 = (size_t)std::min<int64_t>((p->L + C - 1) / C, 64);  // exact restarts
+  return 2 * rows + 4 * state + align256(BH * P2 * SZ * sizeof(float)) + align256(BH * (P2 + 1) * SZ * sizeof(float)) +
+         align256(2 * BH * NW * (size_t)p->M * p->d * sizeof(float));
 }
-int ps_parts(const slim_problem* p) { return std::min(ps_slices(p), 64); }
-struct PsLayout {
-  size_t kmax, U, Gh, s[2], g[2], parts, bounds, dw, total;
+struct PsPlan {
+  int nch, runs;  // chunks per head and run, runs
+  int starts;     // exact states kept at run boundaries (backward, several runs)
+  int nwg;        // workgroups of the backward's passes (each holds a dW partial)
+  size_t S, G, DN, P, dA, shift, carry, gcarry, cshift[2], start, dw, total;
 };
-PsLayout ps_layout(const slim_problem* p, int phase) {
-  PsLayout l;
+PsPlan ps_plan_for(const slim_problem* p, int phase, int nch) {
+  PsPlan l;
   std::memset(&l, 0, sizeof(l));
+  const size_t BH = (size_t)p->B * p->H, SZ = state_elems(p), f = sizeof(float);
+  const int64_t chunks = (p->L + slim::kPsChunk - 1) / slim::kPsChunk;
+  l.nch = nch;
+  l.runs = (int)((chunks + nch - 1) / nch);
+  const size_t n = BH * nch, pitch = (size_t)p->d + 4;
   size_t off = 0;
   auto take = [&](size_t& at, size_t bytes) {
     at = off;
     off += align256(bytes);
   };
-  const size_t BH = (size_t)p->B * p->H, SZ = state_elems(p), NW = ps_workgroups(p);
-  const size_t rows = (size_t)clamp_C(p) * BH * SZ * sizeof(float);  // one slice's states
-  take(l.U, rows);
-  take(l.s[0], BH * SZ * sizeof(float));
-  take(l.s[1], BH * SZ * sizeof(float));
+  take(l.S, n * p->M * pitch * f);
+  if (l.runs > 1) take(l.carry, BH * SZ * f);
   if (phase == SLIM_PHASE_FWD) {
-    take(l.kmax, BH * NW * sizeof(float));
+    if (p->kind == SLIM_FAVOR_PLUS) {
+      take(l.shift, n * f);
+      if (l.runs > 1)
+        for (int i = 0; i < 2; ++i) take(l.cshift[i], BH * f);
+    }
   } else {
-    const size_t P2 = ps_parts(p);
-    take(l.Gh, rows);
-    take(l.g[0], BH * SZ * sizeof(float));
-    take(l.g[1], BH * SZ * sizeof(float));
-    take(l.parts, BH * P2 * SZ * sizeof(float));
-    take(l.bounds, BH * (P2 + 1) * SZ * sizeof(float));
-    take(l.dw, 2 * BH * NW * (size_t)p->M * p->d * sizeof(float));
+    // (one workgroup per compute unit where LDS holds one, else two)
+    l.nwg = (int)std::min<size_t>(p->M == 256 ? 256 : 512, n);
+    take(l.G, n * p->M * pitch * f);
+    take(l.DN, n * slim::kPsChunk * pitch * f);
+    take(l.P, n * slim::kPsChunk * slim::kPsChunk * f);
+    take(l.dA, n * slim::kPsChunk * slim::kPsChunk * f);
+    take(l.gcarry, BH * SZ * f);
+    if (l.runs > 1) {
+      l.starts = std::min(l.runs, 64);
+      take(l.start, l.starts * BH * SZ * f);
+    }
+    take(l.dw, (size_t)l.nwg * p->M * p->d * f);
   }
   l.total = off;
   return l;
 }
+// The most chunks per head and run that the workspace holds, up to 1024 over
+// all heads: four rounds of workgroups, and states that stay in the device's
+// last-level cache between the passes over them.
+PsPlan ps_plan(const slim_problem* p, int phase) {
+  const size_t budget = ps_budget(p, phase);
+  const int64_t chunks = (p->L + slim::kPsChunk - 1) / slim::kPsChunk;
+  int nch = (int)std::min<int64_t>(chunks, std::max<int64_t>(1, 1024 / (p->B * p->H)));
+  // SLIM_PS_CHUNKS (debugging) forces fewer, so that short sequences take several runs
+  const char* env = getenv("SLIM_PS_CHUNKS");
+  if (env != nullptr && atoi(env) > 0) nch = std::min(nch, atoi(env));
+  PsPlan l = ps_plan_for(p, phase, nch);
+  while (nch > 1 && l.total > budget) {
+    nch -= std::max(1, nch / 16);
+    l = ps_plan_for(p, phase, nch);
+  }
+  return l;
+}
+size_t ps_ws_bytes(const slim_problem* p, int phase) { return std::max(ps_budget(p, phase), ps_plan(p, phase).total); }
 
 size_t fwd_ws_bytes(const slim_problem* p) {
-  if (ps(p)) return ps_layout(p, SLIM_PHASE_FWD).total;
+  if (ps(p)) return ps_ws_bytes(p, SLIM_PHASE_FWD);
   if (quad(p)) return quad_fwd_layout(p).total;
   return fwd_layout(p, plan_fwd_segments(p)).total;
 }
 size_t bwd_ws_bytes(const slim_problem* p) {
-  if (ps(p)) return ps_layout(p, SLIM_PHASE_BWD).total;
+  if (ps(p)) return ps_ws_bytes(p, SLIM_PHASE_BWD);
   if (quad(p)) return quad_bwd_layout(p).total;
   return bwd_layout(p, plan_segments(p)).total;
 }
@@ -900,60 +936,49 @@ slim::PsArgs ps_args(const slim_problem* p, const void* Q, const void* K, const 
   a.L = (int)p->L;
   a.d = (int)p->d;
   a.M = (int)p->M;
-  a.C = clamp_C(p);
   a.kind = p->kind == SLIM_FAVOR_PLUS ? slim::kFavor : p->kind == SLIM_RELU ? slim::kRelu : slim::kSquare;
   a.relu_eps = p->relu_eps;
   a.bf16 = p->dtype == SLIM_BF16 ? 1 : 0;
-  a.nslot = ps_workgroups(p);
   return a;
 }
+// run n of a plan: its first row and its chunks
+void ps_run(const slim_problem* p, const PsPlan& l, int n, slim::PsArgs& a) {
+  const int64_t rows = (int64_t)l.nch * slim::kPsChunk;
+  a.row0 = (int)(n * rows);
+  a.nch = (int)((std::min<int64_t>(rows, p->L - a.row0) + slim::kPsChunk - 1) / slim::kPsChunk);
+}
 
-// Forward in the explicit prefix-sum mode (arguments checked by fwd_impl):
-//   (0) FAVOR+: one key shift per head, the largest key exponent over all
-//       rows and the initial state's;
-//   (1) the state before the first slice: the initial state at that shift;
-//   (2) per slice: each row's term g(k)^T [v | 1]; their prefix sums from the
-//       state before the slice, written out for every row (the last is the
-//       state after the slice); the outputs from them.
+// Forward in the explicit prefix-sum mode (arguments checked by fwd_impl),
+// per run of chunks: what each chunk adds, relative to its own largest key
+// exponent (FAVOR+); the state before every chunk relative to the largest
+// exponent so far; the outputs from them.
 int ps_fwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
                 const float* state_in, const float* kshift_in, void* Y, float* state_out, float* kshift_out, char* w,
                 hipStream_t s) {
-  const PsLayout lay = ps_layout(p, SLIM_PHASE_FWD);
+  const PsPlan lay = ps_plan(p, SLIM_PHASE_FWD);
   const bool favor = p->kind == SLIM_FAVOR_PLUS;
-  const int BH = (int)(p->B * p->H), SZ = (int)state_elems(p), C = clamp_C(p), NS = ps_slices(p);
-  const int NW = ps_workgroups(p);
   slim::PsArgs a = ps_args(p, Q, K, V, W);
-  a.U = (float*)(w + lay.U);
+  a.S = (float*)(w + lay.S);
+  a.seg_shift = favor ? (float*)(w + lay.shift) : nullptr;
   a.Y = Y;
-  hipError_t e;
-  if (favor) {
-    a.part = (float*)(w + lay.kmax);
-    e = slim::launch_ps(slim::kPsKmax, a, NW, 0, s);
-    if (e != hipSuccess) return hip_fail(e, "key-maximum launch");
-    e = slim::launch_kshift_reduce(a.part, NW, state_in != nullptr ? kshift_in : nullptr, kshift_out, BH, s);
-    if (e != hipSuccess) return hip_fail(e, "key-shift launch");
-    a.kshift = kshift_out;
-  }
-  float* S[2] = {(float*)(w + lay.s[0]), (float*)(w + lay.s[1])};
-  e = slim::launch_state_combine(state_in, SZ, favor ? kshift_in : nullptr, favor ? kshift_out : nullptr, nullptr, 0,
-                                 1.f, S[0], BH, SZ, s);
-  if (e != hipSuccess) return hip_fail(e, "state launch");
-  e = timed_launch(SLIM_PHASE_FWD, s, [&]() -> hipError_t {
-    int cur = 0;
-    for (int n = 0; n < NS; ++n) {
-      a.row0 = n * C;
-      a.rows = (int)std::min<int64_t>(C, p->L - (int64_t)n * C);
-      const int nwg = std::min(NW, a.rows);
-      hipError_t er = slim::launch_ps(slim::kPsTerms, a, nwg, 0, s);
+  a.S_in = state_in;
+  a.in_stride = state_elems(p);
+  a.in_shift = favor && state_in != nullptr ? kshift_in : nullptr;
+  const hipError_t e = timed_launch(SLIM_PHASE_FWD, s, [&]() -> hipError_t {
+    for (int n = 0; n < lay.runs; ++n) {
+      const bool last = n == lay.runs - 1;
+      ps_run(p, lay, n, a);
+      hipError_t er = slim::launch_ps(slim::kPsSum, a, 0, s);
       if (er != hipSuccess) return er;
-      a.S_in = S[cur];
-      a.in_stride = (size_t)SZ;
-      a.S_out = (n == NS - 1 && state_out != nullptr) ? state_out : S[cur ^ 1];
-      er = slim::launch_ps(slim::kPsScan0, a, 0, 0, s);
+      a.S_out = last ? state_out : (float*)(w + lay.carry);
+      a.shift_out = !favor ? nullptr : last ? kshift_out : (float*)(w + lay.cshift[n & 1]);
+      er = slim::launch_ps(slim::kPsScan0, a, 0, s);
       if (er != hipSuccess) return er;
-      er = slim::launch_ps(slim::kPsOut, a, nwg, 0, s);
+      a.kshift = a.shift_out;
+      er = slim::launch_ps(slim::kPsOut, a, (int)(a.nch * p->B * p->H), s);
       if (er != hipSuccess) return er;
-      cur ^= 1;
+      a.S_in = a.S_out;
+      a.in_shift = a.shift_out;
     }
     return hipSuccess;
   });
@@ -962,116 +987,101 @@ int ps_fwd_impl(const slim_problem* p, const void* Q, const void* K, const void*
 }
 
 // Backward in the explicit prefix-sum mode (arguments checked by slim_bwd):
-//   (1) exact states at the boundaries of P2 parts of whole slices (what
-//       each part's rows add, then their prefix from the initial state);
-//   (2) the slices in reverse: each row's term again, the state before the
-//       slice (the exact one at a part's first slice, else the state after
-//       it minus the slice's terms, eq. 17) and the prefix sums from it; the
-//       queries' gradient and their terms g(q) [dN | dD]; the reverse prefix
-//       sums of those from the cotangent after the slice (the last is the
-//       cotangent before it, eq. 18); the keys' and values' gradient;
+//   (1) several runs: the exact state before up to 64 of them (all, unless
+//       there are more runs);
+//   (2) the runs in reverse: the state before the run (an exact one, else the
+//       state after it minus what it adds, eq. 17) and before its chunks; the
+//       queries' pass; the cotangents after its chunks (eq. 18); the keys';
 //   (3) dstate_in, and dW from the workgroups' partials in a fixed order.
 int ps_bwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
                 const float* state_in, const float* kshift_in, const float* kshift, const void* dY,
                 const float* dstate_out, void* dQ, void* dK, void* dV, float* dW, float* dstate_in, char* w,
                 hipStream_t s) {
-  const PsLayout lay = ps_layout(p, SLIM_PHASE_BWD);
+  const PsPlan lay = ps_plan(p, SLIM_PHASE_BWD);
   const bool favor = p->kind == SLIM_FAVOR_PLUS;
-  const int BH = (int)(p->B * p->H), SZ = (int)state_elems(p), C = clamp_C(p), NS = ps_slices(p);
-  const int NW = ps_workgroups(p), P2 = ps_parts(p);
-  const size_t MD = (size_t)p->M * p->d;
+  const int BH = (int)(p->B * p->H), SZ = (int)state_elems(p);
   slim::PsArgs a = ps_args(p, Q, K, V, W);
   a.kshift = favor ? kshift : nullptr;
-  a.U = (float*)(w + lay.U);
-  a.Gh = (float*)(w + lay.Gh);
+  a.S = (float*)(w + lay.S);
+  a.G = (float*)(w + lay.G);
+  a.DN = (float*)(w + lay.DN);
+  a.P = (float*)(w + lay.P);
+  a.dA = (float*)(w + lay.dA);
   a.dY = dY;
   a.dQ = dQ;
   a.dK = dK;
   a.dV = dV;
-  hipError_t e;
+  a.dW_part = (float*)(w + lay.dw);
+  a.in_stride = (size_t)SZ;
+  float* carry = (float*)(w + lay.carry);
+  float* gcarry = (float*)(w + lay.gcarry);
+  const int R = lay.runs, NP = std::max(lay.starts, 1);
+  auto start_of = [&](int r) { return (float*)(w + lay.start) + (size_t)r * BH * SZ; };
+  auto first_of = [&](int r) { return (int)((int64_t)r * R / NP); };  // first run of part r
+  // the state before run n of the running sums below
+  auto from = [&](const float* S) {
+    a.S_in = S;
+    a.in_shift = favor && S != nullptr && S == state_in ? kshift_in : nullptr;
+  };
   // (1)
-  a.part = (float*)(w + lay.parts);
-  e = slim::launch_ps(slim::kPsSum, a, P2, NS, s);
-  if (e != hipSuccess) return hip_fail(e, "part-sum launch");
-  const float* bounds = (const float*)(w + lay.bounds);
-  {
-    slim::ScanArgs sc;
-    std::memset(&sc, 0, sizeof(sc));
-    sc.seg = a.part;
-    sc.init = state_in;
-    sc.init_shift = favor ? kshift_in : nullptr;
-    sc.shift = favor ? kshift : nullptr;
-    sc.out = (float*)(w + lay.bounds);
-    sc.BH = BH;
-    sc.P = P2;
-    sc.SZ = SZ;
-    sc.favor = favor ? 1 : 0;
-    e = slim::launch_scan_bwd(sc, s);
-    if (e != hipSuccess) return hip_fail(e, "boundary-scan launch");
+  if (R > 1) {
+    from(state_in);
+    const int upto = NP == R ? R - 1 : R;  // (with fewer parts than runs the state after the last is needed too)
+    int r = 1;
+    for (int n = 0; n < upto; ++n) {
+      ps_run(p, lay, n, a);
+      hipError_t e = slim::launch_ps(slim::kPsSum, a, 0, s);
+      if (e != hipSuccess) return hip_fail(e, "run-sum launch");
+      const bool keep = r < NP && first_of(r) == n + 1;
+      a.S_out = keep ? start_of(r) : carry;
+      r += keep;
+      e = slim::launch_ps(slim::kPsScan0, a, 0, s);
+      if (e != hipSuccess) return hip_fail(e, "run-scan launch");
+      from(a.S_out);
+    }
   }
-  float* dw_part = (float*)(w + lay.dw);
-  e = slim::launch_state_combine(nullptr, 0, nullptr, nullptr, nullptr, 0, 1.f, dw_part, 2 * BH * NW, (int)MD, s);
-  if (e != hipSuccess) return hip_fail(e, "dW-partial launch");
-  float* sb[2] = {(float*)(w + lay.s[0]), (float*)(w + lay.s[1])};
-  float* gb[2] = {(float*)(w + lay.g[0]), (float*)(w + lay.g[1])};
-  const size_t bstride = (size_t)(P2 + 1) * SZ;  // between heads of one boundary
-  auto first_of_part = [&](int r) { return (int)((int64_t)r * NS / P2); };
   const float* Gafter = dstate_out;  // nullptr: zero
   // (2)
-  e = timed_launch(SLIM_PHASE_BWD, s, [&]() -> hipError_t {
-    hipError_t er;
-    int r = P2 - 1, cs = 0, cg = 0;
-    const float* Safter = nullptr;
-    for (int n = NS - 1; n >= 0; --n) {
-      while (first_of_part(r) > n) --r;
-      a.row0 = n * C;
-      a.rows = (int)std::min<int64_t>(C, p->L - (int64_t)n * C);
-      const int nwg = std::min(NW, a.rows);
-      er = slim::launch_ps(slim::kPsTerms, a, nwg, 0, s);
+  const hipError_t e = timed_launch(SLIM_PHASE_BWD, s, [&]() -> hipError_t {
+    int r = NP - 1;
+    for (int n = R - 1; n >= 0; --n) {
+      while (first_of(r) > n) --r;
+      ps_run(p, lay, n, a);
+      hipError_t er = slim::launch_ps(slim::kPsSum, a, 0, s);
       if (er != hipSuccess) return er;
-      int mode;
-      if (n == first_of_part(r)) {
-        mode = slim::kPsScan2;
-        a.S_in = bounds + (size_t)r * SZ;
-        a.in_stride = bstride;
-      } else if (n == first_of_part(r + 1) - 1) {
-        mode = slim::kPsScan1;
-        a.S_in = bounds + (size_t)(r + 1) * SZ;
-        a.in_stride = bstride;
+      if (n == first_of(r)) {
+        from(r == 0 ? state_in : start_of(r));
+        a.S_out = nullptr;
+        er = slim::launch_ps(slim::kPsScan0, a, 0, s);
       } else {
-        mode = slim::kPsScan1;
-        a.S_in = Safter;
-        a.in_stride = (size_t)SZ;
+        from(r < NP - 1 && n == first_of(r + 1) - 1 ? start_of(r + 1) : carry);
+        a.S_out = carry;
+        er = slim::launch_ps(slim::kPsScan1, a, 0, s);
       }
-      a.S_out = sb[cs];
-      er = slim::launch_ps(mode, a, 0, 0, s);
       if (er != hipSuccess) return er;
-      Safter = sb[cs];
-      cs ^= 1;
-      a.dW_part = dw_part;
-      er = slim::launch_ps(slim::kPsGq, a, nwg, 0, s);
+      a.first = n == R - 1;
+      er = slim::launch_ps(slim::kPsRows, a, lay.nwg, s);
       if (er != hipSuccess) return er;
       a.G_in = Gafter;
-      a.G_out = gb[cg];
-      er = slim::launch_ps(slim::kPsRscan, a, 0, 0, s);
+      a.G_out = gcarry;
+      er = slim::launch_ps(slim::kPsRscan, a, 0, s);
       if (er != hipSuccess) return er;
-      Gafter = gb[cg];
-      cg ^= 1;
-      a.dW_part = dw_part + (size_t)BH * NW * MD;
-      er = slim::launch_ps(slim::kPsGk, a, nwg, 0, s);
+      Gafter = gcarry;
+      er = slim::launch_ps(slim::kPsKeys, a, lay.nwg, s);
       if (er != hipSuccess) return er;
     }
     return hipSuccess;
   });
   if (e != hipSuccess) return hip_fail(e, "PS-mode backward launches");
   // (3) the cotangent of state_in, relative to kshift_in (FAVOR+ with an initial state)
+  hipError_t er;
   if (dstate_in != nullptr) {
-    e = slim::launch_state_combine(Gafter, SZ, favor ? kshift_in : nullptr, favor ? kshift : nullptr, nullptr, 0, 1.f,
-                                   dstate_in, BH, SZ, s);
-    if (e != hipSuccess) return hip_fail(e, "dstate_in launch");
+    er = slim::launch_state_combine(Gafter, SZ, favor ? kshift_in : nullptr, favor ? kshift : nullptr, nullptr, 0, 1.f,
+                                    dstate_in, BH, SZ, s);
+    if (er != hipSuccess) return hip_fail(er, "dstate_in launch");
   }
-  e = slim::launch_dw_reduce(dw_part, 2 * BH * NW, (int)MD, dW, s);
-  if (e != hipSuccess) return hip_fail(e, "dW-reduction launch");
+  er = slim::launch_dw_reduce(a.dW_part, lay.nwg, (int)(p->M * p->d), dW, s);
+  if (er != hipSuccess) return hip_fail(er, "dW-reduction launch");
   return ok();
 }
 

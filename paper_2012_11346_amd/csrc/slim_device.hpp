@@ -359,6 +359,16 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// exp(x) to about one unit in the last place: the rounding error of x log2(e)
+// enters the result as a first-order term
+__device__ __forceinline__ float exp_f32(float x) {
+  constexpr float kLo = 1.925963033500e-8f;  // log2(e) - float(log2(e))
+  const float t = x * kLog2e;
+  const float e = fmaf(x, kLog2e, -t) + x * kLo;
+  const float r = fast_exp2(t);
+  return x < -150.f ? 0.f : fmaf(r, e * 0.6931471805599453f, r);
+}
+
 // ------------------------------------------------------------- swizzled LDS tiles
 //
 // LDS of gfx950 serves reads from 64 four-byte banks (256 B per clock) and

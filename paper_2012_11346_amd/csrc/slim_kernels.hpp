@@ -252,50 +252,53 @@ hipError_t launch_dw_reduce(const float* part, int n_parts, int n, float* dW, hi
   X(bf16, 64, 16, 32, kSquare) X(bf16, 32, 16, 32, kSquare)                               \
   X(float, 64, 16, 32, kSquare) X(float, 32, 16, 32, kSquare)
 
-// Explicit prefix-sum within-slice mode (slim_ps.hip): the states of every
-// row of a slice written out, then used; streaming kernels for any
-// configuration.  Launch selector `which`:
+// Explicit prefix-sum mode (slim_ps.hip): the states at the boundaries of
+// 64-row chunks written out, then used; float32 for any configuration.
+// Launch selector `which`:
+constexpr int kPsChunk = 64;  // rows of a chunk
 enum PsKernel {
-  kPsKmax = 0,   // part[head][wg]: largest key exponent of the rows a workgroup visits
-  kPsTerms = 1,  // U[head][i] = g(k)^T [v | 1] for the slice's rows
-  kPsScan0 = 2,  // prefix sums of U from S_in (or zero); S_out = the last
-  kPsScan1 = 3,  // S_out = S_in - sum U (eq. 17), then prefix sums from it
-  kPsScan2 = 4,  // S_out = S_in (exact), then prefix sums from it
-  kPsOut = 5,    // Y of the slice's rows from U
-  kPsGq = 6,     // dq, dW (queries), query terms g(q) [dN | dD] -> Gh
-  kPsRscan = 7,  // reverse prefix sums of Gh from G_in (or zero); G_out = the first
-  kPsGk = 8,     // dk, dv, dW (keys) from Gh
-  kPsSum = 9     // part[head][r][m][e]: what the rows of slices [r NS / P2, (r + 1) NS / P2) add
+  kPsSum = 0,    // S[head][chunk] = what the chunk's keys add (relative to kshift, or to their own maximum -> seg_shift)
+  kPsScan0 = 1,  // S: state before every chunk from S_in (or zero); S_out = the state after the last
+  kPsScan1 = 2,  // S_out = S_in - sum S (eq. 17), then as kPsScan0 from it
+  kPsOut = 3,    // Y
+  kPsRows = 4,   // dQ, dW (queries); DN, P, dA for kPsKeys; G[head][chunk] = what the chunk adds to the cotangent
+  kPsRscan = 5,  // G: cotangent after every chunk from G_in (or zero); G_out = the one before the first
+  kPsKeys = 6    // dK, dV, dW (keys)
 };
 struct PsArgs {
   const void* Q;
   const void* K;
   const void* V;
   const void* dY;
-  const float* W;       // [M, d]
-  const float* kshift;  // [B H] FAVOR+ key shift
+  const float* W;         // [M, d]
+  const float* kshift;    // [B H] FAVOR+ key shift, or nullptr
   void* Y;
   void* dQ;
   void* dK;
   void* dV;
-  float* U;             // [B H][C][d + 1][M] the slice's states (or its rows' terms)
-  float* Gh;            // [B H][C][d + 1][M] query terms, then the states' cotangents
-  const float* S_in;    // state of head h at S_in + h in_stride ([m][d + 1])
+  float* S;               // [B H][nch][M][d + 4] chunk sums, then the states before the chunks
+  float* G;               // [B H][nch][M][d + 4] what the chunks add to the cotangent, then the cotangents after them
+  float* DN;              // [B H][nch][64][d + 4] rows [dN | dD]
+  float* P;               // [B H][nch][64][64] g(q) . g(k), lower triangle
+  float* dA;              // [B H][nch][64][64] its cotangent, lower triangle
+  float* seg_shift;       // [B H][nch] the chunks' own key shifts, or nullptr (sums relative to kshift)
+  const float* S_in;      // state of head h at S_in + h in_stride ([m][d + 1]), or nullptr (zero)
   size_t in_stride;
-  float* S_out;         // [B H][M][d + 1]
-  const float* G_in;    // [B H][M][d + 1] cotangent after the slice, or nullptr (zero)
-  float* G_out;         // [B H][M][d + 1] cotangent before the slice
-  float* part;          // kPsKmax: [B H][workgroups]; kPsSum: [B H][P2][M][d + 1]
-  float* dW_part;       // [B H][nslot][M][d], added to (workgroup w of head h: slot h nslot + w)
-  int nslot;
-  int B, H, L, d, M, C;  // C: rows of U and Gh per head (the longest slice)
-  int row0, rows;        // the slice
-  int kind;              // Kind
+  const float* in_shift;  // [B H] key shift of S_in, or nullptr (the common one)
+  float* S_out;           // [B H][M][d + 1], may be nullptr
+  float* shift_out;       // [B H] the common shift found (with seg_shift)
+  const float* G_in;      // [B H][M][d + 1] cotangent after the run, or nullptr (zero)
+  float* G_out;           // [B H][M][d + 1] cotangent before it
+  float* dW_part;         // [workgroups][M][d]
+  int first;              // kPsRows: dW_part is set, not added to
+  int B, H, L, d, M;
+  int row0, nch;          // the run: chunks of rows [row0, row0 + 64 nch), cut at L
+  int kind;               // Kind
   float relu_eps;
-  int bf16;              // element type of Q, K, V, dY, Y, dQ, dK, dV: bf16 (1) or float (0)
+  int bf16;               // element type of Q, K, V, dY, Y, dQ, dK, dV: bf16 (1) or float (0)
 };
-// grid (nwg, B H); extra: kPsSum's slice count
-hipError_t launch_ps(int which, const PsArgs& a, int nwg, int extra, hipStream_t s);
+// nwg: workgroups of kPsOut, kPsRows and kPsKeys
+hipError_t launch_ps(int which, const PsArgs& a, int nwg, hipStream_t s);
 
 // configurations of the whole-slice quadratic form (bf16, 32 or 64 features
 // per wave)

@@ -1,0 +1,852 @@
+// Explicit prefix-sum evaluation (slim_problem.within = SLIM_WITHIN_PS): the
+// prefix sums of eq. 3 are written out and then used, in float32 throughout
+// (float32 matrix cores) for every dtype, map and shape of the problem
+// description, float32 at d M = 16384 included.
+//
+// The prefix sums are kept at the boundaries of 64-row chunks: with the state
+// S before a chunk, row t of it is
+//   [N | D]_t = g(q_t)^T S + sum_{s <= t in the chunk} (g(q_t) . g(k_s)) [v_s | 1],
+// and with the cotangent G after the chunk (the sum of g(q) [dN | dD] over
+// all later rows) a key row s takes
+//   dg(k_s) = G [v_s | 1] + sum_{t >= s in the chunk} dA_ts g(q_t),  dA_ts = dN_t . v_s + dD_t.
+// So every chunk is independent of the others once S and G are known: one
+// workgroup per chunk and no serial walk.  Chunks are processed in runs of as
+// many per head as the workspace holds states for.
+//
+// Kernels: ps_sum (what each chunk adds to the state, and its largest key
+// exponent), ps_scan (state before every chunk, in place), ps_rows (queries:
+// Y; backward: dQ, the queries' dW share, what the chunk adds to the
+// cotangent), ps_rscan (cotangent after every chunk, in place), ps_keys
+// (dK, dV, the keys' dW share).
+//
+// Bound: float32 matrix products, 157 TFLOP/s at most.  64 rows per chunk:
+// the products inside the chunk grow with its length, the traffic of the
+// boundary states falls with it (about 1 KB per row and pass at M = 256,
+// d = 64).  A wave owns 16 FT features of all 64 rows; features stay in
+// registers in the result layout, which is directly an operand of every
+// product that contracts over rows (chunk sums, the triangular products of
+// the backward, dW), and pass through LDS once for those that contract over
+// features.  LDS pitches are 4 modulo 64 words: 16-byte reads along a row and
+// 4-byte reads along a column are then both free of bank conflicts in the
+// k order 4 g + j of the four chained products.
+//
+// At B 1, H 8, L 2048, d 64, M 256, float32, forward and backward, the former
+// form of this mode (the state after every row streamed through HBM) took
+// 6.07 ms; see the launchers' user for the workspace plan.
+#pragma once
+
+#include "slim_common.hpp"
+#include "slim_kernels.hpp"
+
+namespace slim {
+
+namespace ps {
+
+constexpr int kCh = kPsChunk;  // rows of a chunk
+static_assert(kCh == 64, "four 16-row tiles");
+
+template <class T_, int D_, int M_>
+struct PsCfg {
+  typedef T_ T;
+  static constexpr int D = D_, M = M_;
+  static constexpr int NW = M == 64 ? 4 : 8;   // waves
+  static constexpr int TH = NW * 64;           // threads
+  static constexpr int FT = M / (16 * NW);     // 16-feature tiles a wave owns
+  static constexpr int ET = D / 16;            // 16-column tiles of a row
+  static constexpr int KM = M / 16;            // 16-deep blocks of the feature index
+  static constexpr int LP = M + 4;             // LDS pitch of [row][feature]
+  static constexpr int SP = D + 4;             // pitch of states and of [row][dN | dD] rows
+  static constexpr int RG = NW / ET;           // row groups: waves sharing a column tile
+  static constexpr int RPW = 4 / RG;           // row tiles of a wave's output column tile
+  static constexpr int TPR = TH / kCh;         // threads per row of the row sums
+};
+
+// row tile i of group rg (two per group: one early and one late row tile, so
+// that triangular products cost the groups the same)
+template <int RPW>
+__device__ __forceinline__ int row_tile(int rg, int i) {
+  if constexpr (RPW == 1) return rg;
+  else if constexpr (RPW == 2) return i == 0 ? rg : 3 - rg;
+  else return i;
+}
+
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 ld4(const bf16* p) {
+  return __builtin_convertvector(*reinterpret_cast<const bf16x4*>(p), f32x4);
+}
+// p, opaque to the compiler: loads of W inside the chunk loop are then not
+// hoisted out of it (they would hold a hundred registers across the loop)
+__device__ __forceinline__ const float* opaque(const float* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+// the wave's index as a scalar, and the lane coordinates made opaque at the
+// start of a phase (else every lane-dependent address of the chunk loop is
+// formed before it and kept, which spills)
+__device__ __forceinline__ int uniform_wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+__device__ __forceinline__ void refresh(int& g, int& c) { asm volatile("" : "+v"(g), "+v"(c)); }
+// acc += A B over 16 of the contraction index: lane (g, c), entry j <-> k = 4 g + j
+__device__ __forceinline__ f32x4 mma16(f32x4 acc, const f32x4& a, const f32x4& b) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+  return acc;
+}
+// X[k0 + 4 g + j][col0 + c] (pitch ld): an operand contracting over the rows of X
+template <class T>
+__device__ __forceinline__ f32x4 col4(const T* X, int ld, int k0, int col, int g) {
+  f32x4 f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) f[j] = to_f32(X[(k0 + 4 * g + j) * ld + col]);
+  return f;
+}
+
+// A feature is kept as x: the feature itself (FAVOR+) or the logit (ReLU, square)
+__device__ __forceinline__ float feat(int kind, float x, float eps) {
+  return kind == kFavor ? x : kind == kRelu ? fmaxf(x, 0.f) + eps : x * x;
+}
+__device__ __forceinline__ f32x4 feat4(int kind, const f32x4& x, float eps) {
+  f32x4 f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) f[r] = feat(kind, x[r], eps);
+  return f;
+}
+// d loss / d logit from d loss / d feature (the shifts are constants)
+__device__ __forceinline__ float coef_of(int kind, float dphi, float x) {
+  return kind == kFavor ? dphi * x : kind == kRelu ? (x > 0.f ? dphi : 0.f) : 2.f * x * dphi;
+}
+
+// logits of the chunk's 64 rows against the wave's features, result layout
+// [row 16 rt + 4 g + r][feature f0 + 16 ft + c]; nx[rt]: squared norm of row
+// 16 rt + c.  Rows past the last one repeat it.
+template <class G>
+__device__ __forceinline__ void logits(const typename G::T* X, const float* W, int l0, int last, int f0, int g, int c,
+                                       f32x4 (&x)[4][G::FT], float (&nx)[4]) {
+  f32x4 b[G::FT][G::ET];
+#pragma unroll
+  for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+    for (int kk = 0; kk < G::ET; ++kk) b[ft][kk] = ld4(W + (f0 + 16 * ft + c) * G::D + 16 * kk + 4 * g);
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt) {
+    const typename G::T* row = X + (size_t)min(l0 + 16 * rt + c, last) * G::D + 4 * g;
+    f32x4 a[G::ET];
+#pragma unroll
+    for (int kk = 0; kk < G::ET; ++kk) a[kk] = ld4(row + 16 * kk);
+    float s = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < G::ET; ++kk)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s = fmaf(a[kk][j], a[kk][j], s);
+    nx[rt] = wave_sum_over_g(s);
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft) {
+      // (a sum per 16 of the row's columns: the exponential turns a logit's
+      // absolute error into the feature's relative one)
+      f32x4 acc[G::ET];
+#pragma unroll
+      for (int kk = 0; kk < G::ET; ++kk) acc[kk] = mma16(zero4(), a[kk], b[ft][kk]);
+      if constexpr (G::ET == 4) x[rt][ft] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+      else x[rt][ft] = acc[0] + acc[1];
+    }
+  }
+}
+
+// keys: FAVOR+ exponents w.k - |k|^2/2 from the logits
+template <class G>
+__device__ __forceinline__ void key_exponents(f32x4 (&x)[4][G::FT], const float (&nx)[4], int g) {
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float h = 0.5f * __shfl(nx[rt], 4 * g + r, 64);
+#pragma unroll
+      for (int ft = 0; ft < G::FT; ++ft) x[rt][ft][r] -= h;
+    }
+}
+template <class G>
+__device__ __forceinline__ void key_features(f32x4 (&x)[4][G::FT], float shift) {
+  const float ism = rsqrtf((float)G::M);
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[rt][ft][r] = exp_f32(x[rt][ft][r] - shift) * ism;
+}
+// queries: exp(logit - the row's largest logit); red: NW x 64 floats of LDS.  One barrier.
+template <class G>
+__device__ __forceinline__ void query_features(f32x4 (&x)[4][G::FT], float* red, int w, int g, int c) {
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt) {
+    f32x4 mx = x[rt][0];
+#pragma unroll
+    for (int ft = 1; ft < G::FT; ++ft)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], x[rt][ft][r]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mx[r] = wave_max_over_c(mx[r]);
+    if (c == 0) *reinterpret_cast<f32x4*>(red + w * kCh + 16 * rt + 4 * g) = mx;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt) {
+    f32x4 mx = ld4(red + 16 * rt + 4 * g);
+#pragma unroll
+    for (int v = 1; v < G::NW; ++v) {
+      const f32x4 o = ld4(red + v * kCh + 16 * rt + 4 * g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], o[r]);
+    }
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[rt][ft][r] = exp_f32(x[rt][ft][r] - mx[r]);
+  }
+}
+
+// the wave's features of all rows into LDS [row][feature]
+template <class G>
+__device__ __forceinline__ void put_features(float* Z, const f32x4 (&f)[4][G::FT], int f0, int g, int c) {
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Z[(16 * rt + 4 * g + r) * G::LP + f0 + 16 * ft + c] = f[rt][ft][r];
+}
+
+constexpr int kPP = kCh + 4;  // LDS pitch of the [t][s] matrices
+
+// acc[i] (rows 16 rt[i] ..) += the triangular product with P [t][s] in LDS:
+//   TRANS = false: out[t] += sum_{s <= t} P[t][s] b[s]
+//   TRANS = true:  out[s] += sum_{t >= s} P[t][s] b[t]
+// b[kt][j] = row 16 kt + 4 g + j, column c.  The diagonal blocks of P hold
+// zeros outside the triangle.  Where b holds an infinity or NaN, zero times it
+// must not reach the rows outside the triangle: those (rare) products are
+// summed term by term instead.
+template <bool TRANS, int N>
+__device__ __forceinline__ void tri_mma(f32x4 (&acc)[N], const int (&rt)[N], const float* P, const f32x4 (&b)[4], int g,
+                                        int c) {
+  float bad = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bad = fmaf(b[kt][j], 0.f, bad);
+  if (!__any(bad != 0.f)) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (TRANS ? kt >= rt[i] : kt <= rt[i]) {
+          const f32x4 a = TRANS ? col4(P, kPP, 16 * kt, 16 * rt[i] + c, g) : ld4(P + (16 * rt[i] + c) * kPP + 16 * kt + 4 * g);
+          acc[i] = mma16(acc[i], a, b[kt]);
+        }
+    return;
+  }
+  for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float v = __shfl(b[kt][j], 16 * gg + c, 64);
+        const int k = 16 * kt + 4 * gg + j;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int o = 16 * rt[i] + 4 * g + r;
+            if (TRANS ? k >= o : k <= o) acc[i][r] = fmaf(TRANS ? P[k * kPP + o] : P[o * kPP + k], v, acc[i][r]);
+          }
+      }
+}
+
+// lower-triangle 16 x 16 tile i of the chunk's [t][s] matrix
+__device__ __forceinline__ void tri_tile(int i, int& t, int& s) {
+  t = i < 1 ? 0 : i < 3 ? 1 : i < 6 ? 2 : 3;
+  s = i - t * (t + 1) / 2;
+}
+
+// ---- what the rows of each chunk add to the state, [m][e] of pitch D + 4
+// (column D: sum of the features), relative to kshift (given) or to the
+// chunk's own largest key exponent (-> seg_shift).  Grid: (chunks, heads).
+template <class G>
+__global__ __launch_bounds__(G::TH) void ps_sum_kernel(PsArgs a) {
+  typedef typename G::T T;
+  constexpr int D = G::D, SP = G::SP;
+  __shared__ float Vs[kCh * SP];
+  __shared__ float red[G::NW];
+  const int w = uniform_wave(), g = lane_g(), c = lane_c(), f0 = 16 * G::FT * w;
+  const int ch = blockIdx.x, head = blockIdx.y;
+  const int l0 = a.row0 + ch * kCh, n = min(kCh, a.L - l0);
+  const T* K = (const T*)a.K + (size_t)head * a.L * D;
+  const T* V = (const T*)a.V + (size_t)head * a.L * D;
+  for (int i = threadIdx.x; i < kCh * (D / 4); i += G::TH) {
+    const int r = i / (D / 4), q = i % (D / 4);
+    f32x4 v = zero4();
+    if (r < n) v = ld4(V + (size_t)(l0 + r) * D + 4 * q);
+    *reinterpret_cast<f32x4*>(Vs + r * SP + 4 * q) = v;
+  }
+  f32x4 x[4][G::FT];
+  float nx[4];
+  logits<G>(K, a.W, l0, a.L - 1, f0, g, c, x, nx);
+  float shift = 0.f;
+  if (a.kind == kFavor) {
+    key_exponents<G>(x, nx, g);
+    if (a.seg_shift != nullptr) {
+      float mx = -INFINITY;  // (rows past the end repeat the last one)
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, x[rt][ft][r]);
+      mx = wave_max(mx);
+      if (lane_id() == 0) red[w] = mx;
+      __syncthreads();
+      shift = red[0];
+#pragma unroll
+      for (int v = 1; v < G::NW; ++v) shift = fmaxf(shift, red[v]);
+      if (threadIdx.x == 0) a.seg_shift[(size_t)head * a.nch + ch] = shift;
+    } else {
+      shift = a.kshift[head];
+    }
+    key_features<G>(x, shift);
+  }
+#pragma unroll
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        x[rt][ft][r] = 16 * rt + 4 * g + r < n ? feat(a.kind, x[rt][ft][r], a.relu_eps) : 0.f;
+  __syncthreads();
+  float* out = a.S + ((size_t)head * a.nch + ch) * G::M * SP;
+#pragma unroll
+  for (int ft = 0; ft < G::FT; ++ft) {
+    float z = 0.f;
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) z += (x[rt][ft][0] + x[rt][ft][1]) + (x[rt][ft][2] + x[rt][ft][3]);
+    z = wave_sum_over_g(z);
+    if (g == 0) out[(f0 + 16 * ft + c) * SP + D] = z;
+  }
+#pragma unroll
+  for (int et = 0; et < G::ET; ++et) {
+    f32x4 acc[G::FT];
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft) acc[ft] = zero4();
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      const f32x4 b = col4(Vs, SP, 16 * kt, 16 * et + c, g);
+#pragma unroll
+      for (int ft = 0; ft < G::FT; ++ft) acc[ft] = mma16(acc[ft], x[kt][ft], b);
+    }
+#pragma unroll
+    for (int ft = 0; ft < G::FT; ++ft)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(f0 + 16 * ft + 4 * g + r) * SP + 16 * et + c] = acc[ft][r];
+  }
+}
+
+// ---- the queries of a chunk, from the state S before it.  Forward: Y.
+// BWD: dQ; the rows [dN | dD] and the matrices P = g(Q) g(K)^T and dA (lower
+// triangle), which the keys' pass reads; what the chunk adds to the cotangent
+// (g(Q)^T [dN | dD] -> G); the queries' share of dW, summed over the chunks a
+// workgroup visits.  Grid: any number of workgroups.
+template <class G, bool BWD>
+__global__ __launch_bounds__(G::TH) void ps_rows_kernel(PsArgs a) {
+  typedef typename G::T T;
+  constexpr int D = G::D, M = G::M, FT = G::FT, ET = G::ET, SP = G::SP, LP = G::LP, RPW = G::RPW, TPR = G::TPR;
+  __shared__ float PQ[kCh * LP];  // g(Q) [row][feature], then [dN] [row][e] of pitch SP
+  __shared__ float PK[kCh * LP];  // g(K), then the queries' logit cotangents
+  __shared__ float PS[kCh * kPP]; // P, then dA
+  __shared__ float zs[M];         // column D of S
+  __shared__ float red[G::NW * kCh];
+  __shared__ float den[kCh], ddv[kCh];
+  const int w = uniform_wave(), f0 = 16 * FT * w;
+  int g = lane_g(), c = lane_c();
+  const int et = w % ET, rg = w / ET;
+  int rts[RPW];
+#pragma unroll
+  for (int i = 0; i < RPW; ++i) rts[i] = row_tile<RPW>(rg, i);
+  f32x4 dw[FT][ET];
+  if constexpr (BWD) {
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+      for (int e = 0; e < ET; ++e) dw[ft][e] = zero4();
+  }
+  const int total = a.nch * a.B * a.H;
+  for (int idx = blockIdx.x; idx < total; idx += gridDim.x) {
+    const int head = idx / a.nch, ch = idx - head * a.nch;
+    const int l0 = a.row0 + ch * kCh, n = min(kCh, a.L - l0);
+    const size_t base = (size_t)head * a.L * D;
+    const T* Q = (const T*)a.Q + base;
+    const T* V = (const T*)a.V + base;
+    const float* S = a.S + (size_t)idx * M * SP;
+    for (int m = threadIdx.x; m < M; m += G::TH) zs[m] = S[m * SP + D];
+    const float* W = opaque(a.W);
+    refresh(g, c);
+    // this wave's columns of S, for the outputs (the backward is short of
+    // registers and reads them where they are used)
+    f32x4 sb[BWD ? 1 : G::KM];
+    if constexpr (!BWD) {
+#pragma unroll
+      for (int k = 0; k < G::KM; ++k) sb[k] = col4(S, SP, 16 * k, 16 * et + c, g);
+    }
+    f32x4 xq[4][FT], xk[4][FT];
+    {
+      float nx[4];
+      logits<G>((const T*)a.K + base, W, l0, a.L - 1, f0, g, c, xk, nx);
+      if (a.kind == kFavor) {
+        key_exponents<G>(xk, nx, g);
+        key_features<G>(xk, a.kshift[head]);
+      }
+      logits<G>(Q, W, l0, a.L - 1, f0, g, c, xq, nx);
+      if (a.kind == kFavor) query_features<G>(xq, red, w, g, c);
+    }
+    f32x4 fk[4][FT];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) fk[rt][ft] = feat4(a.kind, xk[rt][ft], a.relu_eps);
+    put_features<G>(PK, fk, f0, g, c);
+    {
+      f32x4 fq[4][FT];
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) fq[rt][ft] = feat4(a.kind, xq[rt][ft], a.relu_eps);
+      put_features<G>(PQ, fq, f0, g, c);
+    }
+    __syncthreads();
+    // N from the state before the chunk
+    f32x4 acc[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) acc[i] = zero4();
+    if constexpr (!BWD) {
+#pragma unroll
+      for (int k = 0; k < G::KM; ++k)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) acc[i] = mma16(acc[i], ld4(PQ + (16 * rts[i] + c) * LP + 16 * k + 4 * g), sb[k]);
+    } else {
+#pragma unroll 4
+      for (int k = 0; k < G::KM; ++k) {
+        const f32x4 b = col4(S, SP, 16 * k, 16 * et + c, g);
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) acc[i] = mma16(acc[i], ld4(PQ + (16 * rts[i] + c) * LP + 16 * k + 4 * g), b);
+      }
+    }
+    // P, lower triangle
+    for (int i = w; i < 10; i += G::NW) {
+      int t, s;
+      tri_tile(i, t, s);
+      f32x4 p0 = zero4(), p1 = zero4();
+#pragma unroll 2
+      for (int k = 0; k < G::KM; k += 2) {
+        p0 = mma16(p0, ld4(PQ + (16 * t + c) * LP + 16 * k + 4 * g), ld4(PK + (16 * s + c) * LP + 16 * k + 4 * g));
+        p1 = mma16(p1, ld4(PQ + (16 * t + c) * LP + 16 * k + 16 + 4 * g), ld4(PK + (16 * s + c) * LP + 16 * k + 16 + 4 * g));
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int tt = 16 * t + 4 * g + r, sc = 16 * s + c;
+        const float p = sc <= tt ? p0[r] + p1[r] : 0.f;
+        PS[tt * kPP + sc] = p;
+        if constexpr (BWD) a.P[((size_t)idx * kCh + tt) * kCh + sc] = p;
+      }
+    }
+    refresh(g, c);
+    // D from the state, TPR threads per row
+    const int drow = threadIdx.x / TPR, dpart = threadIdx.x % TPR;
+    float dsum = 0.f;
+#pragma unroll 4
+    for (int k = dpart; k < M / 4; k += TPR) {
+      const f32x4 p = ld4(PQ + drow * LP + 4 * k), z = ld4(zs + 4 * k);
+      dsum += (p[0] * z[0] + p[1] * z[1]) + (p[2] * z[2] + p[3] * z[3]);
+    }
+    f32x4 vb[4];
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int s = 16 * kt + 4 * g + j;
+        vb[kt][j] = to_f32(V[(size_t)min(l0 + s, a.L - 1) * D + 16 * et + c]);
+      }
+    __syncthreads();
+    {
+      float s2 = 0.f;
+      for (int s = dpart; s <= drow; s += TPR) s2 += PS[drow * kPP + s];
+      dsum = sum_lane_group<TPR>(dsum + s2);
+      if (dpart == 0) den[drow] = dsum;
+    }
+    tri_mma<false>(acc, rts, PS, vb, g, c);
+    __syncthreads();
+    if constexpr (!BWD) {
+      T* Y = (T*)a.Y + base;
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int t = 16 * rts[i] + 4 * g + r;
+          if (t < n) Y[(size_t)(l0 + t) * D + 16 * et + c] = cvt<T>(acc[i][r] / den[t]);
+        }
+    } else {
+      refresh(g, c);
+      const T* dY = (const T*)a.dY + base;
+      float* DN = a.DN + (size_t)idx * kCh * SP;
+      float* dNs = PQ;
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) {
+        f32x4 dot;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int t = 16 * rts[i] + 4 * g + r;
+          const float dy = t < n ? to_f32(dY[(size_t)(l0 + t) * D + 16 * et + c]) : 0.f;
+          const float dn = t < n ? dy / den[t] : 0.f;
+          dot[r] = wave_sum_over_c(t < n ? dy * acc[i][r] : 0.f);
+          dNs[t * SP + 16 * et + c] = dn;
+          DN[t * SP + 16 * et + c] = dn;
+        }
+        if (c == 0) *reinterpret_cast<f32x4*>(red + et * kCh + 16 * rts[i] + 4 * g) = dot;
+      }
+      __syncthreads();
+      if (threadIdx.x < kCh) {
+        const int t = threadIdx.x;
+        float s = red[t];
+#pragma unroll
+        for (int e = 1; e < ET; ++e) s += red[e * kCh + t];
+        // dD = -dY . N / D^2
+        const float dd = t < n ? -s / (den[t] * den[t]) : 0.f;
+        ddv[t] = dd;
+        DN[t * SP + D] = dd;
+      }
+      __syncthreads();
+      refresh(g, c);
+      // dA, lower triangle
+      for (int i = w; i < 10; i += G::NW) {
+        int t, s;
+        tri_tile(i, t, s);
+        f32x4 p = ld4(ddv + 16 * t + 4 * g);
+#pragma unroll
+        for (int k = 0; k < ET; ++k)
+          p = mma16(p, ld4(dNs + (16 * t + c) * SP + 16 * k + 4 * g),
+                    ld4(V + (size_t)min(l0 + 16 * s + c, a.L - 1) * D + 16 * k + 4 * g));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int tt = 16 * t + 4 * g + r, sc = 16 * s + c;
+          const float da = sc <= tt && tt < n ? p[r] : 0.f;
+          PS[tt * kPP + sc] = da;
+          a.dA[((size_t)idx * kCh + tt) * kCh + sc] = da;
+        }
+      }
+      __syncthreads();
+      refresh(g, c);
+      // dg(q) for the wave's features, and from it the logits' cotangents
+      f32x4 cf[4][FT];
+      const int all[4] = {0, 1, 2, 3};
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) {
+        f32x4 dp[4];
+        const float z = zs[f0 + 16 * ft + c];
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+          const f32x4 dd = ld4(ddv + 16 * rt + 4 * g);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dp[rt][r] = dd[r] * z;
+        }
+#pragma unroll
+        for (int k = 0; k < ET; ++k) {
+          const f32x4 b = ld4(S + (f0 + 16 * ft + c) * SP + 16 * k + 4 * g);
+#pragma unroll
+          for (int rt = 0; rt < 4; ++rt) dp[rt] = mma16(dp[rt], ld4(dNs + (16 * rt + c) * SP + 16 * k + 4 * g), b);
+        }
+        const f32x4 b[4] = {fk[0][ft], fk[1][ft], fk[2][ft], fk[3][ft]};
+        tri_mma<false>(dp, all, PS, b, g, c);
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            cf[rt][ft][r] = 16 * rt + 4 * g + r < n ? coef_of(a.kind, dp[rt][r], xq[rt][ft][r]) : 0.f;
+      }
+      put_features<G>(PK, cf, f0, g, c);
+      refresh(g, c);
+      // what the chunk adds to the cotangent, and to dW
+      float* out = a.G + (size_t)idx * M * SP;
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) xq[rt][ft] = feat4(a.kind, xq[rt][ft], a.relu_eps);
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) {
+        float z = 0.f;
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+          const f32x4 dd = ld4(ddv + 16 * rt + 4 * g);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) z = fmaf(xq[rt][ft][r], dd[r], z);
+        }
+        z = wave_sum_over_g(z);
+        if (g == 0) out[(f0 + 16 * ft + c) * SP + D] = z;
+      }
+#pragma unroll
+      for (int e = 0; e < ET; ++e) {
+        f32x4 gs[FT];
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) gs[ft] = zero4();
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+          const f32x4 b = col4(dNs, SP, 16 * kt, 16 * e + c, g);
+          f32x4 q;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            q[j] = to_f32(Q[(size_t)min(l0 + 16 * kt + 4 * g + j, a.L - 1) * D + 16 * e + c]);
+#pragma unroll
+          for (int ft = 0; ft < FT; ++ft) {
+            gs[ft] = mma16(gs[ft], xq[kt][ft], b);
+            dw[ft][e] = mma16(dw[ft][e], cf[kt][ft], q);
+          }
+        }
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) out[(f0 + 16 * ft + 4 * g + r) * SP + 16 * e + c] = gs[ft][r];
+      }
+      __syncthreads();
+      // dq = coef W (FAVOR+: Y does not change with the length of g(q), so the
+      // sum of a row's coefficients, which the norm term multiplies, is zero)
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) acc[i] = zero4();
+      W = opaque(W);
+      refresh(g, c);
+#pragma unroll 4
+      for (int k = 0; k < G::KM; ++k) {
+        const f32x4 b = col4(W, D, 16 * k, 16 * et + c, g);
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) acc[i] = mma16(acc[i], ld4(PK + (16 * rts[i] + c) * LP + 16 * k + 4 * g), b);
+      }
+      T* dQ = (T*)a.dQ + base;
+#pragma unroll
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int t = 16 * rts[i] + 4 * g + r;
+          if (t < n) dQ[(size_t)(l0 + t) * D + 16 * et + c] = cvt<T>(acc[i][r]);
+        }
+    }
+    __syncthreads();
+  }
+  if constexpr (BWD) {
+    float* p = a.dW_part + (size_t)blockIdx.x * M * D;
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+      for (int e = 0; e < ET; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float* q = p + (f0 + 16 * ft + 4 * g + r) * D + 16 * e + c;
+          *q = a.first ? dw[ft][e][r] : *q + dw[ft][e][r];
+        }
+  }
+}
+
+// ---- the keys and values of a chunk, from the cotangent G after it and the
+// rows and matrices the queries' pass wrote: dK, dV and the keys' share of
+// dW (added to the queries').
+template <class G>
+__global__ __launch_bounds__(G::TH) void ps_keys_kernel(PsArgs a) {
+  typedef typename G::T T;
+  constexpr int D = G::D, M = G::M, FT = G::FT, ET = G::ET, SP = G::SP, LP = G::LP, RPW = G::RPW;
+  __shared__ float PK[kCh * LP];   // g(K), then the keys' logit cotangents
+  __shared__ float PS[kCh * kPP];  // P
+  __shared__ float DA[kCh * kPP];  // dA
+  __shared__ float red[G::NW * kCh];
+  const int w = uniform_wave(), f0 = 16 * FT * w;
+  int g = lane_g(), c = lane_c();
+  const int et = w % ET, rg = w / ET;
+  int rts[RPW];
+#pragma unroll
+  for (int i = 0; i < RPW; ++i) rts[i] = row_tile<RPW>(rg, i);
+  f32x4 dw[FT][ET];
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int e = 0; e < ET; ++e) dw[ft][e] = zero4();
+  const int total = a.nch * a.B * a.H;
+  for (int idx = blockIdx.x; idx < total; idx += gridDim.x) {
+    const int head = idx / a.nch, ch = idx - head * a.nch;
+    const int l0 = a.row0 + ch * kCh, n = min(kCh, a.L - l0);
+    const size_t base = (size_t)head * a.L * D;
+    const T* K = (const T*)a.K + base;
+    const T* V = (const T*)a.V + base;
+    const float* Gc = a.G + (size_t)idx * M * SP;
+    const float* DN = a.DN + (size_t)idx * kCh * SP;
+    for (int i = threadIdx.x; i < kCh * kCh / 4; i += G::TH) {
+      const int t = i / (kCh / 4), q = i % (kCh / 4);
+      *reinterpret_cast<f32x4*>(PS + t * kPP + 4 * q) = ld4(a.P + ((size_t)idx * kCh + t) * kCh + 4 * q);
+      *reinterpret_cast<f32x4*>(DA + t * kPP + 4 * q) = ld4(a.dA + ((size_t)idx * kCh + t) * kCh + 4 * q);
+    }
+    const float* W = opaque(a.W);
+    refresh(g, c);
+    f32x4 xq[4][FT], xk[4][FT];
+    float nx[4];
+    logits<G>((const T*)a.Q + base, W, l0, a.L - 1, f0, g, c, xq, nx);
+    if (a.kind == kFavor) query_features<G>(xq, red, w, g, c);
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) xq[rt][ft] = feat4(a.kind, xq[rt][ft], a.relu_eps);
+    logits<G>(K, W, l0, a.L - 1, f0, g, c, xk, nx);
+    if (a.kind == kFavor) {
+      key_exponents<G>(xk, nx, g);
+      key_features<G>(xk, a.kshift[head]);
+    }
+    {
+      f32x4 fk[4][FT];
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) fk[rt][ft] = feat4(a.kind, xk[rt][ft], a.relu_eps);
+      put_features<G>(PK, fk, f0, g, c);
+    }
+    __syncthreads();
+    refresh(g, c);
+    // dV
+    f32x4 acc[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) acc[i] = zero4();
+#pragma unroll 4
+    for (int k = 0; k < G::KM; ++k) {
+      const f32x4 b = col4(Gc, SP, 16 * k, 16 * et + c, g);
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) acc[i] = mma16(acc[i], ld4(PK + (16 * rts[i] + c) * LP + 16 * k + 4 * g), b);
+    }
+    {
+      f32x4 nb[4];
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) nb[kt] = col4(DN, SP, 16 * kt, 16 * et + c, g);
+      tri_mma<true>(acc, rts, PS, nb, g, c);
+    }
+    T* dV = (T*)a.dV + base;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = 16 * rts[i] + 4 * g + r;
+        if (s < n) dV[(size_t)(l0 + s) * D + 16 * et + c] = cvt<T>(acc[i][r]);
+      }
+    refresh(g, c);
+    // dg(k) for the wave's features, and from it the logits' cotangents
+    f32x4 cf[4][FT];
+    const int all[4] = {0, 1, 2, 3};
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft) {
+      f32x4 dp[4];
+      const float z = Gc[(f0 + 16 * ft + c) * SP + D];
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt) dp[rt] = f32x4{z, z, z, z};
+#pragma unroll
+      for (int k = 0; k < ET; ++k) {
+        const f32x4 b = ld4(Gc + (f0 + 16 * ft + c) * SP + 16 * k + 4 * g);
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt)
+          dp[rt] = mma16(dp[rt], ld4(V + (size_t)min(l0 + 16 * rt + c, a.L - 1) * D + 16 * k + 4 * g), b);
+      }
+      const f32x4 b[4] = {xq[0][ft], xq[1][ft], xq[2][ft], xq[3][ft]};
+      tri_mma<true>(dp, all, DA, b, g, c);
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          cf[rt][ft][r] = 16 * rt + 4 * g + r < n ? coef_of(a.kind, dp[rt][r], xk[rt][ft][r]) : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < ET; ++e)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        f32x4 kv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) kv[j] = to_f32(K[(size_t)min(l0 + 16 * kt + 4 * g + j, a.L - 1) * D + 16 * e + c]);
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) dw[ft][e] = mma16(dw[ft][e], cf[kt][ft], kv);
+      }
+    __syncthreads();  // (red and PK are free)
+    if (a.kind == kFavor) {
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt) {
+        f32x4 s = cf[rt][0];
+#pragma unroll
+        for (int ft = 1; ft < FT; ++ft)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[r] += cf[rt][ft][r];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = wave_sum_over_c(s[r]);
+        if (c == 0) *reinterpret_cast<f32x4*>(red + w * kCh + 16 * rt + 4 * g) = s;
+      }
+    }
+    put_features<G>(PK, cf, f0, g, c);
+    __syncthreads();
+    // dk = coef W - k sum(coef) (the norm term: FAVOR+)
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) acc[i] = zero4();
+    W = opaque(W);
+    refresh(g, c);
+#pragma unroll 4
+    for (int k = 0; k < G::KM; ++k) {
+      const f32x4 b = col4(W, D, 16 * k, 16 * et + c, g);
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) acc[i] = mma16(acc[i], ld4(PK + (16 * rts[i] + c) * LP + 16 * k + 4 * g), b);
+    }
+    T* dK = (T*)a.dK + base;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      f32x4 cs = zero4();
+      if (a.kind == kFavor) {
+#pragma unroll
+        for (int v = 0; v < G::NW; ++v) {
+          const f32x4 o = ld4(red + v * kCh + 16 * rts[i] + 4 * g);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) cs[r] += o[r];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = 16 * rts[i] + 4 * g + r;
+        if (s >= n) continue;
+        const size_t at = (size_t)(l0 + s) * D + 16 * et + c;
+        float v = acc[i][r];
+        if (a.kind == kFavor) v = fmaf(-to_f32(K[at]), cs[r], v);
+        dK[at] = cvt<T>(v);
+      }
+    }
+    __syncthreads();
+  }
+  float* p = a.dW_part + (size_t)blockIdx.x * M * D;
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int e = 0; e < ET; ++e)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[(f0 + 16 * ft + 4 * g + r) * D + 16 * e + c] += dw[ft][e][r];
+}
+
+// ---- launcher of one configuration
+template <class G>
+hipError_t launch_rows_g(int which, const PsArgs& a, int nwg, hipStream_t s) {
+  const dim3 b(G::TH);
+  switch (which) {
+    case kPsSum: hipLaunchKernelGGL((ps_sum_kernel<G>), dim3(a.nch, a.B * a.H), b, 0, s, a); break;
+    case kPsOut: hipLaunchKernelGGL((ps_rows_kernel<G, false>), dim3(nwg), b, 0, s, a); break;
+    case kPsRows: hipLaunchKernelGGL((ps_rows_kernel<G, true>), dim3(nwg), b, 0, s, a); break;
+    case kPsKeys: hipLaunchKernelGGL((ps_keys_kernel<G>), dim3(nwg), b, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+template <class T, int D>
+hipError_t launch_rows_t(int which, const PsArgs& a, int nwg, hipStream_t s) {
+  if (a.M == 256) return launch_rows_g<PsCfg<T, D, 256>>(which, a, nwg, s);
+  if (a.M == 128) return launch_rows_g<PsCfg<T, D, 128>>(which, a, nwg, s);
+  return launch_rows_g<PsCfg<T, D, 64>>(which, a, nwg, s);
+}
+
+}  // namespace ps
+}  // namespace slim

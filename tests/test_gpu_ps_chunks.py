@@ -1,0 +1,92 @@
+"""The prefix-sum mode's chunks and runs at their edges: rows around the
+64-row chunk, several runs per call (forced with SLIM_PS_CHUNKS), more runs
+than exact restarts (more than 64: states recovered by eq. 17), every
+(d, M, dtype) instantiation, and infinities and NaN, which reach exactly the
+rows the definition makes depend on them (a chunk's triangular products must
+not multiply them by zero).
+
+Bars: 1e-5 max-relative for float32 and 2e-2 for bf16, as everywhere.
+Downdated states: a run's start is the state after it minus what it adds, so
+each of the at most two downdates per part here adds one rounding of the
+state after it (2^-24 of it); the plain float32 bar holds."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth import Workload, make_inputs
+from tests.gpu_common import TOL, dev, host64, need_gpu, report
+
+pytestmark = pytest.mark.gpu
+
+# B, H, L, d, M, C, dtype, kind, chunks per run (0: the plan's)
+CASES = [
+    (1, 2, 1, 64, 256, 1, "f32", "favor+", 0),
+    (1, 1, 63, 64, 128, 16, "f32", "favor+", 0),
+    (2, 1, 64, 32, 256, 64, "f32", "relu", 0),
+    (1, 3, 65, 64, 64, 9, "f32", "favor+", 0),
+    (1, 2, 300, 64, 256, 64, "f32", "favor+", 2),
+    (2, 2, 257, 32, 128, 300, "bf16", "favor+", 1),
+    (1, 2, 200, 64, 64, 32, "f32", "square", 1),
+    (1, 1, 129, 32, 64, 1, "bf16", "relu", 0),
+    (1, 1, 150, 64, 128, 20, "bf16", "relu", 2),
+    (1, 1, 64 * 66 + 5, 32, 64, 64, "f32", "favor+", 1),  # 67 runs, 64 restarts
+]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_chunks_and_runs(i, monkeypatch):
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    B, H, L, d, M, C, dtype, kind, run = CASES[i]
+    print(f"[ps chunks] case={i} {CASES[i]}", flush=True)
+    if run:
+        monkeypatch.setenv("SLIM_PS_CHUNKS", str(run))
+    x = make_inputs(Workload(f"psc{i}", 960 + i, B, H, L, d, M, (C,), dtype, kind))
+    if kind == "square":
+        x["W"] = torch.eye(64, dtype=torch.float32)
+    Q, K, V, W, dY = (dev(x[k]) for k in ("Q", "K", "V", "W", "dY"))
+    Y, st, ks = slim.fwd(Q, K, V, W, C, kind, within="ps")
+    g = slim.bwd(Q, K, V, W, dY, C, ks, kind, within="ps", want_dstate_in=True)
+    torch.cuda.synchronize()
+    tol = TOL[dtype]
+    report("Y", host64(Y), O.attention_forward(x["Q"], x["K"], x["V"], x["W"], kind), tol)
+    _, stref = O.slim_forward(x["Q"], x["K"], x["V"], x["W"], C, kind, within="quadratic")
+    s = host64(st)
+    if kind == "favor+":
+        s = s * np.exp(host64(ks))[:, :, None, None]
+    report("state_out", s, stref, tol)
+    ref = O.attention_backward(x["Q"], x["K"], x["V"], x["W"], x["dY"], kind)
+    for n, a, r in zip(("dQ", "dK", "dV", "dW"), g[:4], ref):
+        if np.max(np.abs(r)) < 1e-9:  # one row: Y = V whatever Q and K are
+            assert np.max(np.abs(host64(a))) <= 1e-5, n
+            continue
+        report(n, host64(a), r, tol)
+
+
+@pytest.mark.parametrize("what", ["V", "Q"])
+def test_not_finite(what):
+    """One infinity in V reaches its column of Y from its row on and nothing
+    before; one NaN in Q reaches dK and dV of its row and the earlier ones
+    and nothing after."""
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    B, H, L, d, M, C, r = 1, 2, 200, 64, 256, 50, 91
+    print(f"[ps chunks] not finite in {what}", flush=True)
+    x = make_inputs(Workload("psnf", 975, B, H, L, d, M, (C,), "f32", "favor+"))
+    x[what][0, 0, r, 7] = float("inf") if what == "V" else float("nan")
+    Q, K, V, W, dY = (dev(x[k]) for k in ("Q", "K", "V", "W", "dY"))
+    Y, _, ks = slim.fwd(Q, K, V, W, C, within="ps")
+    g = slim.bwd(Q, K, V, W, dY, C, ks, within="ps")
+    torch.cuda.synchronize()
+    Y, dK, dV = Y.cpu(), g[1].cpu(), g[2].cpu()
+    if what == "V":
+        assert not torch.isfinite(Y[0, 0, r:, 7]).any() and torch.isfinite(Y[0, 0, :r]).all()
+        assert torch.isfinite(Y[0, 0, :, :7]).all()
+    else:
+        assert torch.isnan(dV[0, 0, : r + 1]).all() and torch.isfinite(dV[0, 0, r + 1 :]).all()
+        assert torch.isnan(dK[0, 0, : r + 1]).all() and torch.isfinite(dK[0, 0, r + 1 :]).all()
+    assert torch.isfinite(Y[0, 1]).all() and torch.isfinite(dK[0, 1]).all() and torch.isfinite(dV[0, 1]).all()
