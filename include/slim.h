@@ -78,10 +78,15 @@ typedef enum { SLIM_PHASE_FWD = 0, SLIM_PHASE_BWD = 1 } slim_phase;
  *                          leave the chip; the work per row does not depend
  *                          on C)
  *   SLIM_WITHIN_QUADRATIC  the slice as one masked quadratic form (eq. 2
- *                          inside the slice), slices one after another and the
- *                          32-row tiles of a slice in parallel: the work per
- *                          row grows with C (bf16 problems with M of 128 or
- *                          256, FAVOR+ or ReLU)
+ *                          inside the slice): the work per row grows with C.
+ *                          The slices of a group run in parallel, groups one
+ *                          after another; slices are rounded up to whole
+ *                          256-row blocks, and slices of more rows than a
+ *                          group holds (131072 over the heads; fewer on the
+ *                          fixed scratch of slim_fwd_noalloc) are taken in
+ *                          pieces, which changes nothing but the rounding
+ *                          (bf16 problems with M of 128 or 256, FAVOR+ or
+ *                          ReLU)
  *   SLIM_WITHIN_PS         the explicit prefix sum the paper benchmarks as
  *                          "PS": prefix sums written out, then used, here at
  *                          the boundaries of 64-row chunks (the rows of a
@@ -283,7 +288,7 @@ int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V,
  * around the launch of its main walk kernel (the forward walk that writes Y,
  * the reverse walk of the backward), so the caller can read that kernel's
  * own duration; the other launches of the call fall outside the pair (in the
- * quadratic within-slice mode the pair brackets the launches of all
+ * quadratic and prefix-sum modes the pair brackets the launches of all
  * slices).  The setting is consumed by that one call.  NULL for both clears
  * it.
  * Returns SLIM_OK, or SLIM_EINVAL for an unknown phase or only one NULL. */

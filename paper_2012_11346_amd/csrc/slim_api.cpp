@@ -322,90 +322,88 @@ BwdLayout bwd_layout(const slim_problem* p, int P) {
   return l;
 }
 
-// ---- the quadratic within-slice mode: slices one after another, the 32-row
-// tiles of a slice in parallel
-int quad_slices(const slim_problem* p) { return (int)((p->L + clamp_C(p) - 1) / clamp_C(p)); }
-int quad_tiles(const slim_problem* p) { return (clamp_C(p) + kTileRows - 1) / kTileRows; }
-// workgroups per head of the per-slice passes: one per query (key) tile, up
-// to about eight per compute unit over all heads.  SLIM_QUAD_WORKGROUPS
-// (debugging) forces fewer, so that workgroups take several tiles.
-int quad_workgroups(const slim_problem* p) {
-  int64_t n = std::min<int64_t>(quad_tiles(p), 2048 / (p->B * p->H));
-  const char* env = getenv("SLIM_QUAD_WORKGROUPS");
-  if (env != nullptr && atoi(env) > 0) n = std::min<int64_t>(n, atoi(env));
-  return (int)std::max<int64_t>(1, n);
-}
-// parts of the per-slice key sums, and of the key maxima over the whole head
-int quad_sum_parts(const slim_problem* p) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>((quad_tiles(p) + 3) / 4, kTargetWorkgroupsForward / (p->B * p->H)));
-}
+// ---- the quadratic within-slice mode.  The slices of a group run in
+// parallel, the groups of a range of heads one after another.
+//   C: the slices it works on.  Any partition of the rows is exact, so the
+//      problem's slice length is rounded up to whole 256-row blocks (512-row
+//      parts beyond 512), and slices of more rows than a group holds over its
+//      heads are taken in pieces;
+//   rows: rows of a group over its heads (features take 4 M bytes each).
+constexpr int kQuadRows = 131072;  // preferred: 512 blocks, two rounds of workgroups
+constexpr int kQuadHeads = 512;   // heads of a range at most
+constexpr int kQuadStarts = 16;    // exact states kept before groups; the others are downdated (eq. 17)
+struct QuadPlan {
+  int heads, C, part_rows, n;  // heads of a range; slice and part length; rows of a group
+  int groups, starts, nwg, max_parts;
+  size_t wfrag, wtab, kmax, part, FK, FQ, ST, carry, start, gcarry, GT, DN, dD, gpart, dw, total;
+};
+size_t wfrag_bytes_of(const slim_problem* p);
 int quad_max_parts(const slim_problem* p) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(std::max(1, count_tiles(p) / 4), kTargetWorkgroupsForward / (p->B * p->H)));
 }
-// states at exact restarts of the backward's downdates: the slices are cut
-// into this many runs, and each run's downdates start from an exact state
-int quad_runs(const slim_problem* p) {
-  const char* env = getenv("SLIM_QUAD_RUNS");
-  if (env != nullptr && atoi(env) > 0) return std::min(atoi(env), quad_slices(p));
-  return std::min(quad_slices(p), 16);
+int quad_env(const char* name, int v) {
+  const char* env = getenv(name);
+  return env != nullptr && atoi(env) > 0 ? atoi(env) : v;
 }
-
-struct QuadFwdLayout {
-  size_t wfrag, kmax, sa, sb, parts, total;
-};
-QuadFwdLayout quad_fwd_layout(const slim_problem* p) {
-  QuadFwdLayout l{0, 0, 0, 0, 0, 0};
-  const size_t heads = (size_t)p->B * p->H, se = state_elems(p) * sizeof(float);
+QuadPlan quad_plan_for(const slim_problem* p, int phase, int64_t rows, int heads) {
+  QuadPlan l;
+  std::memset(&l, 0, sizeof(l));
+  const int64_t BH = p->B * p->H;
+  const size_t SZ = (size_t)p->M * (p->d + 1) * sizeof(float);
+  l.heads = heads;
+  constexpr int64_t kB = slim::kQuadBlock, kPart = 2 * kB;
+  const int64_t per_head = std::max<int64_t>(kB, rows / heads / kB * kB);  // rows of a group per head
+  int64_t C = std::min((std::min<int64_t>(p->C, p->L) + kB - 1) / kB * kB, per_head);
+  if (C > kPart) C = std::min((C + kPart - 1) / kPart, per_head / kPart) * kPart;
+  l.C = (int)C;
+  l.part_rows = (int)std::min<int64_t>(C, kPart);
+  const int64_t slices = (p->L + C - 1) / C;
+  l.n = (int)std::min<int64_t>(p->L, C * std::min(slices, std::max<int64_t>(1, per_head / C)));
+  l.groups = (int)((p->L + l.n - 1) / l.n);
+  l.max_parts = quad_max_parts(p);
+  const size_t n = (size_t)heads * l.n, parts = (size_t)heads * ((l.n + l.part_rows - 1) / l.part_rows);
+  const size_t gslices = (size_t)heads * ((l.n + C - 1) / C), blocks = (size_t)heads * ((l.n + kB - 1) / kB);
+  const bool bwd = phase == SLIM_PHASE_BWD;
   size_t off = 0;
-  l.wfrag = off;
-  off += align256(wfrag_bytes_of(p));
-  l.kmax = off;
-  off += align256(heads * quad_max_parts(p) * sizeof(float));
-  l.sa = off;
-  off += align256(heads * se);
-  l.sb = off;
-  off += align256(heads * se);
-  l.parts = off;
-  off += align256(heads * quad_sum_parts(p) * se);
+  auto take = [&](size_t& at, size_t bytes) {
+    at = off;
+    off += align256(bytes);
+  };
+  take(l.wfrag, wfrag_bytes_of(p));
+  take(l.wtab, (size_t)3 * p->M * p->d * 2);
+  if (!bwd) take(l.kmax, BH * l.max_parts * sizeof(float));
+  take(l.part, parts * SZ);
+  take(l.FK, n * p->M * 2);
+  take(l.FQ, n * p->M * 2);
+  take(l.ST, gslices * slim::quad_table_bytes(p->d, p->M, bwd));
+  if (l.groups > 1) take(l.carry, heads * SZ);
+  if (bwd) {
+    if (l.groups > 1) {
+      l.starts = std::min(l.groups, quad_env("SLIM_QUAD_RUNS", kQuadStarts));
+      take(l.start, (size_t)l.starts * heads * SZ);
+    }
+    take(l.gcarry, heads * SZ);
+    take(l.GT, gslices * slim::quad_table_bytes(p->d, p->M, true));
+    take(l.DN, n * p->d * 2);
+    take(l.dD, n * sizeof(float));
+    take(l.gpart, blocks * SZ);
+    l.nwg = (int)std::min<size_t>(blocks, quad_env("SLIM_QUAD_WORKGROUPS", 256));
+    take(l.dw, (size_t)l.nwg * p->M * p->d * sizeof(float));
+  }
   l.total = off;
   return l;
 }
-
-// workgroups per head of the backward passes (each holds a dW partial)
-int quad_bwd_workgroups(const slim_problem* p) {
-  return std::min(quad_workgroups(p), (int)std::max<int64_t>(1, 1024 / (p->B * p->H)));
-}
-size_t state_frag_bytes_of(const slim_problem* p);
-// backward workspace: W in fragment order; the run sums and the exact
-// states at the run boundaries; states and cotangents (two each, used in
-// turn); per-slice parts; fragment tables of the state and the cotangent;
-// the query pass's rows [dN|dD|shift]; the dW partials
-struct QuadBwdLayout {
-  size_t wfrag, seg, bounds, s[2], g[2], parts, sfrag, gfrag, dn, dw_part, total;
-};
-QuadBwdLayout quad_bwd_layout(const slim_problem* p) {
-  QuadBwdLayout l;
-  std::memset(&l, 0, sizeof(l));
-  const size_t heads = (size_t)p->B * p->H, se = state_elems(p) * sizeof(float);
-  const int R = quad_runs(p);
-  size_t off = 0;
-  auto take = [&](size_t& at, size_t n) {
-    at = off;
-    off += align256(n);
-  };
-  take(l.wfrag, wfrag_bytes_of(p));
-  take(l.seg, heads * R * se);
-  take(l.bounds, heads * (R + 1) * se);
-  take(l.s[0], heads * se);
-  take(l.s[1], heads * se);
-  take(l.g[0], heads * se);
-  take(l.g[1], heads * se);
-  take(l.parts, heads * std::max(quad_sum_parts(p), 1) * se);
-  take(l.sfrag, heads * state_frag_bytes_of(p));
-  take(l.gfrag, heads * state_frag_bytes_of(p));
-  take(l.dn, heads * (size_t)clamp_C(p) * (p->d + 4) * sizeof(float));
-  take(l.dw_part, heads * quad_bwd_workgroups(p) * (size_t)p->M * p->d * sizeof(float));
-  l.total = off;
+// The preferred plan, or the largest that fits `limit` bytes: fewer rows, then
+// fewer heads at a time.  SLIM_QUAD_ROWS (debugging) forces fewer rows.
+QuadPlan quad_plan(const slim_problem* p, int phase, size_t limit = (size_t)-1) {
+  int64_t rows = quad_env("SLIM_QUAD_ROWS", kQuadRows);
+  int heads = (int)std::min<int64_t>(p->B * p->H, kQuadHeads);
+  QuadPlan l = quad_plan_for(p, phase, rows, heads);
+  while (l.total > limit && (heads > 1 || rows > slim::kQuadBlock)) {
+    if (rows > slim::kQuadBlock * (int64_t)heads) rows /= 2;
+    else heads = (heads + 1) / 2;
+    l = quad_plan_for(p, phase, rows, heads);
+  }
   return l;
 }
 
@@ -416,8 +414,6 @@ typedef hipError_t (*wfrag_fn)(const slim::WfragArgs&, hipStream_t);
 typedef size_t (*size_fn)();
 typedef hipError_t (*carry_fn)(const slim::CarryArgs&, hipStream_t);
 typedef hipError_t (*ksum_fn)(const slim::KsumArgs&, int, hipStream_t);
-typedef hipError_t (*quad_fn)(const slim::QuadArgs&, int, hipStream_t);
-typedef hipError_t (*sfrag_fn)(const float*, void*, const float*, void*, int, hipStream_t);
 
 struct Dispatch {
   fwd_fn fwd;
@@ -429,10 +425,6 @@ struct Dispatch {
   carry_fn carry;
   carry_fn carry8;  // 8-wave carry pass (nullptr where not built)
   ksum_fn ksum;  // key sums of row ranges (nullptr where not built: the key-only walk serves)
-  quad_fn quad_fwd;  // quadratic within-slice mode (nullptr where not built)
-  quad_fn quad_dq, quad_dk, quad_gsum;
-  sfrag_fn state_frag;
-  size_fn state_frag_bytes;
 };
 
 template <class T, int D, int FW, int KIND>
@@ -440,8 +432,6 @@ Dispatch make_dispatch() {
   typedef slim::Cfg<T, D, FW, kTileRows, KIND> G;
   return Dispatch{&slim::launch_fwd_walk<G>, &slim::launch_featmap<G>, &slim::launch_bwd_walk<G>, nullptr,
                   &slim::launch_wfrag<G>,    &slim::wfrag_bytes<G>,     &slim::launch_carry<G>,    nullptr,
-                  nullptr,                   nullptr,                   nullptr,
-                  nullptr,                   nullptr,                   nullptr,
                   nullptr};
 }
 template <int D, int FW, int KIND>
@@ -450,13 +440,6 @@ Dispatch make_dispatch8() {
   d.bwd8 = &slim::launch_bwd_walk8<slim::Cfg<slim::bf16, D, FW, kTileRows, KIND>>;
   d.ksum = &slim::launch_ksum<slim::Cfg<slim::bf16, D, FW, kTileRows, KIND>>;
   d.carry8 = &slim::launch_carry8<slim::Cfg<slim::bf16, D, FW, kTileRows, KIND>>;
-  typedef slim::Cfg<slim::bf16, D, FW, kTileRows, KIND> G;
-  d.quad_fwd = &slim::launch_quad_fwd<G>;
-  d.quad_dq = &slim::launch_quad_dq<G>;
-  d.quad_dk = &slim::launch_quad_dk<G>;
-  d.quad_gsum = &slim::launch_quad_gsum<G>;
-  d.state_frag = &slim::launch_state_frag<G>;
-  d.state_frag_bytes = &slim::state_frag_bytes<G>;
   return d;
 }
 
@@ -504,10 +487,6 @@ Dispatch dispatch(const slim_problem* p) {
 }
 
 size_t wfrag_bytes_of(const slim_problem* p) { return dispatch(p).wfrag_bytes(); }
-size_t state_frag_bytes_of(const slim_problem* p) {
-  const Dispatch d = dispatch(p);
-  return d.state_frag_bytes != nullptr ? d.state_frag_bytes() : 0;
-}
 bool has_ksum(const slim_problem* p) { return dispatch(p).ksum != nullptr; }
 bool has_carry8(const slim_problem* p) { return dispatch(p).carry8 != nullptr; }
 size_t context_bytes(const slim_problem* p) {
@@ -594,12 +573,12 @@ size_t ps_ws_bytes(const slim_problem* p, int phase) { return std::max(ps_budget
 
 size_t fwd_ws_bytes(const slim_problem* p) {
   if (ps(p)) return ps_ws_bytes(p, SLIM_PHASE_FWD);
-  if (quad(p)) return quad_fwd_layout(p).total;
+  if (quad(p)) return quad_plan(p, SLIM_PHASE_FWD).total;
   return fwd_layout(p, plan_fwd_segments(p)).total;
 }
 size_t bwd_ws_bytes(const slim_problem* p) {
   if (ps(p)) return ps_ws_bytes(p, SLIM_PHASE_BWD);
-  if (quad(p)) return quad_bwd_layout(p).total;
+  if (quad(p)) return quad_plan(p, SLIM_PHASE_BWD).total;
   return bwd_layout(p, plan_segments(p)).total;
 }
 
@@ -680,86 +659,136 @@ int slim_featmap(const slim_problem* p, const void* X, const float* W, int role,
 
 namespace {
 
-// Forward in the quadratic within-slice mode (arguments checked by fwd_impl):
-//   (0) one key shift per head: the largest key exponent of every part and
-//       of the initial state;
-//   (1) the state before the first slice: the initial state, rescaled to
-//       that shift;
-//   (2) per slice: the outputs of its query tiles from the state before it
-//       and its keys up to each row; what its keys add, in parts; the state
-//       after it = the state before + the parts.
-int quad_fwd_impl(const slim_problem* p, const Dispatch& dp, const void* Q, const void* K, const void* V,
-                  const float* W, const float* state_in, const float* kshift_in, void* Y, float* state_out,
-                  float* kshift_out, char* w, hipStream_t s) {
-  const QuadFwdLayout lay = quad_fwd_layout(p);
+// A range of heads of a problem in the quadratic mode, as a problem of one
+// batch entry, and pointers to its first head's rows and states
+struct QuadRange {
+  int h0, H;
+  size_t row;    // bytes of a head's rows
+  size_t state;  // entries of a state
+  const void* rows(const void* x) const { return (const char*)x + h0 * row; }
+  void* rows(void* x) const { return (char*)x + h0 * row; }
+  const float* states(const float* x) const { return x != nullptr ? x + h0 * state : nullptr; }
+  float* states(float* x) const { return x != nullptr ? x + h0 * state : nullptr; }
+  const float* heads(const float* x) const { return x != nullptr ? x + h0 : nullptr; }
+};
+// Arguments of a range's kernels, and of its key sums over one group's parts
+void quad_args(const slim_problem* p, const QuadPlan& lay, const QuadRange& rg, const void* Q, const void* K,
+               const void* V, const float* W, const float* kshift, char* w, slim::QuadArgs& a, slim::KsumArgs& ks) {
   const bool favor = p->kind == SLIM_FAVOR_PLUS;
-  const int BH = (int)(p->B * p->H), SZ = (int)state_elems(p);
-  const int C = clamp_C(p), NS = quad_slices(p), tps = quad_tiles(p);
-  hipError_t e;
+  const DropPlan dr = drop_plan(p);
+  std::memset(&a, 0, sizeof(a));
+  a.Q = rg.rows(Q);
+  a.K = rg.rows(K);
+  a.V = rg.rows(V);
+  a.W = W;
+  a.kshift = favor ? rg.heads(kshift) : nullptr;
+  a.wtab = w + lay.wtab;
+  a.FK = w + lay.FK;
+  a.FQ = w + lay.FQ;
+  a.part = (const float*)(w + lay.part);
+  a.ST = w + lay.ST;
+  a.H = rg.H;
+  a.L = (int)p->L;
+  a.C = lay.C;
+  a.head0 = rg.h0;
+  a.part_rows = lay.part_rows;
+  a.kind = favor ? slim::kFavor : slim::kRelu;
+  a.relu_eps = p->relu_eps;
+  set_drop(a, dr);
+  a.drop_C = clamp_C(p);
+  std::memset(&ks, 0, sizeof(ks));
+  set_drop(ks, dr);
+  ks.drop_C = a.drop_C;
+  ks.head0 = rg.h0;
+  ks.K = a.K;
+  ks.V = a.V;
+  ks.W = W;
+  ks.Wfrag = w + lay.wfrag;
+  ks.shift = a.kshift;
+  ks.out = (float*)(w + lay.part);
+  ks.B = 1;
+  ks.H = rg.H;
+  ks.L = (int)p->L;
+  ks.C = lay.C;
+  ks.align = lay.part_rows / kTileRows;
+  ks.relu_eps = p->relu_eps;
+}
+// group n: its rows, and what each of its parts adds to the state
+hipError_t quad_group(const slim_problem* p, const Dispatch& dp, const QuadPlan& lay, int n, slim::QuadArgs& a,
+                      slim::KsumArgs& ks, hipStream_t s) {
+  a.row0 = n * lay.n;
+  a.n = (int)std::min<int64_t>(lay.n, p->L - a.row0);
+  a.parts = (a.n + lay.part_rows - 1) / lay.part_rows;
+  ks.P2 = a.parts;
+  ks.tile_begin = a.row0 / kTileRows;
+  ks.tile_end = ks.tile_begin + (a.n + kTileRows - 1) / kTileRows;
+  return dp.ksum(ks, slim::kSumStates, s);
+}
+// W as the key sums and the mode's own kernels take it
+hipError_t quad_prep(const slim_problem* p, const Dispatch& dp, const QuadPlan& lay, const float* W, char* w,
+                     hipStream_t s) {
   slim::WfragArgs wf;
   wf.W = W;
   wf.out = w + lay.wfrag;
-  e = dp.wfrag(wf, s);
-  if (e != hipSuccess) return hip_fail(e, "W-fragment launch");
-  slim::KsumArgs ks;
-  std::memset(&ks, 0, sizeof(ks));
-  set_drop(ks, drop_plan(p));
-  ks.K = K;
-  ks.V = V;
-  ks.W = W;
-  ks.Wfrag = wf.out;
-  ks.B = (int)p->B;
-  ks.H = (int)p->H;
-  ks.L = (int)p->L;
-  ks.C = C;
-  ks.relu_eps = p->relu_eps;
+  const hipError_t e = dp.wfrag(wf, s);
+  if (e != hipSuccess) return e;
+  slim::QuadArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.W = W;
+  a.wtab = w + lay.wtab;
+  return slim::launch_quad(slim::kQuadPrep, a, p->d, p->M, s);
+}
+
+// Forward in the quadratic within-slice mode (arguments checked by fwd_impl):
+//   (0) one key shift per head: the largest key exponent of every part and
+//       of the initial state;
+//   (1) per range of heads and group of slices: what the keys of each part
+//       add to the state and the state before every slice; the features of
+//       its rows; the outputs.
+int quad_fwd_impl(const slim_problem* p, const Dispatch& dp, const void* Q, const void* K, const void* V,
+                  const float* W, const float* state_in, const float* kshift_in, void* Y, float* state_out,
+                  float* kshift_out, char* w, size_t ws_bytes, hipStream_t s) {
+  const QuadPlan lay = quad_plan(p, SLIM_PHASE_FWD, ws_bytes);
+  const bool favor = p->kind == SLIM_FAVOR_PLUS;
+  const int BH = (int)(p->B * p->H);
+  hipError_t e = quad_prep(p, dp, lay, W, w, s);
+  if (e != hipSuccess) return hip_fail(e, "W launch");
   if (favor) {
+    slim::KsumArgs ks;
+    std::memset(&ks, 0, sizeof(ks));
+    ks.K = K;
+    ks.V = V;
+    ks.W = W;
+    ks.Wfrag = w + lay.wfrag;
+    ks.B = (int)p->B;
+    ks.H = (int)p->H;
+    ks.L = (int)p->L;
+    ks.C = clamp_C(p);
     ks.out = (float*)(w + lay.kmax);
-    ks.P2 = quad_max_parts(p);
+    ks.P2 = lay.max_parts;
     e = dp.ksum(ks, slim::kSumMax, s);
     if (e != hipSuccess) return hip_fail(e, "key-maximum launch");
     e = slim::launch_kshift_reduce(ks.out, ks.P2, state_in != nullptr ? kshift_in : nullptr, kshift_out, BH, s);
     if (e != hipSuccess) return hip_fail(e, "key-shift launch");
-    ks.shift = kshift_out;
   }
-  float* Sa = (float*)(w + lay.sa);
-  float* Sb = (float*)(w + lay.sb);
-  float* parts = (float*)(w + lay.parts);
-  e = slim::launch_state_combine(state_in, SZ, favor ? kshift_in : nullptr, favor ? kshift_out : nullptr, nullptr, 0,
-                                 1.f, Sa, BH, SZ, s);
-  if (e != hipSuccess) return hip_fail(e, "state launch");
-  slim::QuadArgs qa;
-  std::memset(&qa, 0, sizeof(qa));
-  set_drop(qa, drop_plan(p));
-  qa.Q = Q;
-  qa.K = K;
-  qa.V = V;
-  qa.Wfrag = wf.out;
-  qa.kshift = favor ? kshift_out : nullptr;
-  qa.Y = Y;
-  qa.B = (int)p->B;
-  qa.H = (int)p->H;
-  qa.L = (int)p->L;
-  qa.C = C;
-  qa.relu_eps = p->relu_eps;
-  ks.out = parts;
-  ks.P2 = quad_sum_parts(p);
   e = timed_launch(SLIM_PHASE_FWD, s, [&]() -> hipError_t {
-    for (int n = 0; n < NS; ++n) {
-      qa.row0 = n * C;
-      qa.rows = (int)std::min<int64_t>(C, p->L - (int64_t)n * C);
-      qa.S = Sa;
-      hipError_t er = dp.quad_fwd(qa, quad_workgroups(p), s);
-      if (er != hipSuccess) return er;
-      if (n == NS - 1 && state_out == nullptr) break;
-      ks.tile_begin = n * tps;
-      ks.tile_end = n * tps + (qa.rows + kTileRows - 1) / kTileRows;
-      er = dp.ksum(ks, slim::kSumStates, s);
-      if (er != hipSuccess) return er;
-      er = slim::launch_state_combine(Sa, SZ, nullptr, nullptr, parts, ks.P2, 1.f, n == NS - 1 ? state_out : Sb, BH, SZ,
-                                      s);
-      if (er != hipSuccess) return er;
-      std::swap(Sa, Sb);
+    for (int h0 = 0; h0 < BH; h0 += lay.heads) {
+      const QuadRange rg{h0, std::min(lay.heads, BH - h0), (size_t)p->L * p->d * 2, state_elems(p)};
+      slim::QuadArgs a;
+      slim::KsumArgs ks;
+      quad_args(p, lay, rg, Q, K, V, W, kshift_out, w, a, ks);
+      a.Y = rg.rows(Y);
+      a.S_in = rg.states(state_in);
+      a.in_shift = favor && state_in != nullptr ? rg.heads(kshift_in) : nullptr;
+      for (int n = 0; n < lay.groups; ++n) {
+        hipError_t er = quad_group(p, dp, lay, n, a, ks, s);
+        if (er != hipSuccess) return er;
+        a.S_out = n == lay.groups - 1 ? rg.states(state_out) : (float*)(w + lay.carry);
+        for (const int k : {slim::kQuadStates, slim::kQuadFeat, slim::kQuadFwd})
+          if ((er = slim::launch_quad(k, a, p->d, p->M, s)) != hipSuccess) return er;
+        a.S_in = a.S_out;
+        a.in_shift = nullptr;
+      }
     }
     return hipSuccess;
   });
@@ -767,158 +796,102 @@ int quad_fwd_impl(const slim_problem* p, const Dispatch& dp, const void* Q, cons
   return ok();
 }
 
-// Backward in the quadratic within-slice mode (arguments checked by slim_bwd):
-//   (1) exact states at the boundaries of R runs of whole slices (slice-
-//       aligned key sums, then their prefix from the initial state);
-//   (2) the slices in reverse, each with the state before it (the exact
-//       state at a run's first slice, else the state after it downdated by
-//       what the slice's keys add, eq. 17) and the cotangent after it: the
-//       query pass, the key pass, then the cotangent before it (eq. 18);
-//   (3) dstate_in, and dW from the workgroups' partials in a fixed order.
+// Backward in the quadratic within-slice mode (arguments checked by slim_bwd),
+// per range of heads:
+//   (1) several groups: the exact state before up to kQuadStarts of them;
+//   (2) the groups in reverse: the state before the group (an exact one, else
+//       the state after it minus what it adds, eq. 17) and before its slices;
+//       the features of its rows; the queries' pass; the cotangent after its
+//       slices and before the group (eq. 18); the keys' pass;
+//   (3) dstate_in.  dW from the workgroups' partials in a fixed order.
 int quad_bwd_impl(const slim_problem* p, const Dispatch& dp, const void* Q, const void* K, const void* V,
                   const float* W, const float* state_in, const float* kshift_in, const float* kshift, const void* dY,
                   const float* dstate_out, void* dQ, void* dK, void* dV, float* dW, float* dstate_in, char* w,
-                  hipStream_t s) {
-  const QuadBwdLayout lay = quad_bwd_layout(p);
+                  size_t ws_bytes, hipStream_t s) {
+  const QuadPlan lay = quad_plan(p, SLIM_PHASE_BWD, ws_bytes);
   const bool favor = p->kind == SLIM_FAVOR_PLUS;
   const int BH = (int)(p->B * p->H), SZ = (int)state_elems(p);
-  const int C = clamp_C(p), NS = quad_slices(p), tps = quad_tiles(p), R = quad_runs(p);
-  const int P2 = quad_sum_parts(p), NW = quad_bwd_workgroups(p);
-  hipError_t e;
-  slim::WfragArgs wf;
-  wf.W = W;
-  wf.out = w + lay.wfrag;
-  e = dp.wfrag(wf, s);
-  if (e != hipSuccess) return hip_fail(e, "W-fragment launch");
-  slim::KsumArgs ks;
-  std::memset(&ks, 0, sizeof(ks));
-  set_drop(ks, drop_plan(p));
-  ks.K = K;
-  ks.V = V;
-  ks.W = W;
-  ks.Wfrag = wf.out;
-  ks.shift = favor ? kshift : nullptr;
-  ks.B = (int)p->B;
-  ks.H = (int)p->H;
-  ks.L = (int)p->L;
-  ks.C = C;
-  ks.relu_eps = p->relu_eps;
-  // (1)
-  ks.out = (float*)(w + lay.seg);
-  ks.P2 = R;
-  ks.align = tps;
-  e = dp.ksum(ks, slim::kSumStates, s);
-  if (e != hipSuccess) return hip_fail(e, "run-sum launch");
-  const float* bounds = (const float*)(w + lay.bounds);
-  const size_t bstride = (size_t)(R + 1) * SZ;  // between heads of one boundary
-  {
-    slim::ScanArgs sc;
-    std::memset(&sc, 0, sizeof(sc));
-    sc.seg = ks.out;
-    sc.init = state_in;
-    sc.init_shift = favor ? kshift_in : nullptr;
-    sc.shift = favor ? kshift : nullptr;
-    sc.out = (float*)(w + lay.bounds);
-    sc.BH = BH;
-    sc.P = R;
-    sc.SZ = SZ;
-    sc.favor = favor ? 1 : 0;
-    e = slim::launch_scan_bwd(sc, s);
-    if (e != hipSuccess) return hip_fail(e, "boundary-scan launch");
-  }
-  ks.align = 0;
-  ks.out = (float*)(w + lay.parts);
-  ks.P2 = P2;
-  float* dw_part = (float*)(w + lay.dw_part);
-  e = slim::launch_state_combine(nullptr, 0, nullptr, nullptr, nullptr, 0, 1.f, dw_part, BH * NW, (int)(p->M * p->d), s);
+  hipError_t e = quad_prep(p, dp, lay, W, w, s);
+  if (e != hipSuccess) return hip_fail(e, "W launch");
+  float* dw_part = (float*)(w + lay.dw);
+  e = slim::launch_state_combine(nullptr, 0, nullptr, nullptr, nullptr, 0, 1.f, dw_part, lay.nwg, (int)(p->M * p->d), s);
   if (e != hipSuccess) return hip_fail(e, "dW-partial launch");
-  float* parts = (float*)(w + lay.parts);
-  float* sbuf[2] = {(float*)(w + lay.s[0]), (float*)(w + lay.s[1])};
-  float* gbuf[2] = {(float*)(w + lay.g[0]), (float*)(w + lay.g[1])};
-  const float* Gafter = dstate_out;
-  int gb = 0;
-  if (Gafter == nullptr) {
-    e = slim::launch_state_combine(nullptr, 0, nullptr, nullptr, nullptr, 0, 1.f, gbuf[1], BH, SZ, s);
-    if (e != hipSuccess) return hip_fail(e, "cotangent launch");
-    Gafter = gbuf[1];
-  }
-  slim::QuadArgs qa;
-  std::memset(&qa, 0, sizeof(qa));
-  set_drop(qa, drop_plan(p));
-  qa.Q = Q;
-  qa.K = K;
-  qa.V = V;
-  qa.dY = dY;
-  qa.Wfrag = wf.out;
-  qa.kshift = favor ? kshift : nullptr;
-  qa.Sfrag = w + lay.sfrag;
-  qa.Gfrag = w + lay.gfrag;
-  qa.DN = (float*)(w + lay.dn);
-  qa.dQ = dQ;
-  qa.dK = dK;
-  qa.dV = dV;
-  qa.dW_part = dw_part;
-  qa.out = parts;
-  qa.B = (int)p->B;
-  qa.H = (int)p->H;
-  qa.L = (int)p->L;
-  qa.C = C;
-  qa.relu_eps = p->relu_eps;
-  auto first_of_run = [&](int r) { return (int)((int64_t)r * NS / R); };
-  // (2)
   e = timed_launch(SLIM_PHASE_BWD, s, [&]() -> hipError_t {
-    hipError_t er;
-    int r = R - 1, sb = 0;
-    const float* Safter = nullptr;  // the state after slice n, unless n ends its run
-    for (int n = NS - 1; n >= 0; --n) {
-      while (first_of_run(r) > n) --r;
-      const int rows = (int)std::min<int64_t>(C, p->L - (int64_t)n * C);
-      const bool run_end = (n == first_of_run(r + 1) - 1);
-      float* Sb = sbuf[sb];
-      sb ^= 1;
-      if (n == first_of_run(r)) {
-        er = slim::launch_state_combine(bounds + (size_t)r * SZ, bstride, nullptr, nullptr, nullptr, 0, 1.f, Sb, BH, SZ,
-                                        s);
-      } else {
-        ks.tile_begin = n * tps;
-        ks.tile_end = n * tps + (rows + kTileRows - 1) / kTileRows;
-        er = dp.ksum(ks, slim::kSumStates, s);
-        if (er != hipSuccess) return er;
-        if (run_end) er = slim::launch_state_combine(bounds + (size_t)(r + 1) * SZ, bstride, nullptr, nullptr, parts, P2,
-                                                     -1.f, Sb, BH, SZ, s);
-        else er = slim::launch_state_combine(Safter, SZ, nullptr, nullptr, parts, P2, -1.f, Sb, BH, SZ, s);
+    for (int h0 = 0; h0 < BH; h0 += lay.heads) {
+      const QuadRange rg{h0, std::min(lay.heads, BH - h0), (size_t)p->L * p->d * 2, state_elems(p)};
+      hipError_t er;
+      slim::QuadArgs a;
+      slim::KsumArgs ks;
+      quad_args(p, lay, rg, Q, K, V, W, kshift, w, a, ks);
+      a.dY = rg.rows(dY);
+      a.GT = w + lay.GT;
+      a.DN = w + lay.DN;
+      a.dD = (float*)(w + lay.dD);
+      a.gpart = (float*)(w + lay.gpart);
+      a.dQ = rg.rows(dQ);
+      a.dK = rg.rows(dK);
+      a.dV = rg.rows(dV);
+      a.dW_part = dw_part;
+      a.nwg = lay.nwg;
+      const float* S0 = rg.states(state_in);
+      float* carry = (float*)(w + lay.carry);
+      float* gcarry = (float*)(w + lay.gcarry);
+      const int R = lay.groups, NP = std::max(lay.starts, 1);
+      auto start_of = [&](int r) { return (float*)(w + lay.start) + (size_t)r * rg.H * SZ; };
+      auto first_of = [&](int r) { return (int)((int64_t)r * R / NP); };  // first group of part r
+      auto from = [&](const float* S) {
+        a.S_in = S;
+        a.in_shift = favor && S != nullptr && S == S0 ? rg.heads(kshift_in) : nullptr;
+      };
+      // (1)
+      if (R > 1) {
+        from(S0);
+        const int upto = NP == R ? R - 1 : R;
+        int r = 1;
+        for (int n = 0; n < upto; ++n) {
+          er = quad_group(p, dp, lay, n, a, ks, s);
+          if (er != hipSuccess) return er;
+          const bool keep = r < NP && first_of(r) == n + 1;
+          a.S_out = keep ? start_of(r) : carry;
+          r += keep;
+          er = slim::launch_quad(slim::kQuadStates, a, p->d, p->M, s);
+          if (er != hipSuccess) return er;
+          from(a.S_out);
+        }
       }
-      if (er != hipSuccess) return er;
-      Safter = Sb;
-      er = dp.state_frag(Sb, w + lay.sfrag, Gafter, w + lay.gfrag, BH, s);
-      if (er != hipSuccess) return er;
-      qa.S = Sb;
-      qa.Gc = Gafter;
-      qa.row0 = n * C;
-      qa.rows = rows;
-      er = dp.quad_dq(qa, NW, s);
-      if (er != hipSuccess) return er;
-      er = dp.quad_dk(qa, NW, s);
-      if (er != hipSuccess) return er;
-      if (n > 0 || dstate_in != nullptr) {
-        er = dp.quad_gsum(qa, P2, s);
+      // (2)
+      a.G_in = rg.states(dstate_out);
+      int r = NP - 1;
+      for (int n = R - 1; n >= 0; --n) {
+        while (first_of(r) > n) --r;
+        er = quad_group(p, dp, lay, n, a, ks, s);
         if (er != hipSuccess) return er;
-        er = slim::launch_state_combine(Gafter, SZ, nullptr, nullptr, parts, P2, 1.f, gbuf[gb], BH, SZ, s);
+        a.down = n != first_of(r);
+        if (!a.down) {
+          from(r == 0 ? S0 : start_of(r));
+          a.S_out = nullptr;
+        } else {
+          from(r < NP - 1 && n == first_of(r + 1) - 1 ? start_of(r + 1) : carry);
+          a.S_out = carry;
+        }
+        for (const int k : {slim::kQuadStates, slim::kQuadFeat})
+          if ((er = slim::launch_quad(k, a, p->d, p->M, s)) != hipSuccess) return er;
+        a.G_out = gcarry;
+        for (const int k : {slim::kQuadDq, slim::kQuadCot, slim::kQuadDk})
+          if ((er = slim::launch_quad_bwd(k, a, p->d, p->M, s)) != hipSuccess) return er;
+        a.G_in = gcarry;
+      }
+      // (3) the cotangent of state_in, relative to kshift_in (FAVOR+ with an initial state)
+      if (dstate_in != nullptr) {
+        er = slim::launch_state_combine(gcarry, SZ, favor ? rg.heads(kshift_in) : nullptr, a.kshift, nullptr, 0, 1.f,
+                                        rg.states(dstate_in), rg.H, SZ, s);
         if (er != hipSuccess) return er;
-        Gafter = gbuf[gb];
-        gb ^= 1;
       }
     }
     return hipSuccess;
   });
   if (e != hipSuccess) return hip_fail(e, "quadratic-mode backward launches");
-  // (3) the cotangent of state_in, relative to kshift_in (FAVOR+ with an initial state)
-  if (dstate_in != nullptr) {
-    e = slim::launch_state_combine(Gafter, SZ, favor ? kshift_in : nullptr, favor ? kshift : nullptr, nullptr, 0, 1.f,
-                                   dstate_in, BH, SZ, s);
-    if (e != hipSuccess) return hip_fail(e, "dstate_in launch");
-  }
-  e = slim::launch_dw_reduce(dw_part, BH * NW, (int)(p->M * p->d), dW, s);
+  e = slim::launch_dw_reduce(dw_part, lay.nwg, (int)(p->M * p->d), dW, s);
   if (e != hipSuccess) return hip_fail(e, "dW-reduction launch");
   return ok();
 }
@@ -1089,7 +1062,7 @@ int ps_bwd_impl(const slim_problem* p, const void* Q, const void* K, const void*
 // library's static scratch for slim_fwd_noalloc).
 int fwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
              const float* state_in, const float* kshift_in, void* Y, float* logD, float* state_out, float* kshift_out,
-             float* ctx, void* ws, size_t ws_bytes, void* stream) {
+             float* ctx, void* ws, size_t ws_bytes, size_t need, void* stream) {
   int st = check_problem(p);
   if (st != SLIM_OK) return st;
   if (Q == nullptr || K == nullptr || V == nullptr || W == nullptr || Y == nullptr)
@@ -1103,7 +1076,6 @@ int fwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V,
   if (logD != nullptr && (ps(p) || quad(p)))
     return fail(SLIM_EUNSUPPORTED, "logD is written by the tile-walk mode (within = SLIM_WITHIN_ITER) only");
   if (!context_used(p)) ctx = nullptr;
-  const size_t need = fwd_ws_bytes(p);
   if (need > 0 && (ws == nullptr || ws_bytes < need))
     return fail(SLIM_EWORKSPACE, "forward workspace needs %zu bytes, got %zu", need, ws == nullptr ? 0 : ws_bytes);
   if (ps(p))
@@ -1111,7 +1083,7 @@ int fwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V,
   const Dispatch dp = dispatch(p);
   if (quad(p))
     return quad_fwd_impl(p, dp, Q, K, V, W, state_in, kshift_in, Y, state_out, kshift_out, (char*)ws,
-                         (hipStream_t)stream);
+                         ws_bytes, (hipStream_t)stream);
   const int P = plan_fwd_segments(p);
   const FwdLayout lay = fwd_layout(p, P);
   const bool favor = p->kind == SLIM_FAVOR_PLUS;
@@ -1278,7 +1250,8 @@ extern "C" {
 int slim_fwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
              const float* state_in, const float* kshift_in, void* Y, float* logD, float* state_out, float* kshift_out,
              float* ctx, void* ws, size_t ws_bytes, void* stream) {
-  return fwd_impl(p, Q, K, V, W, state_in, kshift_in, Y, logD, state_out, kshift_out, ctx, ws, ws_bytes, stream);
+  const size_t need = check_problem(p) == SLIM_OK ? fwd_ws_bytes(p) : 0;
+  return fwd_impl(p, Q, K, V, W, state_in, kshift_in, Y, logD, state_out, kshift_out, ctx, ws, ws_bytes, need, stream);
 }
 
 size_t slim_noalloc_scratch_bytes(void) { return kNoallocScratchBytes; }
@@ -1288,7 +1261,8 @@ int slim_fwd_noalloc(const slim_problem* p, const void* Q, const void* K, const 
                      float* kshift_out, float* ctx, void* stream) {
   int st = check_problem(p);
   if (st != SLIM_OK) return st;
-  const size_t need = fwd_ws_bytes(p);
+  // (the quadratic mode takes fewer rows at a time where its preferred plan does not fit)
+  const size_t need = quad(p) ? quad_plan(p, SLIM_PHASE_FWD, kNoallocScratchBytes).total : fwd_ws_bytes(p);
   if (need > kNoallocScratchBytes)
     return fail(SLIM_EUNSUPPORTED, "slim_fwd_noalloc: the forward needs %zu bytes of scratch, the static scratch holds %zu",
                 need, kNoallocScratchBytes);
@@ -1298,7 +1272,7 @@ int slim_fwd_noalloc(const slim_problem* p, const void* Q, const void* K, const 
     if (st != SLIM_OK) return st;
   }
   return fwd_impl(p, Q, K, V, W, state_in, kshift_in, Y, logD, state_out, kshift_out, ctx, ws, kNoallocScratchBytes,
-                  stream);
+                  need, stream);
 }
 
 int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
@@ -1329,7 +1303,7 @@ int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V,
   const Dispatch dp = dispatch(p);
   if (quad(p))
     return quad_bwd_impl(p, dp, Q, K, V, W, state_in, kshift_in, kshift, dY, dstate_out, dQ, dK, dV, dW, dstate_in,
-                         (char*)ws, (hipStream_t)stream);
+                         (char*)ws, ws_bytes, (hipStream_t)stream);
   const int P = plan_segments(p);
   const BwdLayout lay = bwd_layout(p, P);
   hipStream_t s = (hipStream_t)stream;

@@ -64,6 +64,8 @@ __device__ __forceinline__ Lane fresh_lane() {
 }
 __device__ __forceinline__ Lane this_lane() { return Lane{lane_g(), lane_c()}; }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
+// the same as a scalar
+__device__ __forceinline__ int uniform_wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // k offset of slot s of lane group g inside a 32-deep block
 __device__ __forceinline__ int kp(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }

@@ -149,36 +149,67 @@ struct KsumArgs {
   uint64_t drop_seed;
   uint32_t drop_t;
   float drop_scale;
+  int drop_C;  // slice length of the masks' seeds (0: C)
+  int head0;   // head h of the call is head head0 + h of the masks
 };
 
-// In-slice masked quadratic form (the slice evaluated as a whole, Sec. 3.2
-// with eq. 2 inside the slice): slices are processed one after another,
-// the query (or key) tiles of a slice in parallel.
+constexpr int kQuadBlock = 256;  // rows of a workgroup's block of the quadratic mode
+// In-slice masked quadratic form (eq. 2 inside a slice of C rows, C a
+// multiple of the block): the slices of a group in parallel, groups one after
+// another.  Head h of a group is head head0 + h of the problem (dropout);
+// every pointer is that of the group's first head.
 struct QuadArgs {
   const void* Q;
   const void* K;
   const void* V;
   const void* dY;
-  const void* Wfrag;      // fragment-ordered W (WFragLayout), with the low parts
-  const float* kshift;    // [B,H] key shift (FAVOR+)
-  const float* S;         // [B,H,M,D+1] state before the slice (relative to kshift)
-  const void* Sfrag;      // its fragment tables (StateFragLayout), backward query pass
-  const float* Gc;        // [B,H,M,D+1] state cotangent after the slice (backward key pass)
-  const void* Gfrag;      // its fragment tables
-  void* Y;                // forward: out [B,H,L,D]
-  float* DN;              // backward: [B,H,C,D+4] per row of the slice: dN[0,D), dD, the query row shift
+  const float* W;         // [M, d]
+  const float* kshift;    // [H] key shift (FAVOR+), or nullptr
+  void* wtab;             // bf16: W hi [M][d], W lo [M][d], W^T hi [d][M] in slot order
+  void* FK;               // [H][n][M] bf16: features of the group's keys, slot order
+  void* FQ;               // ... of its queries (FAVOR+: relative to the row's largest logit)
+  void* Y;
+  const float* part;      // [H][parts][M][d + 1] what each run of part_rows rows adds to the state
+  const float* S_in;      // [H][M][d + 1] state before the group, or nullptr (zero)
+  const float* in_shift;  // [H] its key shift, or nullptr (kshift)
+  float* S_out;           // [H][M][d + 1] state after the group (down: before it), or nullptr
+  int down;               // S_in is the state after the group (eq. 17: the parts are subtracted first)
+  void* ST;               // [H][slices] tables of the state before each slice: S^T [d][M] bf16, S [M][d] bf16
+                          // (both in slot order; S only in the backward), z [M] float
+  void* GT;               // the same of the cotangent after each slice
+  void* DN;               // [H][n][d] bf16 dN, slot order
+  float* dD;              // [H][n]
+  float* gpart;           // [H][blocks][M][d + 1] what each block adds to the cotangent
+  const float* G_in;      // [H][M][d + 1] cotangent after the group, or nullptr (zero)
+  float* G_out;           // [H][M][d + 1] cotangent before it
   void* dQ;
   void* dK;
   void* dV;
-  float* dW_part;         // [B,H,gridDim.x][M,D] partial dW per workgroup, accumulated (+=)
-  float* out;             // cotangent sums: [B,H,gridDim.x][M,D+1] per part
-  int B, H, L, C;
-  int row0, rows;         // the slice: rows [row0, row0 + rows)
+  float* dW_part;         // [nwg][M][d], added to
+  int nwg;                // workgroups of the backward's passes
+  int H, L, C, head0;
+  int row0, n;            // the group: rows [row0, row0 + n), row0 a multiple of C
+  int parts, part_rows;   // part_rows divides C (or covers the group)
+  int kind;
   float relu_eps;
   uint64_t drop_seed;
   uint32_t drop_t;
   float drop_scale;
+  int drop_C;             // the problem's slice length (the masks' seeds)
 };
+enum QuadKernel {
+  kQuadPrep = 0,    // wtab
+  kQuadFeat = 1,    // FK, FQ
+  kQuadStates = 2,  // ST, S_out
+  kQuadFwd = 3,     // Y
+  kQuadDq = 4,      // dQ, dW share; DN, dD, gpart
+  kQuadCot = 5,     // GT, G_out
+  kQuadDk = 6       // dK, dV, dW share
+};
+hipError_t launch_quad(int which, const QuadArgs& a, int d, int M, hipStream_t s);
+hipError_t launch_quad_bwd(int which, const QuadArgs& a, int d, int M, hipStream_t s);
+// bytes of one state table
+__host__ __device__ inline size_t quad_table_bytes(int d, int M, bool both) { return (size_t)M * d * 2 * (both ? 2 : 1) + (size_t)M * 4; }
 
 // Sum of per-part states: out = f * in + sign * sum_p part[p] per head, with
 // f = exp(in_shift - shift) when both shifts are given (FAVOR+), else 1;
@@ -186,22 +217,6 @@ struct QuadArgs {
 // of `out` at out + h * SZ, its parts at part + (h * P2 + p) * SZ.
 hipError_t launch_state_combine(const float* in, size_t in_stride, const float* in_shift, const float* shift,
                                 const float* part, int P2, float sign, float* out, int BH, int SZ, hipStream_t s);
-template <class G>
-hipError_t launch_quad_fwd(const QuadArgs& a, int nwg, hipStream_t s);
-// backward of one slice: the query pass (dN, dD, dQ, dW), the key pass
-// (dK, dV, dW), the sum of Q~^T [dN|dD] over the slice in nwg parts
-template <class G>
-hipError_t launch_quad_dq(const QuadArgs& a, int nwg, hipStream_t s);
-template <class G>
-hipError_t launch_quad_dk(const QuadArgs& a, int nwg, hipStream_t s);
-template <class G>
-hipError_t launch_quad_gsum(const QuadArgs& a, int nwg, hipStream_t s);
-// fragment tables of n states [BH][M][D+1] (n = 1 or 2: X0 -> F0, X1 -> F1)
-template <class G>
-hipError_t launch_state_frag(const float* X0, void* F0, const float* X1, void* F1, int BH, hipStream_t s);
-template <class G>
-size_t state_frag_bytes();
-
 template <class G>
 hipError_t launch_fwd_walk(const FwdArgs& a, int mode, hipStream_t s);
 template <class G>
@@ -299,13 +314,6 @@ struct PsArgs {
 };
 // nwg: workgroups of kPsOut, kPsRows and kPsKeys
 hipError_t launch_ps(int which, const PsArgs& a, int nwg, hipStream_t s);
-
-// configurations of the whole-slice quadratic form (bf16, 32 or 64 features
-// per wave)
-#define SLIM_FOR_EACH_QUAD_CONFIG(X)                                                  \
-  X(bf16, 64, 64, 32, kFavor) X(bf16, 64, 32, 32, kFavor) X(bf16, 32, 64, 32, kFavor) \
-  X(bf16, 32, 32, 32, kFavor) X(bf16, 64, 64, 32, kRelu) X(bf16, 64, 32, 32, kRelu)  \
-  X(bf16, 32, 64, 32, kRelu) X(bf16, 32, 32, 32, kRelu)
 
 // configurations served by the 8-wave backward walk
 #define SLIM_FOR_EACH_BF16_CONFIG(X)                                                  \

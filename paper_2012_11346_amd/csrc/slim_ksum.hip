@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void ksum_kernel(KsumArgs a) {
     }
   };
   // value dropout: dropped elements of the value rows are zeroed when staged
-  const Drop drop{a.drop_seed, a.drop_t, a.C, head};
+  const Drop drop{a.drop_seed, a.drop_t, a.drop_C > 0 ? a.drop_C : a.C, (uint64_t)a.head0 + head};
   sk.fetch(rK, 0, tid);
   if constexpr (SUMS) sv.fetch(rV, 0, tid);
   fetch_q(0, tid);

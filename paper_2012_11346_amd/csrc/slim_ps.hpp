@@ -80,10 +80,9 @@ __device__ __forceinline__ const float* opaque(const float* p) {
   asm volatile("" : "+s"(p));
   return p;
 }
-// the wave's index as a scalar, and the lane coordinates made opaque at the
-// start of a phase (else every lane-dependent address of the chunk loop is
-// formed before it and kept, which spills)
-__device__ __forceinline__ int uniform_wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+// the lane coordinates made opaque at the start of a phase (else every
+// lane-dependent address of the chunk loop is formed before it and kept,
+// which spills)
 __device__ __forceinline__ void refresh(int& g, int& c) { asm volatile("" : "+v"(g), "+v"(c)); }
 // acc += A B over 16 of the contraction index: lane (g, c), entry j <-> k = 4 g + j
 __device__ __forceinline__ f32x4 mma16(f32x4 acc, const f32x4& a, const f32x4& b) {

@@ -1,302 +1,301 @@
-// The slice evaluated as a whole: Algorithm 1 with the masked quadratic form
-// of eq. 2 inside each slice (Sec. 3.2).  Slices are processed one after
-// another, as in the paper; inside a slice every 32-row query tile t is
-// independent given the state B^(n-1) before the slice:
+// The quadratic within-slice mode: Algorithm 1 with the masked quadratic form
+// of eq. 2 inside each slice (Sec. 3.2).  For a query t of a slice whose
+// state before it is [S | z],
 //
-//   N_t = Q~_t [S|z] + sum_{u <= t in the slice} tril_u=t(Q~_t K~_u^T) [V_u|1],
-//   Y_t = N_t / D_t,
+//   N_t = g(q_t)^T [S | z] + sum_{s <= t in the slice} (g(q_t) . g(k_s)) [v_s | 1],   Y_t = N_t / D_t,
 //
-// so the work per row grows with the slice length C (C / 2 key tiles on
-// average), where the tile walks of the other kernels carry the state from
-// tile to tile and do the same work for every C.  Four waves per workgroup,
-// wave w owning features [w FW, (w + 1) FW); each wave sums its features'
-// share of N over the key tiles and the shares meet in LDS once per query
-// tile.  Key features are recomputed for every (query, key) tile pair: no
-// buffer of size C is kept.
-#include "slim_common.hpp"
-#include "slim_kernels.hpp"
+// so the work per row grows with the slice length (C / 2 keys on average,
+// 2 M + 2 d operations each).  Given the states before the slices the query
+// blocks of all slices are independent: one workgroup per 256 queries, eight
+// waves of 32 (128 stream every key row twice as often from the L2 and the
+// last-level cache, which then set the pace), streaming the slice's keys up to the diagonal in 64-row tiles
+// (double-buffered in LDS, one barrier per tile).  The features of keys and
+// queries are computed once per row and kept in bf16 as the products take
+// them, 4 M bytes per row for as many slices at a time as a workspace of
+// fixed size holds; forming them per (query, key) tile pair instead was two
+// thirds of the products.
+//
+// A wave's scores are formed transposed (rows keys, columns its queries), so
+// they are the operand of the product with V without leaving registers, and
+// the row normaliser is a sum over registers.
+//
+// Bound: instruction issue.  A 32 x 32 score tile is 20 products of 32 cycles
+// and about 150 vector and 40 LDS instructions per wave; the LDS port is a
+// fifth busy (bank conflicts 7 % of that) and the matrix cores a quarter.
+//
+// At B 4, H 8, L 8192, C 1024, d 64, M 256, forward and backward: 8.42 ms with
+// one launch per slice and pass, 32-row tiles and the features formed again
+// for every tile pair; 1.92 ms with 128-row blocks; 1.59 ms with 256.  Of
+// those: dq 0.53, dk 0.44, features 0.19, fwd 0.17, key sums 0.15.
+#include <algorithm>
+
+#include "slim_quad.hpp"
 
 namespace slim {
+namespace quad {
 
-template <class G>
-struct QuadLds {
-  typedef typename G::T T;
-  static constexpr int D = G::D, FW = G::FW, TR = G::TR;
-  static constexpr int LDQ = D + 8;        // row tiles
-  static constexpr int LDZ = TR + 8;       // K~ as [feature][row], per wave
-  static constexpr int LDR = D + 4;        // reduction rows (floats)
-  static constexpr size_t TILE = al16((size_t)TR * LDQ * sizeof(T));
-  static constexpr size_t oQ = 0, oK = TILE, oV = 2 * TILE;
-  static constexpr size_t oF = 3 * TILE;   // floats: kn[TR], qmx[4][TR]
-  static constexpr size_t oZ = oF + al16(5 * TR * sizeof(float));
-  static constexpr size_t ZW = al16((size_t)FW * LDZ * sizeof(T));
-  static constexpr size_t oR = oZ + 4 * ZW;
-  static constexpr size_t RW = al16((size_t)TR * LDR * sizeof(float));
-  static constexpr size_t TOTAL = oR + 4 * RW;
-};
+// ---- W as bf16: hi [M][D], lo [M][D] (hi + lo carries about 16 bits of W),
+// and hi transposed [D][M] in slot order
+template <int D, int M>
+__global__ __launch_bounds__(256) void prep_kernel(QuadArgs a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= M * D) return;
+  bf16* t = (bf16*)a.wtab;
+  const int m = i / D, e = i % D;
+  const float x = a.W[i];
+  t[i] = (bf16)x;
+  t[M * D + i] = w_lo<bf16>(x);
+  t[2 * M * D + e * M + slot_pos(m)] = (bf16)x;
+}
 
-// W fragments of wave w's feature tile mt for the logits: the bf16 values and
-// their low parts, from the fragment table
-template <class G>
-struct QuadW {
-  typedef typename FragT<typename G::T>::type F;
-  __amdgpu_buffer_rsrc_t rs;
-  int lane_off;
-  __device__ QuadW(const void* table) {
-    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(table), (short)0,
-                                           (int)(WFragLayout<G>::TOTAL * 64 * sizeof(F)), 0x00020000);
-    lane_off = lane_id() * (int)sizeof(F);
-  }
-  __device__ __forceinline__ F load(int idx) const {
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 v[sizeof(F) / 16];
+// ---- features of the group's rows.  W (hi and lo) sits in LDS; a wave takes
+// 32 rows at a time, keys and queries of all heads dealt round.
+template <int D, int M>
+__global__ __launch_bounds__(256, 2) void feat_kernel(QuadArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16 Ws[2 * M * D];
+  const int w = uniform_wave();
+  for (int ch = threadIdx.x; ch < 2 * M * D / 8; ch += 256)
+    *reinterpret_cast<u32x4*>(chunk_at<D>(Ws, ch / (D / 8), ch % (D / 8))) = *reinterpret_cast<const u32x4*>((const bf16*)a.wtab + 8 * ch);
+  __syncthreads();
+  const int tiles = (a.n + 31) / 32, total = 2 * a.H * tiles;
+  for (int idx = blockIdx.x * 4 + w; idx < total; idx += gridDim.x * 4) {
+  const int lane = fresh_tid() & 63, h = lane >> 5, i = lane & 31;
+  const int hq = idx / tiles;
+  const bool query = hq >= a.H;
+  const size_t head = query ? hq - a.H : hq;
+  const int row = (idx - hq * tiles) * 32 + i;
+  const bf16* X = (const bf16*)(query ? a.Q : a.K) + (head * a.L + a.row0 + min(row, a.n - 1)) * D;
+  bf16x8 x[D / 16];
 #pragma unroll
-    for (int i = 0; i < (int)(sizeof(F) / 16); ++i)
-      v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off + 16 * i, idx * 64 * (int)sizeof(F), 0);
-    return __builtin_bit_cast(F, v);
-  }
-  __device__ __forceinline__ void get(int w, int mt, F (&hi)[G::EB], F (&lo)[G::EB]) const {
+  for (int kk = 0; kk < D / 16; ++kk) x[kk] = ld8(X + 16 * kk + 8 * h);
+  bf16* out = (bf16*)(query ? a.FQ : a.FK) + (head * a.n + min(row, a.n - 1)) * M + 8 * h;
+  const bool ok = row < a.n;
+  auto logit_tile = [&](int mt) {
+    f32x16 acc = zero16();
 #pragma unroll
-    for (int kb = 0; kb < G::EB; ++kb) {
-      hi[kb] = load(WFragLayout<G>::a(w, mt, kb));
-      lo[kb] = load(WFragLayout<G>::alo(w, mt, kb));
+    for (int kk = 0; kk < D / 16; ++kk) {
+      acc = mma32(acc, row_op<D>(Ws, 32 * mt + i, kk, h), x[kk]);
+      acc = mma32(acc, row_op<D>(Ws, M + 32 * mt + i, kk, h), x[kk]);
     }
-  }
-};
-
-// Forward of one slice: grid (nwg, H, B); workgroup x takes the slice's
-// query tiles x, x + nwg, ...
-template <class G, bool DROP>
-__global__ __launch_bounds__(256, 2) void quad_fwd_kernel(QuadArgs a) {
-  typedef typename G::T T;
-  typedef typename FragT<T>::type F;
-  typedef QuadLds<G> Lay;
-  constexpr int D = G::D, FW = G::FW, M = G::M, TR = G::TR, MT = G::MT, MB = G::MB, ET = G::ET, RT = G::RT;
-  constexpr int LDQ = Lay::LDQ, LDZ = Lay::LDZ, LDR = Lay::LDR;
-  constexpr int TPR = 256 / TR, EPT = D / TPR;
-  static_assert(RT == 2 && G::RB == 1 && MT % 2 == 0, "32-row tiles, whole 32-deep feature blocks");
-
-  __shared__ __attribute__((aligned(16))) char arena[Lay::TOTAL];
-  T* Qs = (T*)(arena + Lay::oQ);
-  T* Ks = (T*)(arena + Lay::oK);
-  T* Vs = (T*)(arena + Lay::oV);
-  float* kn = (float*)(arena + Lay::oF);
-  float* qmx = kn + TR;  // [4][TR]
-  const int w = wave_id();
-  T* Zk = (T*)(arena + Lay::oZ + w * Lay::ZW);  // K~ as [m][s]
-  auto red = [&](int ww) -> float* { return (float*)(arena + Lay::oR + ww * Lay::RW); };
-
-  const int hd = blockIdx.y, b = blockIdx.z;
-  const size_t head = (size_t)b * a.H + hd;
-  const size_t hoff = head * (size_t)a.L * D;
-  const T* Qh = (const T*)a.Q + hoff;
-  const T* Kh = (const T*)a.K + hoff;
-  const T* Vh = (const T*)a.V + hoff;
-  T* Yh = (T*)a.Y + hoff;
-  const QuadW<G> wt(a.Wfrag);
-  const Drop drop{a.drop_seed, a.drop_t, a.C, head};
-  const float half_log2M = 0.5f * __log2f((float)M);
-  const float koff = (G::KIND == kFavor) ? a.kshift[head] * kLog2e + half_log2M : 0.f;
-
-  // this wave's share of the state before the slice: S[mt][et] rows m,
-  // columns e; S[mt][ET] the ones column (z) replicated over 16 columns
-  f32x4 S[MT][ET + 1];
-  {
-    const Lane L = this_lane();
-    const float* sp = a.S + head * (size_t)M * (D + 1);
+    return acc;
+  };
+  auto put_tile = [&](int mt, const f32x16& f) {
+    if (!ok) return;
+    *reinterpret_cast<bf16x8*>(out + 32 * mt) = pack8(f, 0);
+    *reinterpret_cast<bf16x8*>(out + 32 * mt + 16) = pack8(f, 1);
+  };
+  if (a.kind == kFavor && query) {
+    f32x16 l[M / 32];
+    float mx = -INFINITY;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < M / 32; ++mt) {
+      l[mt] = logit_tile(mt);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const size_t row = (size_t)(w * FW + 16 * mt + 4 * L.g + r) * (D + 1);
-#pragma unroll
-        for (int et = 0; et < ET; ++et) S[mt][et][r] = sp[row + 16 * et + L.c];
-        S[mt][ET][r] = sp[row + D];
-      }
-  }
-  // the state as operands contracting over this wave's features, columns e
-  F sf[MB][ET + 1];
-#pragma unroll
-  for (int kb = 0; kb < MB; ++kb)
-#pragma unroll
-    for (int et = 0; et <= ET; ++et) sf[kb][et] = tile_pair_frag<T>(S[2 * kb][et], S[2 * kb + 1][et]);
-
-  const int nt = (a.rows + TR - 1) / TR;
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    const int q0 = a.row0 + t * TR, qcount = min(TR, a.rows - t * TR);
-    __syncthreads();  // the previous tile's readers of Qs and the reduction rows are done
-    load_rows<T, D, TR, LDQ, 256>(Qs, Qh + (size_t)q0 * D, qcount, nullptr);
-    __syncthreads();
-    Lane L = fresh_lane();
-    // query logits Lq[mt][tt]: rows m, columns t (the -|q|^2/2 term cancels
-    // against the row shift)
-    f32x4 Lq[MT][RT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      F hi[G::EB], lo[G::EB];
-      wt.get(w, mt, hi, lo);
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int kb = 0; kb < G::EB; ++kb) {
-          const F qf = frag_rm(L, Qs, LDQ, 16 * tt, 32 * kb);
-          acc = mma(acc, hi[kb], qf);
-          acc = mma(acc, lo[kb], qf);
-        }
-        Lq[mt][tt] = acc;
-      }
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, l[mt][r]);
+      __builtin_amdgcn_sched_barrier(0);  // (no registers for further tiles' operands)
     }
-    if (G::KIND == kFavor) {
+    const float off = fmaxf(mx, __shfl_xor(mx, 32, 64)) * kLog2e;
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        float v = -INFINITY;
+    for (int mt = 0; mt < M / 32; ++mt) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v = fmaxf(v, Lq[mt][tt][r]);
-        v = wave_max_over_g(v);
-        if (L.g == 0) qmx[w * TR + 16 * tt + L.c] = v;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        const int tr = 16 * tt + L.c;
-        const float qs = fmaxf(fmaxf(qmx[tr], qmx[TR + tr]), fmaxf(qmx[2 * TR + tr], qmx[3 * TR + tr])) * kLog2e;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) Lq[mt][tt][r] = fast_exp2(Lq[mt][tt][r] * kLog2e - qs);
-      }
-    } else {
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) Lq[mt][tt][r] = plain_feature<G::KIND>(Lq[mt][tt][r], a.relu_eps);
+      for (int r = 0; r < 16; ++r) l[mt][r] = fast_exp2(l[mt][r] * kLog2e - off);
+      put_tile(mt, l[mt]);
     }
-    // Q~ contracting over this wave's features, columns t
-    F qf[MB][RT];
+    continue;
+  }
+  float off = 0.f;  // keys, FAVOR+: exp2(l log2(e) - off)
+  if (a.kind == kFavor) {
+    float s = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < MB; ++kb)
+    for (int kk = 0; kk < D / 16; ++kk) {
+      const f32x8 v = __builtin_convertvector(x[kk], f32x8);
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) qf[kb][tt] = tile_pair_frag<T>(Lq[2 * kb][tt], Lq[2 * kb + 1][tt]);
+      for (int k = 0; k < 8; ++k) s = fmaf(v[k], v[k], s);
+    }
+    s += __shfl_xor(s, 32, 64);
+    off = a.kshift[head] * kLog2e + 0.5f * __log2f((float)M) + 0.5f * kLog2e * s;
+  }
+  // (ReLU: the derivative's 0/1 decision is read back as phi > eps, so a
+  // positive logit's feature must round above eps)
+  const float eb = (float)(bf16)a.relu_eps;
+  const float up = __uint_as_float(__float_as_uint(eb) + 0x10000u);  // the next bf16
+#pragma unroll 2
+  for (int mt = 0; mt < M / 32; ++mt) {
+    f32x16 f = logit_tile(mt);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x0 = f[r];
+      f[r] = a.kind == kFavor ? fast_exp2(x0 * kLog2e - off) : x0 > 0.f ? fmaxf(x0 + a.relu_eps, up) : eb;
+    }
+    put_tile(mt, f);
+  }
+  }
+}
 
-    // this wave's share of N^T[e][t]: the state before the slice first
-    f32x4 nacc[ET + 1][RT];
-#pragma unroll
-    for (int et = 0; et <= ET; ++et)
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int kb = 0; kb < MB; ++kb) acc = mma(acc, sf[kb][et], qf[kb][tt]);
-        nacc[et][tt] = acc;
-      }
+// one entry [m][e] of a state table
+template <int D, int M>
+__device__ __forceinline__ void put_entry(char* table, bool both, int m, int e, float v) {
+  bf16* T = (bf16*)table;
+  if (e < D) {
+    T[e * M + slot_pos(m)] = (bf16)v;
+    if (both) T[M * D + m * D + slot_pos(e)] = (bf16)v;
+  } else {
+    ((float*)(T + (both ? 2 : 1) * M * D))[m] = v;
+  }
+}
 
-    // then every key tile of the slice up to the diagonal
-    for (int u = 0; u <= t; ++u) {
-      const int k0 = a.row0 + u * TR, kcount = min(TR, a.rows - u * TR);
-      __syncthreads();  // readers of the previous key tile are done
-      load_rows<T, D, TR, LDQ, 256>(Ks, Kh + (size_t)k0 * D, kcount, G::KIND == kFavor ? kn : nullptr);
-      if constexpr (DROP) {
-        // value rows with the dropped elements zeroed (16-byte chunks)
-        constexpr int VEC = 16 / sizeof(T), CPR = D / VEC;
-        for (int ch = threadIdx.x; ch < TR * CPR; ch += 256) {
-          const int r = ch / CPR, cc = ch - (ch / CPR) * CPR;
-          uint4 v = {0u, 0u, 0u, 0u};
-          if (r < kcount) v = *reinterpret_cast<const uint4*>(Vh + (size_t)(k0 + r) * D + cc * VEC);
-          drop_chunk<T>(v, drop, k0 + r, cc * VEC);
-          *reinterpret_cast<uint4*>(Vs + r * LDQ + cc * VEC) = v;
-        }
-      } else {
-        load_rows<T, D, TR, LDQ, 256>(Vs, Vh + (size_t)k0 * D, kcount, nullptr);
+// ---- state before every slice of the group (running sum of the parts) and
+// after the group; one thread per entry, grid (entries / 256, heads)
+template <int D, int M>
+__global__ __launch_bounds__(256) void states_kernel(QuadArgs a, int both) {
+  const int el = blockIdx.x * 256 + threadIdx.x;
+  constexpr int SZ = M * (D + 1);
+  if (el >= SZ) return;
+  const size_t head = blockIdx.y;
+  const int m = el / (D + 1), e = el - m * (D + 1);
+  const int slices = (a.n + a.C - 1) / a.C, spp = a.C / a.part_rows;
+  float v = 0.f;
+  if (a.S_in != nullptr) {
+    v = a.S_in[head * SZ + el];
+    if (a.in_shift != nullptr) v *= fast_exp2((a.in_shift[head] - a.kshift[head]) * kLog2e);
+  }
+  const float* part = a.part + head * a.parts * (size_t)SZ + el;
+  const size_t tb = (size_t)M * D * 2 * (both ? 2 : 1) + M * 4;
+  char* tab = (char*)a.ST + head * slices * tb;
+  if (a.down) {
+    float s = 0.f;
+    for (int p = 0; p < a.parts; p += 8) {
+      float x[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = p + k < a.parts ? part[(size_t)(p + k) * SZ] : 0.f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s += x[k];
+    }
+    v -= s;
+    if (a.S_out != nullptr) a.S_out[head * SZ + el] = v;
+  }
+  for (int p = 0; p < a.parts; p += 8) {
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = p + k < a.parts ? part[(size_t)(p + k) * SZ] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (p + k < a.parts) {
+        if ((p + k) % spp == 0) put_entry<D, M>(tab + (size_t)((p + k) / spp) * tb, both != 0, m, e, v);
+        v += x[k];
       }
-      __syncthreads();
-      L = fresh_lane();
-      // key features of this wave's features -> Zk[m][s] (rows past the
-      // tile: zero)
+  }
+  if (!a.down && a.S_out != nullptr) a.S_out[head * SZ + el] = v;
+}
+
+// ---- outputs: one workgroup per block of queries, the longest first
+template <int D, int M, bool DROP>
+__global__ __launch_bounds__(kTH, 2) void fwd_kernel(QuadArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16 Fs[2][kKT * M];
+  __shared__ __attribute__((aligned(16))) bf16 Vs[2][kKT * D];
+  const int lane = lane_id(), h = lane >> 5, i = lane & 31, w = uniform_wave();
+  const int nb = a.C / kQB, slices = (a.n + a.C - 1) / a.C;
+  const int idx = blockIdx.x;
+  const int head = idx % a.H, sl = idx / a.H % slices, qb = nb - 1 - idx / (a.H * slices);
+  const int s0 = sl * a.C, q0 = s0 + qb * kQB;  // rows of the group
+  if (q0 >= a.n) return;
+  const int q0w = q0 + 32 * w, row = min(q0w + i, a.n - 1);
+  const bf16* FK = (const bf16*)a.FK + (size_t)head * a.n * M;
+  const bf16* FQ = (const bf16*)a.FQ + ((size_t)head * a.n + row) * M + 8 * h;
+  const size_t base = ((size_t)head * a.L + a.row0) * D;
+  const bf16* V = (const bf16*)a.V + base;
+  const char* tab = (const char*)a.ST + ((size_t)head * slices + sl) * quad_table_bytes(D, M, false);
+  const bf16* St = (const bf16*)tab;
+  const float* z = (const float*)(St + M * D);
+  const Drop drop{a.drop_seed, a.drop_t, a.drop_C, (uint64_t)(a.head0 + head)};
+
+  Stage<D, M> sg;
+  sg.fetch(FK + (size_t)s0 * M, V + (size_t)s0 * D, 0, a.n - 1 - s0, fresh_tid());
+  bf16x8 qf[M / 16];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        F hi[G::EB], lo[G::EB];
-        wt.get(w, mt, hi, lo);
+  for (int kb = 0; kb < M / 16; ++kb) qf[kb] = ld8(FQ + 16 * kb);
+  // the state before the slice
+  f32x16 nacc[D / 32];
 #pragma unroll
-        for (int st = 0; st < RT; ++st) {
-          f32x4 acc = zero4();
+  for (int et = 0; et < D / 32; ++et) nacc[et] = zero16();
+  float den = 0.f;
 #pragma unroll
-          for (int kb = 0; kb < G::EB; ++kb) {
-            const F kf = frag_rm(L, Ks, LDQ, 16 * st, 32 * kb);
-            acc = mma(acc, kf, hi[kb]);
-            acc = mma(acc, kf, lo[kb]);
-          }
-          // acc: rows s = 16 st + 4 g + r, columns m = 16 mt + c
+  for (int kb = 0; kb < M / 16; ++kb) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int s = 16 * st + 4 * L.g + r;
-            if (G::KIND == kFavor) {
-              const float kc = s < kcount ? koff + 0.5f * kLog2e * kn[s] : INFINITY;
-              acc[r] = fast_exp2(acc[r] * kLog2e - kc);
-            } else {
-              acc[r] = s < kcount ? plain_feature<G::KIND>(acc[r], a.relu_eps) : 0.f;
-            }
-          }
-          store_tile_T<T>(L, Zk, LDZ, acc, 16 * st, 16 * mt);
-        }
+    for (int et = 0; et < D / 32; ++et) nacc[et] = mma32(nacc[et], ld8(St + (32 * et + i) * M + 16 * kb + 8 * h), qf[kb]);
+    const f32x4 za = ldf4(z + 16 * kb + 4 * h), zb = ldf4(z + 16 * kb + 8 + 4 * h);
+    const f32x8 q = __builtin_convertvector(qf[kb], f32x8);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) den = fmaf(za[k], q[k], fmaf(zb[k], q[4 + k], den));
+  }
+  if (DROP) sg.drop(drop, a.row0 + s0, fresh_tid());
+  sg.template store<true>(Fs[0], Vs[0], fresh_tid());
+  __syncthreads();
+
+  // tiles of 64 keys up to the block's last row
+  const int nt = (min(q0 + kQB, a.n) - s0 + kKT - 1) / kKT;
+  for (int u = 0; u < nt; ++u) {
+    const int bf = u & 1;
+    if (u + 1 < nt) sg.fetch(FK + (size_t)s0 * M, V + (size_t)s0 * D, (u + 1) * kKT, a.n - 1 - s0, fresh_tid());
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int k0 = s0 + u * kKT + 32 * st;
+      if (k0 > q0w) continue;
+      f32x16 acc = zero16();
+#pragma unroll
+      for (int kb = 0; kb < M / 16; ++kb) acc = mma32(acc, row_op<M>(Fs[bf], 32 * st + i, kb, h), qf[kb]);
+      if (k0 == q0w) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (row_of(r, h) > i) acc[r] = 0.f;
       }
-      // scores A^T[s][t] over this wave's features (causal on the diagonal
-      // tile), then N^T += [V|1]^T A^T
-      const bool diag = (u == t);
-      f32x4 At[RT][RT];
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt)
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8 p = pack8(acc, kk);
+        den = sum8(p, den);
 #pragma unroll
-        for (int st = 0; st < RT; ++st) {
-          f32x4 acc = zero4();
-          if (!(diag && st > tt)) {
-#pragma unroll
-            for (int kb = 0; kb < MB; ++kb) acc = mma(acc, frag_tr(L, Zk, LDZ, 32 * kb, 16 * st), qf[kb][tt]);
-            if (diag && st == tt) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (4 * L.g + r > L.c) acc[r] = 0.f;
-            }
-          }
-          At[st][tt] = acc;
-        }
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        const F af = tile_pair_frag<T>(At[0][tt], At[1][tt]);
-#pragma unroll
-        for (int et = 0; et < ET; ++et) nacc[et][tt] = mma(nacc[et][tt], frag_tr(L, Vs, LDQ, 0, 16 * et), af);
-        nacc[ET][tt] = mma(nacc[ET][tt], ones_rows_frag(L, 0, kcount), af);
+        for (int et = 0; et < D / 32; ++et)
+          nacc[et] = mma32(nacc[et], col_op<D, true>(Vs[bf], 32 * st + 16 * kk, 32 * et, lane), p);
       }
     }
-
-    // the waves' shares of N meet in LDS; Y = s N / D
-    L = fresh_lane();
-#pragma unroll
-    for (int tt = 0; tt < RT; ++tt) {
-#pragma unroll
-      for (int et = 0; et < ET; ++et) store_tile_T<float>(L, red(w), LDR, nacc[et][tt], 16 * et, 16 * tt);
-      if (L.g == 0) red(w)[(16 * tt + L.c) * LDR + D] = nacc[ET][tt][0];
+    if (u + 1 < nt) {
+      if (DROP) sg.drop(drop, a.row0 + s0 + (u + 1) * kKT, fresh_tid());
+      sg.template store<true>(Fs[bf ^ 1], Vs[bf ^ 1], fresh_tid());
     }
     __syncthreads();
-    {
-      const int tid = fresh_tid();
-      const int tr = tid / TPR, q = tid % TPR;
-      if (tr < qcount) {
-        const float den = (red(0)[tr * LDR + D] + red(1)[tr * LDR + D]) + (red(2)[tr * LDR + D] + red(3)[tr * LDR + D]);
-        const float inv = a.drop_scale / den;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-          const int e = q * EPT + i;
-          const float n = (red(0)[tr * LDR + e] + red(1)[tr * LDR + e]) + (red(2)[tr * LDR + e] + red(3)[tr * LDR + e]);
-          Yh[(size_t)(q0 + tr) * D + e] = cvt<T>(n * inv);
-        }
-      }
-    }
   }
+  den += __shfl_xor(den, 32, 64);
+  if (q0w + i < a.n) store_row_T<D>((bf16*)a.Y + base + (size_t)(q0w + i) * D, h, nacc, a.drop_scale / den);
+}
+
+template <int D, int M>
+hipError_t launch_dm(int which, const QuadArgs& a, hipStream_t s) {
+  const int slices = (a.n + a.C - 1) / a.C;
+  switch (which) {
+    case kQuadPrep: hipLaunchKernelGGL((prep_kernel<D, M>), dim3((M * D + 255) / 256), dim3(256), 0, s, a); break;
+    case kQuadFeat:
+      hipLaunchKernelGGL((feat_kernel<D, M>), dim3(std::min(512, (2 * a.H * ((a.n + 31) / 32) + 3) / 4)), dim3(256), 0, s, a);
+      break;
+    case kQuadStates:
+      hipLaunchKernelGGL((states_kernel<D, M>), dim3((M * (D + 1) + 255) / 256, a.H), dim3(256), 0, s, a,
+                         a.GT != nullptr ? 1 : 0);
+      break;
+    case kQuadFwd: {
+      const dim3 g(a.C / kQB * slices * a.H);
+      if (a.drop_t != 0) hipLaunchKernelGGL((fwd_kernel<D, M, true>), g, dim3(kTH), 0, s, a);
+      else hipLaunchKernelGGL((fwd_kernel<D, M, false>), g, dim3(kTH), 0, s, a);
+      break;
+    }
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace quad
+
+hipError_t launch_quad(int which, const QuadArgs& a, int d, int M, hipStream_t s) {
+  if (d == 64) return M == 256 ? quad::launch_dm<64, 256>(which, a, s) : quad::launch_dm<64, 128>(which, a, s);
+  return M == 256 ? quad::launch_dm<32, 256>(which, a, s) : quad::launch_dm<32, 128>(which, a, s);
 }
 
 // out = f * in + sign * sum_p part[p], one thread per state entry
@@ -322,17 +321,5 @@ hipError_t launch_state_combine(const float* in, size_t in_stride, const float* 
                      part, P2, sign, out, SZ);
   return hipGetLastError();
 }
-
-template <class G>
-hipError_t launch_quad_fwd(const QuadArgs& a, int nwg, hipStream_t s) {
-  const dim3 grid(nwg, a.H, a.B);
-  if (a.drop_t != 0) hipLaunchKernelGGL((quad_fwd_kernel<G, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((quad_fwd_kernel<G, false>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-#define SLIM_INST_QUAD(T, D, FW, TR, KIND) \
-  template hipError_t launch_quad_fwd<Cfg<T, D, FW, TR, KIND>>(const QuadArgs&, int, hipStream_t);
-SLIM_FOR_EACH_QUAD_CONFIG(SLIM_INST_QUAD)
 
 }  // namespace slim

@@ -1,0 +1,240 @@
+// Building blocks of the quadratic within-slice mode (slim_quad.hip,
+// slim_quad_bwd.hip).
+//
+// Products run on v_mfma_f32_32x32x16_bf16.  With lane = 32 h + i:
+//   operand      lane (h, i), slot s  <->  row/column i, contraction slot (h, s) of a 16-deep block
+//   result       lane (h, i), register r  <->  row (r & 3) + 8 (r >> 2) + 4 h, column i
+// Registers 8 kk .. 8 kk + 7 of a 32 x 32 result are therefore an operand
+// that contracts over the result's rows 16 kk .. 16 kk + 15 in the order
+//   slot (h, s) <-> 16 kk + (s & 3) + 8 (s >> 2) + 4 h,
+// so scores, row cotangents and logit cotangents feed the next product from
+// registers.  The tables those products meet (features, states, W, dN) are
+// stored in that "slot order": inside every 16 elements of a row, position
+// 8 h + s holds element (s & 3) + 8 (s >> 2) + 4 h (the middle two groups of
+// four change places), and a lane's operand is 16 contiguous bytes.  Where
+// the contraction runs over rows of such a tile in LDS instead,
+// ds_read_b64_tr_b16 transposes: it takes groups of four consecutive
+// columns, so the change of places is an address.
+#pragma once
+
+#include "slim_common.hpp"
+#include "slim_kernels.hpp"
+
+namespace slim {
+namespace quad {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kQB = kQuadBlock;    // rows of a block: eight waves of 32
+constexpr int kTH = 2 * kQuadBlock;  // threads
+constexpr int kKT = 64;   // rows of a staged tile
+
+__device__ __forceinline__ f32x16 mma32(const f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.f;
+  return z;
+}
+// registers 8 kk .. 8 kk + 7 as bf16
+__device__ __forceinline__ bf16x8 pack8(const f32x16& x, int kk) {
+  f32x8 v;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) v[s] = x[8 * kk + s];
+  return __builtin_convertvector(v, bf16x8);
+}
+// row of result register r inside its 32-row tile
+__device__ __forceinline__ int row_of(int r, int h) { return (r & 3) + 8 * (r >> 2) + 4 * h; }
+__device__ __forceinline__ bf16x8 ld8(const bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
+__device__ __forceinline__ f32x4 ldf4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
+// Staged tiles: rows of E elements, 16-byte chunks permuted within the row by
+// the row (sw), so that 16 lanes reading one chunk of 16 rows, and the
+// transposing reads of 8 rows x 64 bytes, touch every bank once.
+template <int E>
+__device__ __forceinline__ int chunk_of(int row, int c) {
+  if constexpr (E >= 128) return c ^ (((row & 3) << 2) | ((row >> 2) & 3));  // 16 or 32 chunks
+  else if constexpr (E == 64) return c ^ (((row >> 1) & 1) << 2 | ((row >> 2) & 3));
+  else return c ^ ((row >> 2) & 3);  // four chunks
+}
+template <int E>
+__device__ __forceinline__ bf16* chunk_at(bf16* Z, int row, int c) {
+  return Z + row * E + 8 * chunk_of<E>(row, c);
+}
+// operand: row `row` of the tile, 16-deep block kb of its columns (slot order)
+template <int E>
+__device__ __forceinline__ bf16x8 row_op(const bf16* Z, int row, int kb, int h) {
+  return ld8(chunk_at<E>(const_cast<bf16*>(Z), row, 2 * kb + h));
+}
+// operand contracting over the tile's rows [r0, r0 + 16) (in slot order),
+// columns [c0, c0 + 32): lane i takes column element c0 + i.  SLOT: the
+// tile's rows are in slot order.
+template <int E, bool SLOT>
+__device__ __forceinline__ bf16x8 col_op(const bf16* Z, int r0, int c0, int lane) {
+  const int h = lane >> 5, j = lane & 15, half = (lane >> 4) & 1, q = j & 3;
+  const int e = c0 + 16 * half + 4 * (SLOT ? ((q & 1) << 1 | q >> 1) : q);
+  const int ra = r0 + 4 * h + (j >> 2);
+  typedef SLIM_LDS i16x4 lds_i16x4;
+  const bf16* pa = Z + ra * E + 8 * chunk_of<E>(ra, e >> 3) + (e & 7);
+  const bf16* pb = Z + (ra + 8) * E + 8 * chunk_of<E>(ra + 8, e >> 3) + (e & 7);
+  const bf16x4 a = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)pa));
+  const bf16x4 b = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)pb));
+  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// a 16-byte chunk of eight consecutive elements (chunk c of a row) into a
+// slot-order tile: its halves go to different chunks
+template <int E>
+__device__ __forceinline__ void put_natural(bf16* Z, int row, int c, const u32x4& v) {
+  const int k0 = c & ~1, off = 4 * (c & 1);
+  *reinterpret_cast<u32x2*>(chunk_at<E>(Z, row, k0) + off) = v.xy;
+  *reinterpret_cast<u32x2*>(chunk_at<E>(Z, row, k0 + 1) + off) = v.zw;
+}
+// where element e of a row sits in slot order
+__device__ __forceinline__ int slot_pos(int e) { return (e & ~15) | ((e >> 2 & 1) << 3) | ((e >> 3 & 1) << 2) | (e & 3); }
+
+// Z[row][0..D) of a [rows][D] bf16 tensor as registers of the transposed
+// result layout: x[et][r] = X[row][32 et + row_of(r, h)]
+template <int D>
+__device__ __forceinline__ void load_row_T(const bf16* row, int h, f32x16 (&x)[D / 32]) {
+#pragma unroll
+  for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 v = __builtin_convertvector(*reinterpret_cast<const bf16x4*>(row + 32 * et + 8 * a + 4 * h), f32x4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[et][4 * a + j] = v[j];
+    }
+}
+template <int D>
+__device__ __forceinline__ void store_row_T(bf16* row, int h, const f32x16 (&x)[D / 32], float scale) {
+#pragma unroll
+  for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = scale * x[et][4 * a + j];
+      *reinterpret_cast<bf16x4*>(row + 32 * et + 8 * a + 4 * h) = pk_bf16x4(v);
+    }
+}
+
+// Two staged tensors of a 64-row tile, fetched into registers one tile ahead:
+// F rows of M elements (slot order, copied) and X rows of D elements (natural
+// order for V, slot order for dN).
+template <int D, int M>
+struct Stage {
+  static constexpr int CF = M / 8, CX = D / 8;  // chunks per row
+  static constexpr int NF = kKT * CF / kTH, NX = (kKT * CX + kTH - 1) / kTH;
+  u32x4 f[NF], x[NX];
+  // rows r0 .. r0 + 63 of the tensors (row indices past `last` read row `last`)
+  __device__ __forceinline__ void fetch(const bf16* F, const bf16* X, int r0, int last, int tid) {
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+      const int ch = tid + kTH * k, r = min(r0 + ch / CF, last);
+      f[k] = *reinterpret_cast<const u32x4*>(F + (size_t)r * M + 8 * (ch % CF));
+    }
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int ch = (tid + kTH * k) & (kKT * CX - 1), r = min(r0 + ch / CX, last);  // (D = 32: twice the same)
+      x[k] = *reinterpret_cast<const u32x4*>(X + (size_t)r * D + 8 * (ch % CX));
+    }
+  }
+  // value dropout; l0: the sequence row of the tile's first row
+  __device__ __forceinline__ void drop(const Drop& dp, int l0, int tid) {
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int ch = (tid + kTH * k) & (kKT * CX - 1);
+      uint4 v = {x[k].x, x[k].y, x[k].z, x[k].w};
+      drop_chunk<bf16>(v, dp, l0 + ch / CX, 8 * (ch % CX));
+      x[k] = u32x4{v.x, v.y, v.z, v.w};
+    }
+  }
+  template <bool NATURAL>
+  __device__ __forceinline__ void store(bf16* Fs, bf16* Xs, int tid) const {
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+      const int ch = tid + kTH * k;
+      *reinterpret_cast<u32x4*>(chunk_at<M>(Fs, ch / CF, ch % CF)) = f[k];
+    }
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int ch = (tid + kTH * k) & (kKT * CX - 1);
+      if constexpr (NATURAL) put_natural<D>(Xs, ch / CX, ch % CX, x[k]);
+      else *reinterpret_cast<u32x4*>(chunk_at<D>(Xs, ch / CX, ch % CX)) = x[k];
+    }
+  }
+};
+
+// sum of the eight bf16 values of f, added to acc (products with one, two at a time)
+__device__ __forceinline__ float sum8(const bf16x8& f, float acc) {
+  const bf16x2 one = {(bf16)1.f, (bf16)1.f};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{f[2 * k], f[2 * k + 1]}, one, acc, false);
+  return acc;
+}
+
+// chain rule of the features: the logit cotangents of a wave's 32 rows from
+// dg (rows m, columns the wave's rows) and the row's features F (slot order),
+// as operands (zero for rows past the end), also into the block tile Z;
+// returns the rows' sums
+template <int M>
+__device__ __forceinline__ float coefficients(int kind, const f32x16 (&dg)[M / 32], const bf16* F, float eps, bool ok,
+                                              bf16x8 (&cb)[M / 16], bf16* Z, int row, int h) {
+  eps = (float)(bf16)eps;  // (a positive logit's feature is above it, see feat_kernel)
+  float cs = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < M / 16; ++kb) {
+    const f32x8 phi = __builtin_convertvector(ld8(F + 16 * kb), f32x8);
+    f32x8 v;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float x = dg[kb / 2][8 * (kb & 1) + s];
+      v[s] = kind == kFavor ? x * phi[s] : (phi[s] > eps ? x : 0.f);
+      cs += v[s];
+    }
+    cb[kb] = __builtin_convertvector(v, bf16x8);
+    if (!ok) cb[kb] = bf16x8{};
+    *reinterpret_cast<bf16x8*>(chunk_at<M>(Z, row, 2 * kb + h)) = cb[kb];
+  }
+  return cs + __shfl_xor(cs, 32, 64);
+}
+
+// out[m][e] (+)= sum over the block's rows of Z[row][m] X[row][e], both in LDS
+// in slot order, pitch ldo of out; the M / 32 x D / 32 result tiles go round
+// the waves by features (M = 128: two waves share a feature tile's columns).
+template <int D, int M, bool ADD>
+__device__ __forceinline__ void block_product(const bf16* Z, const bf16* X, float* out, int ldo, int w, int lane) {
+  constexpr int MT = M / 32, ET = D / 32;
+  constexpr int EW = MT == 8 ? ET : (ET == 2 ? 1 : ET);  // column tiles of a wave
+  const int h = lane >> 5, i = lane & 31;
+  const int mt = w % MT, e0 = MT == 8 ? 0 : (w / MT) * EW;
+  if (e0 >= ET) return;
+  f32x16 acc[EW];
+#pragma unroll
+  for (int et = 0; et < EW; ++et) acc[et] = zero16();
+#pragma unroll
+  for (int kb = 0; kb < kQB / 16; ++kb) {
+    const bf16x8 a = col_op<M, true>(Z, 16 * kb, 32 * mt, lane);
+#pragma unroll
+    for (int et = 0; et < EW; ++et) acc[et] = mma32(acc[et], a, col_op<D, true>(X, 16 * kb, 32 * (e0 + et), lane));
+  }
+#pragma unroll
+  for (int et = 0; et < EW; ++et) {
+    float* o = out + (size_t)(32 * mt + 4 * h) * ldo + 32 * (e0 + et) + i;
+    f32x16 old = zero16();
+    if constexpr (ADD) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) old[r] = o[((r & 3) + 8 * (r >> 2)) * ldo];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[((r & 3) + 8 * (r >> 2)) * ldo] = old[r] + acc[et][r];
+  }
+}
+
+}  // namespace quad
+}  // namespace slim

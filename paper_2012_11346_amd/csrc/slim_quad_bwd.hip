@@ -1,921 +1,503 @@
-// Backward of the quadratic within-slice mode: Algorithm 1's reverse sweep
-// with each slice's gradients taken from the masked quadratic form of eq. 2.
-// For slice n, with [S|z] the state before it (eq. 17 downdates it from the
-// state after it) and G the state cotangent after it (eq. 18), rows t, s of
-// the slice and A[t][s] = Q~_t . K~_s (s <= t):
+// Backward of the quadratic within-slice mode (slim_quad.hip), the slices of
+// a group in parallel, per 256-row block (eqs. 17-18 with the masked
+// quadratic form of eq. 2 inside a slice):
 //
-//   query pass  N_t, D_t recomputed as in the forward; dN_t = s dY_t / D_t,
-//               dD_t = -(dY_t . Y_t) / D_t (stored with the row shift of Q~);
-//               dQ~_t = [S|z] [dN_t|dD_t] + sum_{s <= t} dA[t][s] K~_s with
-//               dA[t][s] = dN_t . V_s + dD_t; dQ and the query share of dW
-//   key pass    dK~_s = [V_s|1] G^T + sum_{t >= s} dA[t][s] Q~_t,
-//               dV_s = K~_s G + sum_{t >= s} A[t][s] dN_t; dK, dV and the
-//               key share of dW
-//   G sum       G before the slice = G + sum_t Q~_t^T [dN_t|dD_t]
+//   dq: N and D again from the state before the slice and its keys; the rows
+//       dN = s dY / D, dD = -(dY . Y) / D; dg(q) = S dN + z dD + sum_{s <= t}
+//       dA_ts g(k_s) with dA_ts = dN_t . v_s + dD_t; dQ and the block's share
+//       of dW; what the block adds to the cotangent, g(Q)^T [dN | dD].
+//   cot: the cotangent [G | gz] after every slice.
+//   dk: dv_s = G^T g(k_s) + sum_{t >= s} (g(q_t) . g(k_s)) dN_t; dg(k_s) =
+//       G v_s + gz + sum_{t >= s} dA_ts g(q_t); dK, dV and the share of dW.
 //
-// The passes take the 32-row tiles of the slice in parallel (one workgroup
-// per tile, or several tiles per workgroup) and recompute the features of
-// the other side for every tile pair.  The states enter as fragment tables
-// (state_frag_kernel), so that neither pass holds a state in registers or
-// LDS.  Each tile's dW share is added to its workgroup's own partial (one
-// slot per workgroup, kept across the slices); the partials are summed in a
-// fixed order at the end.
-#include "slim_common.hpp"
-#include "slim_kernels.hpp"
+// Everything is formed transposed, columns the wave's own 32 rows, so that
+// scores, row cotangents and logit cotangents stay in registers from one
+// product to the next; only dW and the cotangent sums, which contract over
+// the block's rows, pass through LDS (in the buffers of the finished stream).
+// Each of dq and dk streams its rows twice, so that a wave never holds the
+// features (operand of the scores) and the accumulators of dg (M / 32 result
+// tiles of 16 registers) at once: two waves fit per SIMD.
+#include "slim_quad.hpp"
 
 namespace slim {
+namespace quad {
 
-// Fragment tables of a state X = [S|z] (M x (D + 1), fp32) as bf16 operands:
-//   block T1 [w][mt][kb]: slot s = X[w FW + 16 mt + c][32 kb + kp(g, s)]           (rows m, contracting over e)
-//   block T2 [w][kb][et]: slot s = X[w FW + 32 kb + kp(g, s)][16 et + c] for et < ET,
-//                         X[w FW + 32 kb + kp(g, s)][D] for et == ET               (contracting over m)
-template <class G>
-struct StateFragLayout {
-  static constexpr int N1 = G::MT * G::EB;
-  static constexpr int N2 = G::MB * (G::ET + 1);
-  static constexpr int TOTAL = 4 * (N1 + N2);  // fragments per head
-  __device__ static int t1(int w, int mt, int kb) { return w * N1 + mt * G::EB + kb; }
-  __device__ static int t2(int w, int kb, int et) { return 4 * N1 + w * N2 + kb * (G::ET + 1) + et; }
-};
-
-// grid (TOTAL, BH, n states), 64 threads: one fragment per wave
-template <class G>
-__global__ __launch_bounds__(64) void state_frag_kernel(const float* X0, bf16x8* F0, const float* X1, bf16x8* F1) {
-  typedef StateFragLayout<G> SL;
-  constexpr int D = G::D, FW = G::FW, M = G::M, EB = G::EB, ET = G::ET;
-  const int f = blockIdx.x, head = blockIdx.y;
-  const float* X = (blockIdx.z ? X1 : X0) + (size_t)head * M * (D + 1);
-  bf16x8* F = (blockIdx.z ? F1 : F0) + (size_t)head * SL::TOTAL * 64;
-  const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-  bf16x8 v;
-  if (f < 4 * SL::N1) {
-    const int w = f / SL::N1, rem = f - w * SL::N1, mt = rem / EB, kb = rem - mt * EB;
-    const float* row = X + (size_t)(w * FW + 16 * mt + c) * (D + 1) + 32 * kb;
+// dx = W^T times the logit cotangents, minus x times their sum (the norm
+// term, FAVOR+), for the lane's row x
+template <int D, int M>
+__device__ __forceinline__ void chain(const QuadArgs& a, const bf16x8 (&cb)[M / 16], float cs, const bf16* xrow,
+                                      bf16* out, bool ok, int lane) {
+  const int h = lane >> 5, i = lane & 31;
+  const bf16* WT = (const bf16*)a.wtab + 2 * M * D + 8 * h;
+  f32x16 x[D / 32];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = cvt<bf16>(row[kp(g, s)]);
-  } else {
-    const int f2 = f - 4 * SL::N1, w = f2 / SL::N2, rem = f2 - w * SL::N2, kb = rem / (ET + 1), et = rem - kb * (ET + 1);
-    const int col = et < ET ? 16 * et + c : D;
+  for (int et = 0; et < D / 32; ++et) x[et] = zero16();
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = cvt<bf16>(X[(size_t)(w * FW + 32 * kb + kp(g, s)) * (D + 1) + col]);
+  for (int kb = 0; kb < M / 16; ++kb)
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et) x[et] = mma32(x[et], ld8(WT + (32 * et + i) * M + 16 * kb), cb[kb]);
+  if (a.kind == kFavor) {
+    f32x16 xr[D / 32];
+    load_row_T<D>(xrow, h, xr);
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[et][r] = fmaf(-xr[et][r], cs, x[et][r]);
   }
-  F[(size_t)f * 64 + lane] = v;
+  if (ok) store_row_T<D>(out, h, x, 1.f);
 }
 
-// W fragments of wave w's feature tile mt for the logits: the bf16 values and
-// their low parts, from the fragment table
-template <class G>
-struct QuadWb {
-  typedef typename FragT<typename G::T>::type F;
-  const F* tab;
-  int lane;
-  __device__ explicit QuadWb(const void* table) : tab((const F*)table), lane(lane_id()) {}
-  __device__ __forceinline__ void get(int w, int mt, F (&hi)[G::EB], F (&lo)[G::EB]) const {
+// the block's rows of X (natural order) into a block tile in slot order;
+// rows past `last` repeat it
+template <int D>
+__device__ __forceinline__ void stage_block(bf16* Xs, const bf16* X, int r0, int last, int tid) {
+  constexpr int CX = D / 8;
 #pragma unroll
-    for (int kb = 0; kb < G::EB; ++kb) {
-      hi[kb] = tab[WFragLayout<G>::a(w, mt, kb) * 64 + lane];
-      lo[kb] = tab[WFragLayout<G>::alo(w, mt, kb) * 64 + lane];
+  for (int k = 0; k < kQB * CX / kTH; ++k) {
+    const int ch = tid + kTH * k;
+    put_natural<D>(Xs, ch / CX, ch % CX,
+                   *reinterpret_cast<const u32x4*>(X + (size_t)min(r0 + ch / CX, last) * D + 8 * (ch % CX)));
+  }
+}
+// a wave's 32 rows of operands (columns its rows) into a block tile
+template <int E>
+__device__ __forceinline__ void put_rows(bf16* Z, const bf16x8 (&f)[E / 16], int row, int h) {
+#pragma unroll
+  for (int kb = 0; kb < E / 16; ++kb) *reinterpret_cast<bf16x8*>(chunk_at<E>(Z, row, 2 * kb + h)) = f[kb];
+}
+
+template <int D, int M, bool DROP>
+__global__ __launch_bounds__(kTH, 2) void dq_kernel(QuadArgs a) {
+  // stream: [2][64][M] key features, [2][64][D] values; then [256][M], [256][D]
+  __shared__ __attribute__((aligned(16))) bf16 Fs[kQB * M];
+  __shared__ __attribute__((aligned(16))) bf16 Vs[kQB * D];
+  const int w = uniform_wave();
+  const int nb = a.C / kQB, slices = (a.n + a.C - 1) / a.C, total = nb * slices * a.H;
+  for (int idx = blockIdx.x; idx < total; idx += gridDim.x) {
+    int tid = fresh_tid(), lane = tid & 63, h = lane >> 5, i = lane & 31;
+    // (lane coordinates formed anew per phase: kept addresses would spill)
+    auto phase = [&] {
+      tid = fresh_tid();
+      lane = tid & 63;
+      h = lane >> 5;
+      i = lane & 31;
+    };
+    const int head = idx % a.H, sl = idx / a.H % slices, qb = nb - 1 - idx / (a.H * slices);
+    const int s0 = sl * a.C, q0 = s0 + qb * kQB;
+    if (q0 >= a.n) continue;
+    const int q0w = q0 + 32 * w, row = min(q0w + i, a.n - 1);
+    const bool ok = q0w + i < a.n;
+    const bf16* FK = (const bf16*)a.FK + ((size_t)head * a.n + s0) * M;
+    const bf16* FQ = (const bf16*)a.FQ + ((size_t)head * a.n + row) * M + 8 * h;
+    const size_t base = ((size_t)head * a.L + a.row0) * D;
+    const bf16* V = (const bf16*)a.V + base + (size_t)s0 * D;
+    const char* tab = (const char*)a.ST + ((size_t)head * slices + sl) * quad_table_bytes(D, M, true);
+    const bf16* St = (const bf16*)tab;
+    const bf16* Sm = St + M * D;
+    const float* z = (const float*)(St + 2 * M * D);
+    const Drop drop{a.drop_seed, a.drop_t, a.drop_C, (uint64_t)(a.head0 + head)};
+    const int last = a.n - 1 - s0;
+    const int nt = (min(q0 + kQB, a.n) - s0 + kKT - 1) / kKT;
+
+    Stage<D, M> sg;
+    sg.fetch(FK, V, 0, last, fresh_tid());
+    bf16x8 qf[M / 16];
+#pragma unroll
+    for (int kb = 0; kb < M / 16; ++kb) qf[kb] = ld8(FQ + 16 * kb);
+    f32x16 nacc[D / 32];
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et) nacc[et] = zero16();
+    float den = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < M / 16; ++kb) {
+#pragma unroll
+      for (int et = 0; et < D / 32; ++et)
+        nacc[et] = mma32(nacc[et], ld8(St + (32 * et + i) * M + 16 * kb + 8 * h), qf[kb]);
+      const f32x4 za = ldf4(z + 16 * kb + 4 * h), zb = ldf4(z + 16 * kb + 8 + 4 * h);
+      const f32x8 q = __builtin_convertvector(qf[kb], f32x8);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) den = fmaf(za[k], q[k], fmaf(zb[k], q[4 + k], den));
     }
-  }
-  __device__ __forceinline__ F b(int w, int kb, int et) const { return tab[WFragLayout<G>::b(w, kb, et) * 64 + lane]; }
-};
-
-// Query features of a staged 32-row tile into Zq[t][m] (this wave's
-// features; rows past `count` zero).  FAVOR+ rows are shifted by `qs` (log2
-// units): the query pass takes the row maxima (qmx, over all waves), the
-// key pass and the G sum the shifts the query pass stored.
-template <class G>
-__device__ __forceinline__ void query_logits(const Lane& L, const QuadWb<G>& wt, int w, const typename G::T* Qs,
-                                             f32x4 (&Lq)[G::MT][G::RT]) {
-  typedef typename FragT<typename G::T>::type F;
-#pragma unroll
-  for (int mt = 0; mt < G::MT; ++mt) {
-    F hi[G::EB], lo[G::EB];
-    wt.get(w, mt, hi, lo);
-#pragma unroll
-    for (int tt = 0; tt < G::RT; ++tt) {
-      f32x4 acc = zero4();
-#pragma unroll
-      for (int kb = 0; kb < G::EB; ++kb) {
-        const F qf = frag_rm(L, Qs, G::D + 8, 16 * tt, 32 * kb);
-        acc = mma(acc, hi[kb], qf);
-        acc = mma(acc, lo[kb], qf);
-      }
-      Lq[mt][tt] = acc;
-    }
-  }
-}
-
-// Key features of a staged 32-row tile into Zk[m][s] (this wave's features;
-// rows past `count` zero), as the forward forms them
-template <class G>
-__device__ __forceinline__ void key_features(const Lane& L, const QuadWb<G>& wt, int w, const typename G::T* Ks,
-                                             const float* kn, float koff, int count, float eps, typename G::T* Zk) {
-  typedef typename FragT<typename G::T>::type F;
-  constexpr int LDZ = G::TR + 8;
-#pragma unroll
-  for (int mt = 0; mt < G::MT; ++mt) {
-    F hi[G::EB], lo[G::EB];
-    wt.get(w, mt, hi, lo);
-#pragma unroll
-    for (int st = 0; st < G::RT; ++st) {
-      f32x4 acc = zero4();
-#pragma unroll
-      for (int kb = 0; kb < G::EB; ++kb) {
-        const F kf = frag_rm(L, Ks, G::D + 8, 16 * st, 32 * kb);
-        acc = mma(acc, kf, hi[kb]);
-        acc = mma(acc, kf, lo[kb]);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int s = 16 * st + 4 * L.g + r;
-        if (G::KIND == kFavor) {
-          const float kc = s < count ? koff + 0.5f * kLog2e * kn[s] : INFINITY;
-          acc[r] = fast_exp2(acc[r] * kLog2e - kc);
-        } else {
-          acc[r] = s < count ? plain_feature<G::KIND>(acc[r], eps) : 0.f;
-        }
-      }
-      store_tile_T<typename G::T>(L, Zk, LDZ, acc, 16 * st, 16 * mt);
-    }
-  }
-}
-
-// Value rows of a key tile into LDS, dropped elements zeroed (value dropout)
-template <class G, bool DROP>
-__device__ __forceinline__ void load_values(typename G::T* Vs, const typename G::T* Vh, int k0, int kcount,
-                                            const Drop& drop) {
-  typedef typename G::T T;
-  constexpr int D = G::D, TR = G::TR, LDQ = D + 8;
-  if constexpr (DROP) {
-    constexpr int VEC = 16 / sizeof(T), CPR = D / VEC;
-    for (int ch = threadIdx.x; ch < TR * CPR; ch += 256) {
-      const int r = ch / CPR, cc = ch - (ch / CPR) * CPR;
-      uint4 v = {0u, 0u, 0u, 0u};
-      if (r < kcount) v = *reinterpret_cast<const uint4*>(Vh + (size_t)(k0 + r) * D + cc * VEC);
-      drop_chunk<T>(v, drop, k0 + r, cc * VEC);
-      *reinterpret_cast<uint4*>(Vs + r * LDQ + cc * VEC) = v;
-    }
-  } else {
-    load_rows<T, D, TR, LDQ, 256>(Vs, Vh + (size_t)k0 * D, kcount, nullptr);
-  }
-}
-
-// dN (as operands), dD and the query row shifts of a query tile from the
-// query pass's rows; rows past `count` zero
-template <class G>
-__device__ __forceinline__ void load_dn(typename G::T* dNs, float* dDs, float* qsh, const float* DNt, int count) {
-  constexpr int D = G::D, TR = G::TR, TPR = 256 / TR, EPT = D / TPR;
-  const int tid = threadIdx.x, tr = tid / TPR, q = tid % TPR;
-  const bool ok = tr < count;
-  const float* src = DNt + (size_t)tr * (D + 4);
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const int e = q * EPT + i;
-    dNs[tr * (D + 8) + e] = cvt<typename G::T>(ok ? src[e] : 0.f);
-  }
-  if (q == 0) {
-    dDs[tr] = ok ? src[D] : 0.f;
-    qsh[tr] = ok ? src[D + 1] : 0.f;
-  }
-}
-
-// dW[m][e] += sum_t P[m][t] X[t][e] over a 32-row tile, this wave's features:
-// P as operand fragments pf(mt) (rows m, contracting over t), X staged in
-// LDS; added to the workgroup's own partial (no other workgroup writes it)
-template <class G, class PF>
-__device__ __forceinline__ void add_dw_tile(const Lane& L, PF pf, const typename G::T* Xs, float* slot, int w) {
-#pragma unroll
-  for (int mt = 0; mt < G::MT; ++mt) {
-    const auto p = pf(mt);
-    f32x4 acc[G::ET];
-#pragma unroll
-    for (int et = 0; et < G::ET; ++et) acc[et] = mma(zero4(), p, frag_tr(L, Xs, G::D + 8, 0, 16 * et));
-#pragma unroll
-    for (int et = 0; et < G::ET; ++et)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float* q = slot + (size_t)(w * G::FW + 16 * mt + 4 * L.g + r) * G::D + 16 * et + L.c;
-        *q += acc[et][r];
-      }
-  }
-}
-
-// ---------------------------------------------------------------- query pass
-
-template <class G>
-struct QuadDqLds {
-  typedef typename G::T T;
-  static constexpr int D = G::D, FW = G::FW, TR = G::TR, M = G::M;
-  static constexpr int LDQ = D + 8, LDZ = TR + 8, LDF = FW + 8, LDR = D + 4;
-  static constexpr size_t TILE = al16((size_t)TR * LDQ * sizeof(T));
-  static constexpr size_t oQ = 0, oK = TILE, oV = 2 * TILE, odN = 3 * TILE;
-  static constexpr size_t oF = 4 * TILE;  // floats: kn, qmx[4], dDs, rsum[4], zs[M]
-  static constexpr size_t oW = oF + al16((10 * TR + M) * sizeof(float));
-  // per wave: Zq [t][m]; then Zk [m][s] + dA [t][s], or the reduction rows
-  static constexpr size_t Z1 = al16((size_t)TR * LDF * sizeof(T));
-  static constexpr size_t ZK = al16((size_t)FW * LDZ * sizeof(T));
-  static constexpr size_t ZA = al16((size_t)TR * LDZ * sizeof(T));
-  static constexpr size_t RD = al16((size_t)TR * LDR * sizeof(float));
-  static constexpr size_t X = (ZK + ZA > RD) ? ZK + ZA : RD;
-  static constexpr size_t WAVE = Z1 + X;
-  static constexpr size_t TOTAL = oW + 4 * WAVE;
-};
-
-template <class G, bool DROP>
-__global__ __launch_bounds__(256, 2) void quad_dq_kernel(QuadArgs a) {
-  typedef typename G::T T;
-  typedef typename FragT<T>::type F;
-  typedef QuadDqLds<G> Lay;
-  typedef StateFragLayout<G> SL;
-  constexpr int D = G::D, FW = G::FW, M = G::M, TR = G::TR, MT = G::MT, MB = G::MB, ET = G::ET, EB = G::EB,
-                RT = G::RT;
-  constexpr int LDQ = Lay::LDQ, LDZ = Lay::LDZ, LDF = Lay::LDF, LDR = Lay::LDR;
-  constexpr int TPR = 256 / TR, EPT = D / TPR;
-  static_assert(RT == 2 && G::RB == 1 && MT % 2 == 0, "32-row tiles, whole 32-deep feature blocks");
-
-  __shared__ __attribute__((aligned(16))) char arena[Lay::TOTAL];
-  T* Qs = (T*)(arena + Lay::oQ);
-  T* Ks = (T*)(arena + Lay::oK);
-  T* Vs = (T*)(arena + Lay::oV);
-  T* dNs = (T*)(arena + Lay::odN);  // dY, then dN in place
-  float* kn = (float*)(arena + Lay::oF);
-  float* qmx = kn + TR;       // [4][TR]
-  float* dDs = qmx + 4 * TR;  // [TR]
-  float* rsum = dDs + TR;     // [4][TR]
-  float* zs = rsum + 4 * TR;  // [M]
-  const int w = wave_id();
-  char* wz = arena + Lay::oW + (size_t)w * Lay::WAVE;
-  T* Zq = (T*)wz;                         // Q~ as [t][m]; then P = chain-rule factor of dQ~, in place
-  T* Zk = (T*)(wz + Lay::Z1);             // K~ as [m][s]
-  T* ZdA = (T*)(wz + Lay::Z1 + Lay::ZK);  // dA as [t][s]
-  auto red = [&](int ww) -> float* { return (float*)(arena + Lay::oW + (size_t)ww * Lay::WAVE + Lay::Z1); };
-
-  const int hd = blockIdx.y, b = blockIdx.z;
-  const size_t head = (size_t)b * a.H + hd;
-  const size_t hoff = head * (size_t)a.L * D;
-  const T* Qh = (const T*)a.Q + hoff;
-  const T* Kh = (const T*)a.K + hoff;
-  const T* Vh = (const T*)a.V + hoff;
-  const T* dYh = (const T*)a.dY + hoff;
-  T* dQh = (T*)a.dQ + hoff;
-  float* DNh = a.DN + head * (size_t)a.C * (D + 4);
-  const QuadWb<G> wt(a.Wfrag);
-  const F* Sf = (const F*)a.Sfrag + head * (size_t)SL::TOTAL * 64;
-  const int lane = lane_id();
-  const Drop drop{a.drop_seed, a.drop_t, a.C, head};
-  const float half_log2M = 0.5f * __log2f((float)M);
-  const float koff = (G::KIND == kFavor) ? a.kshift[head] * kLog2e + half_log2M : 0.f;
-
-  for (int m = threadIdx.x; m < M; m += 256) zs[m] = a.S[(head * M + m) * (size_t)(D + 1) + D];
-  float* dw_slot = a.dW_part + (head * gridDim.x + blockIdx.x) * (size_t)M * D;
-
-  const int nt = (a.rows + TR - 1) / TR;
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    const int q0 = a.row0 + t * TR, qcount = min(TR, a.rows - t * TR);
-    __syncthreads();  // the previous tile's readers of every shared buffer are done
-    load_rows<T, D, TR, LDQ, 256>(Qs, Qh + (size_t)q0 * D, qcount, nullptr);
-    load_rows<T, D, TR, LDQ, 256>(dNs, dYh + (size_t)q0 * D, qcount, nullptr);
+    __syncthreads();  // (the previous block's products are done with the buffers)
+    if (DROP) sg.drop(drop, a.row0 + s0, fresh_tid());
+    sg.template store<true>(Fs, Vs, fresh_tid());
     __syncthreads();
-    Lane L = fresh_lane();
-
-    // (1) query features, Q~ -> Zq[t][m] (rows past the tile zero)
-    f32x4 Lq[MT][RT];
-    query_logits<G>(L, wt, w, Qs, Lq);
-    if (G::KIND == kFavor) {
+    phase();
+    // N and D
+    for (int u = 0; u < nt; ++u) {
+      const bf16* F = Fs + (u & 1) * kKT * M;
+      const bf16* X = Vs + (u & 1) * kKT * D;
+      // (after the last tile the first again, for the second pass)
+      const int un = u + 1 < nt ? u + 1 : 0;
+      sg.fetch(FK, V, un * kKT, last, fresh_tid());
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        float v = -INFINITY;
+      for (int st = 0; st < 2; ++st) {
+        const int k0 = s0 + u * kKT + 32 * st;
+        if (k0 > q0w) continue;
+        f32x16 acc = zero16();
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int kb = 0; kb < M / 16; ++kb) acc = mma32(acc, row_op<M>(F, 32 * st + i, kb, h), qf[kb]);
+        if (k0 == q0w) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v = fmaxf(v, Lq[mt][tt][r]);
-        v = wave_max_over_g(v);
-        if (L.g == 0) qmx[w * TR + 16 * tt + L.c] = v;
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int tt = 0; tt < RT; ++tt) {
-      const int tr = 16 * tt + L.c;
-      const float qs = (G::KIND == kFavor)
-                           ? fmaxf(fmaxf(qmx[tr], qmx[TR + tr]), fmaxf(qmx[2 * TR + tr], qmx[3 * TR + tr])) * kLog2e
-                           : 0.f;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float x = Lq[mt][tt][r];
-          Lq[mt][tt][r] = tr >= qcount ? 0.f
-                          : (G::KIND == kFavor) ? fast_exp2(x * kLog2e - qs)
-                                                : plain_feature<G::KIND>(x, a.relu_eps);
-        }
-        store_tile_T<T>(L, Zq, LDF, Lq[mt][tt], 16 * mt, 16 * tt);
-      }
-    }
-    F qf[MB][RT];
-#pragma unroll
-    for (int kb = 0; kb < MB; ++kb)
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) qf[kb][tt] = tile_pair_frag<T>(Lq[2 * kb][tt], Lq[2 * kb + 1][tt]);
-
-    // (2) this wave's share of N^T[e][t]: the state before the slice, then
-    // every key tile of the slice up to the diagonal (as in the forward)
-    f32x4 nacc[ET + 1][RT];
-#pragma unroll
-    for (int et = 0; et <= ET; ++et)
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int kb = 0; kb < MB; ++kb) acc = mma(acc, Sf[SL::t2(w, kb, et) * 64 + lane], qf[kb][tt]);
-        nacc[et][tt] = acc;
-      }
-    for (int u = 0; u <= t; ++u) {
-      const int k0 = a.row0 + u * TR, kcount = min(TR, a.rows - u * TR);
-      __syncthreads();
-      load_rows<T, D, TR, LDQ, 256>(Ks, Kh + (size_t)k0 * D, kcount, G::KIND == kFavor ? kn : nullptr);
-      load_values<G, DROP>(Vs, Vh, k0, kcount, drop);
-      __syncthreads();
-      L = fresh_lane();
-      key_features<G>(L, wt, w, Ks, kn, koff, kcount, a.relu_eps, Zk);
-      const bool diag = (u == t);
-      f32x4 At[RT][RT];
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt)
-#pragma unroll
-        for (int st = 0; st < RT; ++st) {
-          f32x4 acc = zero4();
-          if (!(diag && st > tt)) {
-#pragma unroll
-            for (int kb = 0; kb < MB; ++kb) acc = mma(acc, frag_tr(L, Zk, LDZ, 32 * kb, 16 * st), qf[kb][tt]);
-            if (diag && st == tt) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (4 * L.g + r > L.c) acc[r] = 0.f;
-            }
-          }
-          At[st][tt] = acc;
+          for (int r = 0; r < 16; ++r)
+            if (row_of(r, h) > i) acc[r] = 0.f;
         }
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        const F af = tile_pair_frag<T>(At[0][tt], At[1][tt]);
+        for (int kk = 0; kk < 2; ++kk) {
+          const bf16x8 p = pack8(acc, kk);
+          den = sum8(p, den);
 #pragma unroll
-        for (int et = 0; et < ET; ++et) nacc[et][tt] = mma(nacc[et][tt], frag_tr(L, Vs, LDQ, 0, 16 * et), af);
-        nacc[ET][tt] = mma(nacc[ET][tt], ones_rows_frag(L, 0, kcount), af);
+          for (int et = 0; et < D / 32; ++et)
+            nacc[et] = mma32(nacc[et], col_op<D, true>(X, 32 * st + 16 * kk, 32 * et, lane), p);
+        }
       }
+      if (DROP) sg.drop(drop, a.row0 + s0 + un * kKT, fresh_tid());
+      sg.template store<true>(Fs + ((u & 1) ^ 1) * kKT * M, Vs + ((u & 1) ^ 1) * kKT * D, fresh_tid());
+      __syncthreads();
     }
-
-    // (3) the waves' shares of N meet in LDS (rows [t][e], e = D: D_t)
-    L = fresh_lane();
-#pragma unroll
-    for (int tt = 0; tt < RT; ++tt) {
-#pragma unroll
-      for (int et = 0; et < ET; ++et) store_tile_T<float>(L, red(w), LDR, nacc[et][tt], 16 * et, 16 * tt);
-      if (L.g == 0) red(w)[(16 * tt + L.c) * LDR + D] = nacc[ET][tt][0];
-    }
-    __syncthreads();
-    // (4) per row: Y = s N / D, dN = s dY / D, dD = -(dY . Y) / D (dN in place
-    // of dY); the rows and the row shift go to the key pass
+    phase();
+    // dN = s dY / D, dD = -(dY . Y) / D
+    bf16x8 dn[D / 16];
+    float dD;
     {
-      const int tid = fresh_tid();
-      const int tr = tid / TPR, q = tid % TPR;
-      const bool ok = tr < qcount;
-      const float den = (red(0)[tr * LDR + D] + red(1)[tr * LDR + D]) + (red(2)[tr * LDR + D] + red(3)[tr * LDR + D]);
-      const float inv = ok ? 1.f / den : 0.f;
-      const float invs = inv * a.drop_scale;
-      float dy[EPT];
+      den += __shfl_xor(den, 32, 64);
+      const float inv = a.drop_scale / den;
+      f32x16 dy[D / 32];
+      load_row_T<D>((const bf16*)a.dY + base + (size_t)row * D, h, dy);
       float dot = 0.f;
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = q * EPT + i;
-        dy[i] = to_f32(dNs[tr * LDQ + e]);
-        const float n = (red(0)[tr * LDR + e] + red(1)[tr * LDR + e]) + (red(2)[tr * LDR + e] + red(3)[tr * LDR + e]);
-        dot += dy[i] * (n * invs);
-      }
-      dot = sum_lane_group<TPR>(dot);
-      float* dst = DNh + (size_t)(t * TR + tr) * (D + 4);
+      for (int et = 0; et < D / 32; ++et)
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const int e = q * EPT + i;
-        const float dn = dy[i] * invs;
-        dNs[tr * LDQ + e] = cvt<T>(dn);
-        if (ok) dst[e] = dn;
-      }
-      if (q == 0) {
-        const float dd = ok ? -dot * inv : 0.f;
-        dDs[tr] = dd;
-        if (ok) {
-          dst[D] = dd;
-          dst[D + 1] = (G::KIND == kFavor) ? fmaxf(fmaxf(qmx[tr], qmx[TR + tr]), fmaxf(qmx[2 * TR + tr], qmx[3 * TR + tr])) * kLog2e
-                                           : 0.f;
+        for (int r = 0; r < 16; ++r) {
+          dot = fmaf(dy[et][r], nacc[et][r], dot);
+          dy[et][r] = ok ? inv * dy[et][r] : 0.f;
         }
+      dot += __shfl_xor(dot, 32, 64);
+      dD = ok ? -dot * inv / den : 0.f;
+#pragma unroll
+      for (int kb = 0; kb < D / 16; ++kb) dn[kb] = pack8(dy[kb / 2], kb & 1);
+      if (ok) {
+        bf16* DN = (bf16*)a.DN + ((size_t)head * a.n + row) * D + 8 * h;
+#pragma unroll
+        for (int kb = 0; kb < D / 16; ++kb) *reinterpret_cast<bf16x8*>(DN + 16 * kb) = dn[kb];
+        if (h == 0) a.dD[(size_t)head * a.n + row] = dD;
       }
     }
-    __syncthreads();  // the reduction rows are read; dN and dD visible
-
-    // (5) dQ~^T[m][t] = sum_e S[m][e] dN[t][e] + z[m] dD[t] + sum_s K~[s][m] dA[t][s]
-    L = fresh_lane();
-    f32x4 dq[MT][RT];
+    // dg(q): from the state, then the keys up to the diagonal
+    f32x16 dg[M / 32];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < M / 32; ++mt) {
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        const float ddt = dDs[16 * tt + L.c];
-        f32x4 acc;
+      for (int b = 0; b < 4; ++b) {
+        const f32x4 zv = ldf4(z + 32 * mt + 8 * b + 4 * h);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = zs[w * FW + 16 * mt + 4 * L.g + r] * ddt;
-#pragma unroll
-        for (int kb = 0; kb < EB; ++kb)
-          acc = mma(acc, Sf[SL::t1(w, mt, kb) * 64 + lane], frag_rm(L, dNs, LDQ, 16 * tt, 32 * kb));
-        dq[mt][tt] = acc;
+        for (int k = 0; k < 4; ++k) dg[mt][4 * b + k] = zv[k] * dD;
       }
-    for (int u = 0; u <= t; ++u) {
-      const int k0 = a.row0 + u * TR, kcount = min(TR, a.rows - u * TR);
-      __syncthreads();
-      load_rows<T, D, TR, LDQ, 256>(Ks, Kh + (size_t)k0 * D, kcount, G::KIND == kFavor ? kn : nullptr);
-      load_values<G, DROP>(Vs, Vh, k0, kcount, drop);
-      __syncthreads();
-      L = fresh_lane();
-      key_features<G>(L, wt, w, Ks, kn, koff, kcount, a.relu_eps, Zk);
-      // dA[t][s] = V[s] . dN[t] + dD[t] (causal; key rows past the tile zero) -> ZdA[t][s]
-      const bool diag = (u == t);
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        const float ddt = dDs[16 * tt + L.c];
+      for (int kb = 0; kb < D / 16; ++kb) dg[mt] = mma32(dg[mt], ld8(Sm + (32 * mt + i) * D + 16 * kb + 8 * h), dn[kb]);
+      if (mt & 1) __builtin_amdgcn_sched_barrier(0);  // (no registers for later tiles' loads)
+    }
+    phase();
+    for (int u = 0; u < nt; ++u) {
+      const int b = (nt + u) & 1;
+      const bf16* F = Fs + b * kKT * M;
+      const bf16* X = Vs + b * kKT * D;
+      if (u + 1 < nt) sg.fetch(FK, V, (u + 1) * kKT, last, fresh_tid());
 #pragma unroll
-        for (int st = 0; st < RT; ++st) {
-          f32x4 acc = zero4();
-          if (!(diag && st > tt)) {
-            acc = f32x4{ddt, ddt, ddt, ddt};
+      for (int st = 0; st < 2; ++st) {
+        const int k0 = s0 + u * kKT + 32 * st;
+        if (k0 > q0w) continue;
+        f32x16 da = zero16();
 #pragma unroll
-            for (int kb = 0; kb < EB; ++kb)
-              acc = mma(acc, frag_rm(L, Vs, LDQ, 16 * st, 32 * kb), frag_rm(L, dNs, LDQ, 16 * tt, 32 * kb));
+        for (int kb = 0; kb < D / 16; ++kb) da = mma32(da, row_op<D>(X, 32 * st + i, kb, h), dn[kb]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (16 * st + 4 * L.g + r >= kcount || (diag && st == tt && 4 * L.g + r > L.c)) acc[r] = 0.f;
+        for (int r = 0; r < 16; ++r) da[r] = k0 == q0w && row_of(r, h) > i ? 0.f : da[r] + dD;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const bf16x8 p = pack8(da, kk);
+#pragma unroll
+          for (int mt = 0; mt < M / 32; ++mt) {
+            dg[mt] = mma32(dg[mt], col_op<M, true>(F, 32 * st + 16 * kk, 32 * mt, lane), p);
+            if (mt % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (registers for four tiles' operands ahead)
           }
-          store_tile_T<T>(L, ZdA, LDZ, acc, 16 * st, 16 * tt);
         }
       }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int tt = 0; tt < RT; ++tt)
-          dq[mt][tt] = mma(dq[mt][tt], frag_rm(L, Zk, LDZ, 16 * mt, 0), frag_rm(L, ZdA, LDZ, 16 * tt, 0));
+      if (u + 1 < nt) {
+        if (DROP) sg.drop(drop, a.row0 + s0 + (u + 1) * kKT, fresh_tid());
+        sg.template store<true>(Fs + (b ^ 1) * kKT * M, Vs + (b ^ 1) * kKT * D, fresh_tid());
+      }
+      __syncthreads();
     }
-
-    // (6) chain rule of the features: P = dQ~ . Q~ (FAVOR+) or dQ~ masked
-    // (ReLU) -> Zq in place; FAVOR+ row sums of P
-    L = fresh_lane();
-    {
-      float rs[RT];
+    // logit cotangents
+    phase();
+    bf16x8 cb[M / 16];
+    const bf16* Qg = (const bf16*)a.Q + base;
+    const float cs = coefficients<M>(a.kind, dg, FQ, a.relu_eps, ok, cb, Fs, 32 * w + i, h);
+    stage_block<D>(Vs, Qg, q0, a.n - 1, tid);
+    chain<D, M>(a, cb, cs, Qg + (size_t)row * D, (bf16*)a.dQ + base + (size_t)row * D, ok, lane);
+    __syncthreads();
+    block_product<D, M, true>(Fs, Vs, a.dW_part + (size_t)blockIdx.x * M * D, D, w, lane);
+    __syncthreads();
+    // what the block adds to the cotangent
 #pragma unroll
-      for (int tt = 0; tt < RT; ++tt) rs[tt] = 0.f;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int tt = 0; tt < RT; ++tt) {
-          const f32x4 qv = load_tile_T(L, Zq, LDF, 16 * mt, 16 * tt);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            dq[mt][tt][r] = vjp_factor<G::KIND>(dq[mt][tt][r], qv[r], 0.f, a.relu_eps);
-            rs[tt] += dq[mt][tt][r];
-          }
-          store_tile_T<T>(L, Zq, LDF, dq[mt][tt], 16 * mt, 16 * tt);
-        }
-      if (G::KIND == kFavor) {
-#pragma unroll
-        for (int tt = 0; tt < RT; ++tt) {
-          const float v = wave_sum_over_g(rs[tt]);
-          if (L.g == 0) rsum[w * TR + 16 * tt + L.c] = v;
-        }
-      }
-    }
-    // dq^T[e][t] = sum_m W[m][e] P[m][t] -> reduction rows [t][e]; dW[m][e] += sum_t P[m][t] Q[t][e]
-#pragma unroll
-    for (int tt = 0; tt < RT; ++tt)
-#pragma unroll
-      for (int et = 0; et < ET; ++et) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int kb = 0; kb < MB; ++kb) acc = mma(acc, wt.b(w, kb, et), frag_rm(L, Zq, LDF, 16 * tt, 32 * kb));
-        store_tile_T<float>(L, red(w), LDR, acc, 16 * et, 16 * tt);
-      }
-    add_dw_tile<G>(L, [&](int mt) { return frag_tr(L, Zq, LDF, 0, 16 * mt); }, Qs, dw_slot, w);
+    for (int kb = 0; kb < M / 16; ++kb)
+      *reinterpret_cast<bf16x8*>(chunk_at<M>(Fs, 32 * w + i, 2 * kb + h)) = ld8(FQ + 16 * kb);
+    put_rows<D>(Vs, dn, 32 * w + i, h);
     __syncthreads();
     {
-      const int tid = fresh_tid();
-      const int tr = tid / TPR, q = tid % TPR;
-      if (tr < qcount) {
-        const float rsv = (G::KIND == kFavor) ? (rsum[tr] + rsum[TR + tr]) + (rsum[2 * TR + tr] + rsum[3 * TR + tr]) : 0.f;
+      const int blocks = (a.n + kQB - 1) / kQB;
+      float* out = a.gpart + ((size_t)head * blocks + q0 / kQB) * (size_t)M * (D + 1);
+      block_product<D, M, false>(Fs, Vs, out, D + 1, w, lane);
+      // column D: dD as two bf16 terms in columns 0 and 1 of an operand
+      if (w < M / 32) {
+        const float* dDb = a.dD + (size_t)head * a.n;
+        f32x16 acc = zero16();
 #pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-          const int e = q * EPT + i;
-          float v = (red(0)[tr * LDR + e] + red(1)[tr * LDR + e]) + (red(2)[tr * LDR + e] + red(3)[tr * LDR + e]);
-          if (G::KIND == kFavor) v -= to_f32(Qs[tr * LDQ + e]) * rsv;
-          dQh[(size_t)(q0 + tr) * D + e] = cvt<T>(v);
+        for (int kb = 0; kb < kQB / 16; ++kb) {
+          bf16x8 b;
+#pragma unroll
+          for (int s = 0; s < 8; ++s) {
+            // (the rows' dD, written by this workgroup before the last barriers)
+            const int t = q0 + 16 * kb + (s & 3) + 8 * (s >> 2) + 4 * h;
+            const float x = t < a.n ? dDb[t] : 0.f;
+            b[s] = i == 0 ? (bf16)x : i == 1 ? w_lo<bf16>(x) : (bf16)0.f;
+          }
+          acc = mma32(acc, col_op<M, true>(Fs, 16 * kb, 32 * w, lane), b);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float v = acc[r] + __shfl_xor(acc[r], 1, 64);
+          if (i == 0) out[(size_t)(32 * w + row_of(r, h)) * (D + 1) + D] = v;
         }
       }
     }
   }
 }
 
-// ---------------------------------------------------------------- key pass
+// ---- cotangent after every slice of the group (running sum of the blocks
+// from the last) and before the group; grid (entries / 256, heads)
+template <int D, int M>
+__global__ __launch_bounds__(256) void cot_kernel(QuadArgs a) {
+  const int el = blockIdx.x * 256 + threadIdx.x;
+  constexpr int SZ = M * (D + 1);
+  if (el >= SZ) return;
+  const size_t head = blockIdx.y;
+  const int m = el / (D + 1), e = el - m * (D + 1);
+  const int slices = (a.n + a.C - 1) / a.C, nb = a.C / kQB, blocks = (a.n + kQB - 1) / kQB;
+  float v = a.G_in != nullptr ? a.G_in[head * SZ + el] : 0.f;
+  const float* part = a.gpart + head * blocks * (size_t)SZ + el;
+  const size_t tb = quad_table_bytes(D, M, true);
+  char* tab = (char*)a.GT + head * slices * tb;
+  for (int p = blocks - 1; p >= 0; p -= 8) {
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = p - k >= 0 ? part[(size_t)(p - k) * SZ] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (p - k >= 0) {
+        if (p - k == blocks - 1 || (p - k + 1) % nb == 0) {
+          char* t = tab + (size_t)((p - k) / nb) * tb;
+          bf16* T = (bf16*)t;
+          if (e < D) {
+            T[e * M + slot_pos(m)] = (bf16)v;
+            T[M * D + m * D + slot_pos(e)] = (bf16)v;
+          } else {
+            ((float*)(T + 2 * M * D))[m] = v;
+          }
+        }
+        v += x[k];
+      }
+  }
+  if (a.G_out != nullptr) a.G_out[head * SZ + el] = v;
+}
 
-template <class G>
-struct QuadDkLds {
-  typedef typename G::T T;
-  static constexpr int D = G::D, FW = G::FW, TR = G::TR, M = G::M;
-  static constexpr int LDQ = D + 8, LDZ = TR + 8, LDF = FW + 8, LDR = D + 4;
-  static constexpr size_t TILE = al16((size_t)TR * LDQ * sizeof(T));
-  static constexpr size_t oK = 0, oV = TILE, oQ = 2 * TILE, odN = 3 * TILE;
-  static constexpr size_t oF = 4 * TILE;  // floats: kn, dDs, qsh, rsum[4], dzs[M]
-  static constexpr size_t oW = oF + al16((7 * TR + M) * sizeof(float));
-  // per wave: Zk [m][s]; then Zq [t][m], or the reduction rows
-  static constexpr size_t ZK = al16((size_t)FW * LDZ * sizeof(T));
-  static constexpr size_t Z1 = al16((size_t)TR * LDF * sizeof(T));
-  static constexpr size_t RD = al16((size_t)TR * LDR * sizeof(float));
-  static constexpr size_t X = Z1 > RD ? Z1 : RD;
-  static constexpr size_t WAVE = ZK + X;
-  static constexpr size_t TOTAL = oW + 4 * WAVE;
-};
+template <int D, int M, bool DROP>
+__global__ __launch_bounds__(kTH, 2) void dk_kernel(QuadArgs a) {
+  // stream: [2][64][M] query features, [2][64][D] dN; then [256][M], [256][D]
+  __shared__ __attribute__((aligned(16))) bf16 Fs[kQB * M];
+  __shared__ __attribute__((aligned(16))) bf16 Ns[kQB * D];
+  const int w = uniform_wave();
+  const int nb = a.C / kQB, slices = (a.n + a.C - 1) / a.C, total = nb * slices * a.H;
+  for (int idx = blockIdx.x; idx < total; idx += gridDim.x) {
+    int tid = fresh_tid(), lane = tid & 63, h = lane >> 5, i = lane & 31;
+    // (lane coordinates formed anew per phase: kept addresses would spill)
+    auto phase = [&] {
+      tid = fresh_tid();
+      lane = tid & 63;
+      h = lane >> 5;
+      i = lane & 31;
+    };
+    const int head = idx % a.H, sl = idx / a.H % slices, b0 = idx / (a.H * slices);
+    const int s0 = sl * a.C, k0 = s0 + b0 * kQB;
+    if (k0 >= a.n) continue;
+    const int k0w = k0 + 32 * w, row = min(k0w + i, a.n - 1);
+    const bool ok = k0w + i < a.n;
+    const int s1 = min(s0 + a.C, a.n);  // end of the slice
+    const bf16* FK = (const bf16*)a.FK + ((size_t)head * a.n + row) * M + 8 * h;
+    const bf16* FQ = (const bf16*)a.FQ + (size_t)head * a.n * M;
+    const bf16* DN = (const bf16*)a.DN + (size_t)head * a.n * D;
+    const float* dDg = a.dD + (size_t)head * a.n;
+    const size_t base = ((size_t)head * a.L + a.row0) * D;
+    const char* tab = (const char*)a.GT + ((size_t)head * slices + sl) * quad_table_bytes(D, M, true);
+    const bf16* Gt = (const bf16*)tab;
+    const bf16* Gm = Gt + M * D;
+    const float* gz = (const float*)(Gt + 2 * M * D);
+    const int nt = (s1 - k0 + kKT - 1) / kKT;
 
-template <class G, bool DROP>
-__global__ __launch_bounds__(256, 2) void quad_dk_kernel(QuadArgs a) {
-  typedef typename G::T T;
-  typedef typename FragT<T>::type F;
-  typedef QuadDkLds<G> Lay;
-  typedef StateFragLayout<G> SL;
-  constexpr int D = G::D, FW = G::FW, M = G::M, TR = G::TR, MT = G::MT, MB = G::MB, ET = G::ET, EB = G::EB,
-                RT = G::RT;
-  constexpr int LDQ = Lay::LDQ, LDZ = Lay::LDZ, LDF = Lay::LDF, LDR = Lay::LDR;
-  constexpr int TPR = 256 / TR, EPT = D / TPR;
-  static_assert(RT == 2 && G::RB == 1 && MT % 2 == 0, "32-row tiles, whole 32-deep feature blocks");
-
-  __shared__ __attribute__((aligned(16))) char arena[Lay::TOTAL];
-  T* Ks = (T*)(arena + Lay::oK);
-  T* Vs = (T*)(arena + Lay::oV);
-  T* Qs = (T*)(arena + Lay::oQ);
-  T* dNs = (T*)(arena + Lay::odN);
-  float* kn = (float*)(arena + Lay::oF);
-  float* dDs = kn + TR;        // [TR]
-  float* qsh = dDs + TR;       // [TR]
-  float* rsum = qsh + TR;      // [4][TR]
-  float* dzs = rsum + 4 * TR;  // [M]
-  const int w = wave_id();
-  char* wz = arena + Lay::oW + (size_t)w * Lay::WAVE;
-  T* Zk = (T*)wz;              // K~ as [m][s]; then P = chain-rule factor of dK~, in place
-  T* Zq = (T*)(wz + Lay::ZK);  // Q~ as [t][m]
-  auto red = [&](int ww) -> float* { return (float*)(arena + Lay::oW + (size_t)ww * Lay::WAVE + Lay::ZK); };
-
-  const int hd = blockIdx.y, b = blockIdx.z;
-  const size_t head = (size_t)b * a.H + hd;
-  const size_t hoff = head * (size_t)a.L * D;
-  const T* Qh = (const T*)a.Q + hoff;
-  const T* Kh = (const T*)a.K + hoff;
-  const T* Vh = (const T*)a.V + hoff;
-  T* dKh = (T*)a.dK + hoff;
-  T* dVh = (T*)a.dV + hoff;
-  const float* DNh = a.DN + head * (size_t)a.C * (D + 4);
-  const QuadWb<G> wt(a.Wfrag);
-  const F* Gf = (const F*)a.Gfrag + head * (size_t)SL::TOTAL * 64;
-  const int lane = lane_id();
-  const Drop drop{a.drop_seed, a.drop_t, a.C, head};
-  const float half_log2M = 0.5f * __log2f((float)M);
-  const float koff = (G::KIND == kFavor) ? a.kshift[head] * kLog2e + half_log2M : 0.f;
-
-  for (int m = threadIdx.x; m < M; m += 256) dzs[m] = a.Gc[(head * M + m) * (size_t)(D + 1) + D];
-  float* dw_slot = a.dW_part + (head * gridDim.x + blockIdx.x) * (size_t)M * D;
-
-  const int nt = (a.rows + TR - 1) / TR;
-  for (int si = blockIdx.x; si < nt; si += gridDim.x) {
-    const int k0 = a.row0 + si * TR, kcount = min(TR, a.rows - si * TR);
-    __syncthreads();  // the previous tile's readers of every shared buffer are done
-    load_rows<T, D, TR, LDQ, 256>(Ks, Kh + (size_t)k0 * D, kcount, G::KIND == kFavor ? kn : nullptr);
-    load_values<G, DROP>(Vs, Vh, k0, kcount, drop);
+    Stage<D, M> sg;
+    sg.fetch(FQ, DN, k0, s1 - 1, fresh_tid());
+    bf16x8 kf[M / 16];
+#pragma unroll
+    for (int kb = 0; kb < M / 16; ++kb) kf[kb] = ld8(FK + 16 * kb);
+    // dV: from the cotangent after the slice, then the queries from the diagonal on
+    f32x16 dv[D / 32];
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et) {
+      dv[et] = zero16();
+#pragma unroll
+      for (int kb = 0; kb < M / 16; ++kb) dv[et] = mma32(dv[et], ld8(Gt + (32 * et + i) * M + 16 * kb + 8 * h), kf[kb]);
+    }
+    __syncthreads();  // (the previous block's product is done with the buffers)
+    sg.template store<false>(Fs, Ns, fresh_tid());
     __syncthreads();
-    Lane L = fresh_lane();
-    key_features<G>(L, wt, w, Ks, kn, koff, kcount, a.relu_eps, Zk);
-
-    // the cotangent after the slice: dK~[s][m] = sum_e V[s][e] G[m][e] + dz[m];
-    // dV^T[e][s] = sum_m G[m][e] K~[s][m] (this wave's features)
-    f32x4 dk[RT][MT], dv[ET][RT];
+    for (int u = 0; u < nt; ++u) {
+      const bf16* F = Fs + (u & 1) * kKT * M;
+      const bf16* X = Ns + (u & 1) * kKT * D;
+      // (after the last tile the first again, for the second pass)
+      sg.fetch(FQ, DN, k0 + (u + 1 < nt ? u + 1 : 0) * kKT, s1 - 1, fresh_tid());
 #pragma unroll
-    for (int st = 0; st < RT; ++st)
+      for (int st = 0; st < 2; ++st) {
+        const int t0 = k0 + u * kKT + 32 * st;
+        if (t0 < k0w || t0 >= s1) continue;
+        f32x16 p = zero16();
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const float dz = dzs[w * FW + 16 * mt + L.c];
-        f32x4 acc;
+        for (int kb = 0; kb < M / 16; ++kb) p = mma32(p, row_op<M>(F, 32 * st + i, kb, h), kf[kb]);
+        if (t0 == k0w || t0 + 32 > s1) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = (16 * st + 4 * L.g + r < kcount) ? dz : 0.f;
+          for (int r = 0; r < 16; ++r) {
+            const int t = t0 + row_of(r, h);
+            if (t < k0w + i || t >= s1) p[r] = 0.f;
+          }
+        }
 #pragma unroll
-        for (int kb = 0; kb < EB; ++kb)
-          acc = mma(acc, frag_rm(L, Vs, LDQ, 16 * st, 32 * kb), Gf[SL::t1(w, mt, kb) * 64 + lane]);
-        dk[st][mt] = acc;
+        for (int kk = 0; kk < 2; ++kk) {
+          const bf16x8 pb = pack8(p, kk);
+#pragma unroll
+          for (int et = 0; et < D / 32; ++et)
+            dv[et] = mma32(dv[et], col_op<D, true>(X, 32 * st + 16 * kk, 32 * et, lane), pb);
+        }
       }
-#pragma unroll
-    for (int et = 0; et < ET; ++et)
-#pragma unroll
-      for (int st = 0; st < RT; ++st) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int kb = 0; kb < MB; ++kb) acc = mma(acc, Gf[SL::t2(w, kb, et) * 64 + lane], frag_tr(L, Zk, LDZ, 32 * kb, 16 * st));
-        dv[et][st] = acc;
-      }
-
-    // every query tile of the slice from the diagonal on
-    for (int t = si; t < nt; ++t) {
-      const int q0 = a.row0 + t * TR, qcount = min(TR, a.rows - t * TR);
+      sg.template store<false>(Fs + ((u & 1) ^ 1) * kKT * M, Ns + ((u & 1) ^ 1) * kKT * D, fresh_tid());
       __syncthreads();
-      load_rows<T, D, TR, LDQ, 256>(Qs, Qh + (size_t)q0 * D, qcount, nullptr);
-      load_dn<G>(dNs, dDs, qsh, DNh + (size_t)t * TR * (D + 4), qcount);
+    }
+    phase();
+    bf16x8 vb[D / 16];
+    {
+      unsigned keep[D / 32];  // dropout: the kept elements of the lane's value columns
+      f32x16 v[D / 32];
+      load_row_T<D>((const bf16*)a.V + base + (size_t)row * D, h, v);
+      if constexpr (DROP) {
+        const Drop drop{a.drop_seed, a.drop_t, a.drop_C, (uint64_t)(a.head0 + head)};
+#pragma unroll
+        for (int et = 0; et < D / 32; ++et) {
+          keep[et] = 0;
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            keep[et] |= drop_keep_bits<4>(drop, a.row0 + row, 32 * et + 8 * b + 4 * h) << (4 * b);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            v[et][r] = keep[et] >> r & 1u ? v[et][r] : 0.f;
+            dv[et][r] = keep[et] >> r & 1u ? dv[et][r] : 0.f;
+          }
+        }
+      }
+#pragma unroll
+      for (int kb = 0; kb < D / 16; ++kb) vb[kb] = pack8(v[kb / 2], kb & 1);
+      if (ok) store_row_T<D>((bf16*)a.dV + base + (size_t)row * D, h, dv, 1.f);
+    }
+    // dg(k), likewise
+    f32x16 dg[M / 32];
+#pragma unroll
+    for (int mt = 0; mt < M / 32; ++mt) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const f32x4 zv = ldf4(gz + 32 * mt + 8 * b + 4 * h);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dg[mt][4 * b + k] = zv[k];
+      }
+#pragma unroll
+      for (int kb = 0; kb < D / 16; ++kb) dg[mt] = mma32(dg[mt], ld8(Gm + (32 * mt + i) * D + 16 * kb + 8 * h), vb[kb]);
+      if (mt & 1) __builtin_amdgcn_sched_barrier(0);  // (no registers for later tiles' loads)
+    }
+    phase();
+    for (int u = 0; u < nt; ++u) {
+      const int b = (nt + u) & 1;
+      const bf16* F = Fs + b * kKT * M;
+      const bf16* X = Ns + b * kKT * D;
+      if (u + 1 < nt) sg.fetch(FQ, DN, k0 + (u + 1) * kKT, s1 - 1, fresh_tid());
+#pragma unroll
+      for (int st = 0; st < 2; ++st) {
+        const int t0 = k0 + u * kKT + 32 * st;
+        if (t0 < k0w || t0 >= s1) continue;
+        f32x16 da;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) da[r] = dDg[min(t0 + row_of(r, h), s1 - 1)];
+#pragma unroll
+        for (int kb = 0; kb < D / 16; ++kb) da = mma32(da, row_op<D>(X, 32 * st + i, kb, h), vb[kb]);
+        if (t0 == k0w || t0 + 32 > s1) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int t = t0 + row_of(r, h);
+            if (t < k0w + i || t >= s1) da[r] = 0.f;
+          }
+        }
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const bf16x8 db = pack8(da, kk);
+#pragma unroll
+          for (int mt = 0; mt < M / 32; ++mt) {
+            dg[mt] = mma32(dg[mt], col_op<M, true>(F, 32 * st + 16 * kk, 32 * mt, lane), db);
+            if (mt % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (registers for four tiles' operands ahead)
+          }
+        }
+      }
+      if (u + 1 < nt) sg.template store<false>(Fs + (b ^ 1) * kKT * M, Ns + (b ^ 1) * kKT * D, fresh_tid());
       __syncthreads();
-      L = fresh_lane();
-      // Q~ with the query pass's row shifts -> Zq[t][m]
-      {
-        f32x4 Lq[MT][RT];
-        query_logits<G>(L, wt, w, Qs, Lq);
-#pragma unroll
-        for (int tt = 0; tt < RT; ++tt) {
-          const int tr = 16 * tt + L.c;
-          const float qs = qsh[tr];
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float x = Lq[mt][tt][r];
-              Lq[mt][tt][r] = tr >= qcount ? 0.f
-                              : (G::KIND == kFavor) ? fast_exp2(x * kLog2e - qs)
-                                                    : plain_feature<G::KIND>(x, a.relu_eps);
-            }
-            store_tile_T<T>(L, Zq, LDF, Lq[mt][tt], 16 * mt, 16 * tt);
-          }
-        }
-      }
-      // A[t][s] over this wave's features and dA[t][s] = dN[t] . V[s] + dD[t]
-      // (causal on the diagonal tile; key rows past the tile zero); then
-      // dV^T[e][s] += sum_t dN[t][e] A[t][s], dK~[s][m] += sum_t dA[t][s] Q~[t][m]
-      const bool diag = (t == si);
-#pragma unroll
-      for (int st = 0; st < RT; ++st) {
-        f32x4 aw[RT], da[RT];
-#pragma unroll
-        for (int tt = 0; tt < RT; ++tt) {
-          f32x4 x = zero4(), y = zero4();
-          if (!(diag && st > tt)) {
-#pragma unroll
-            for (int kb = 0; kb < MB; ++kb)
-              x = mma(x, frag_rm(L, Zq, LDF, 16 * tt, 32 * kb), frag_tr(L, Zk, LDZ, 32 * kb, 16 * st));
-#pragma unroll
-            for (int r = 0; r < 4; ++r) y[r] = dDs[16 * tt + 4 * L.g + r];
-#pragma unroll
-            for (int kb = 0; kb < EB; ++kb)
-              y = mma(y, frag_rm(L, dNs, LDQ, 16 * tt, 32 * kb), frag_rm(L, Vs, LDQ, 16 * st, 32 * kb));
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int sc = 16 * st + L.c;
-              if (sc >= kcount || (diag && sc > 16 * tt + 4 * L.g + r)) {
-                x[r] = 0.f;
-                y[r] = 0.f;
-              }
-            }
-          }
-          aw[tt] = x;
-          da[tt] = y;
-        }
-        const F awf = tile_pair_frag<T>(aw[0], aw[1]);
-        const F daf = tile_pair_frag<T>(da[0], da[1]);
-#pragma unroll
-        for (int et = 0; et < ET; ++et) dv[et][st] = mma(dv[et][st], frag_tr(L, dNs, LDQ, 0, 16 * et), awf);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) dk[st][mt] = mma(dk[st][mt], daf, frag_tr(L, Zq, LDF, 0, 16 * mt));
-      }
     }
-
-    // chain rule of the key features: P = dK~ . K~ (FAVOR+) or masked (ReLU)
-    // -> Zk in place; FAVOR+ row sums of P
-    L = fresh_lane();
-    {
-      float rk[RT][4];
-#pragma unroll
-      for (int st = 0; st < RT; ++st)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) rk[st][r] = 0.f;
-#pragma unroll
-      for (int st = 0; st < RT; ++st)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const f32x4 kv = load_tile_T(L, Zk, LDZ, 16 * st, 16 * mt);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            dk[st][mt][r] = vjp_factor<G::KIND>(dk[st][mt][r], kv[r], 0.f, a.relu_eps);
-            rk[st][r] += dk[st][mt][r];
-          }
-          store_tile_T<T>(L, Zk, LDZ, dk[st][mt], 16 * st, 16 * mt);
-        }
-      if (G::KIND == kFavor) {
-#pragma unroll
-        for (int st = 0; st < RT; ++st)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float v = wave_sum_over_c(rk[st][r]);
-            if (L.c == 0) rsum[w * TR + 16 * st + 4 * L.g + r] = v;
-          }
-      }
-    }
-    // dk^T[e][s] = sum_m W[m][e] P[m][s] -> reduction rows [s][e]; dW[m][e] += sum_s P[m][s] K[s][e]
-#pragma unroll
-    for (int st = 0; st < RT; ++st)
-#pragma unroll
-      for (int et = 0; et < ET; ++et) {
-        f32x4 acc = zero4();
-#pragma unroll
-        for (int kb = 0; kb < MB; ++kb) acc = mma(acc, wt.b(w, kb, et), frag_tr(L, Zk, LDZ, 32 * kb, 16 * st));
-        store_tile_T<float>(L, red(w), LDR, acc, 16 * et, 16 * st);
-      }
-    add_dw_tile<G>(L, [&](int mt) { return frag_rm(L, Zk, LDZ, 16 * mt, 0); }, Ks, dw_slot, w);
+    phase();
+    bf16x8 cb[M / 16];
+    const bf16* Kg = (const bf16*)a.K + base;
+    const float cs = coefficients<M>(a.kind, dg, FK, a.relu_eps, ok, cb, Fs, 32 * w + i, h);
+    stage_block<D>(Ns, Kg, k0, a.n - 1, tid);
+    chain<D, M>(a, cb, cs, Kg + (size_t)row * D, (bf16*)a.dK + base + (size_t)row * D, ok, lane);
     __syncthreads();
-    {
-      const int tid = fresh_tid();
-      const int tr = tid / TPR, q = tid % TPR;
-      if (tr < kcount) {
-        const float rkv = (G::KIND == kFavor) ? (rsum[tr] + rsum[TR + tr]) + (rsum[2 * TR + tr] + rsum[3 * TR + tr]) : 0.f;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-          const int e = q * EPT + i;
-          float v = (red(0)[tr * LDR + e] + red(1)[tr * LDR + e]) + (red(2)[tr * LDR + e] + red(3)[tr * LDR + e]);
-          if (G::KIND == kFavor) v -= to_f32(Ks[tr * LDQ + e]) * rkv;
-          dKh[(size_t)(k0 + tr) * D + e] = cvt<T>(v);
-        }
-      }
-    }
-    __syncthreads();  // the reduction rows are read
-    L = fresh_lane();
-#pragma unroll
-    for (int et = 0; et < ET; ++et)
-#pragma unroll
-      for (int st = 0; st < RT; ++st) store_tile_T<float>(L, red(w), LDR, dv[et][st], 16 * et, 16 * st);
-    __syncthreads();
-    {
-      const int tid = fresh_tid();
-      const int tr = tid / TPR, q = tid % TPR;
-      if (tr < kcount) {
-        const unsigned keep = DROP ? drop_keep_bits<EPT>(drop, k0 + tr, q * EPT) : ~0u;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-          const int e = q * EPT + i;
-          const float v = (red(0)[tr * LDR + e] + red(1)[tr * LDR + e]) + (red(2)[tr * LDR + e] + red(3)[tr * LDR + e]);
-          dVh[(size_t)(k0 + tr) * D + e] = cvt<T>((keep >> i) & 1u ? v : 0.f);
-        }
-      }
-    }
+    block_product<D, M, true>(Fs, Ns, a.dW_part + (size_t)blockIdx.x * M * D, D, w, lane);
   }
 }
 
-// ---------------------------------------------------------------- G sum
-
-template <class G>
-struct QuadGsumLds {
-  typedef typename G::T T;
-  static constexpr int D = G::D, FW = G::FW, TR = G::TR;
-  static constexpr int LDQ = D + 8, LDF = FW + 8, LDD = 24;
-  static constexpr size_t TILE = al16((size_t)TR * LDQ * sizeof(T));
-  static constexpr size_t oQ = 0, odN = TILE, odD = 2 * TILE;  // dD as column 0 of a [TR][16] tile
-  static constexpr size_t oF = odD + al16((size_t)TR * LDD * sizeof(T));  // floats: dDs, qsh
-  static constexpr size_t oW = oF + al16(2 * TR * sizeof(float));
-  static constexpr size_t Z1 = al16((size_t)TR * LDF * sizeof(T));
-  static constexpr size_t TOTAL = oW + 4 * Z1;
-};
-
-// part x of the slice's query tiles: sum_t Q~_t^T [dN_t|dD_t] -> out[B,H,x]
-template <class G>
-__global__ __launch_bounds__(256, 2) void quad_gsum_kernel(QuadArgs a) {
-  typedef typename G::T T;
-  typedef QuadGsumLds<G> Lay;
-  constexpr int D = G::D, FW = G::FW, M = G::M, TR = G::TR, MT = G::MT, ET = G::ET, RT = G::RT;
-  constexpr int LDQ = Lay::LDQ, LDF = Lay::LDF, LDD = Lay::LDD;
-  static_assert(RT == 2 && G::RB == 1, "32-row tiles");
-
-  __shared__ __attribute__((aligned(16))) char arena[Lay::TOTAL];
-  T* Qs = (T*)(arena + Lay::oQ);
-  T* dNs = (T*)(arena + Lay::odN);
-  T* dDt = (T*)(arena + Lay::odD);
-  float* dDs = (float*)(arena + Lay::oF);
-  float* qsh = dDs + TR;
-  const int w = wave_id();
-  T* Zq = (T*)(arena + Lay::oW + (size_t)w * Lay::Z1);
-
-  const int part = blockIdx.x, hd = blockIdx.y, b = blockIdx.z;
-  const size_t head = (size_t)b * a.H + hd;
-  const T* Qh = (const T*)a.Q + head * (size_t)a.L * D;
-  const float* DNh = a.DN + head * (size_t)a.C * (D + 4);
-  const QuadWb<G> wt(a.Wfrag);
-
-  f32x4 Gp[MT][ET + 1];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int et = 0; et <= ET; ++et) Gp[mt][et] = zero4();
-
-  const int nt = (a.rows + TR - 1) / TR;
-  const int t0 = (int)((int64_t)part * nt / gridDim.x), t1 = (int)((int64_t)(part + 1) * nt / gridDim.x);
-  for (int t = t0; t < t1; ++t) {
-    const int q0 = a.row0 + t * TR, qcount = min(TR, a.rows - t * TR);
-    __syncthreads();
-    load_rows<T, D, TR, LDQ, 256>(Qs, Qh + (size_t)q0 * D, qcount, nullptr);
-    load_dn<G>(dNs, dDs, qsh, DNh + (size_t)t * TR * (D + 4), qcount);
-    __syncthreads();
-    if (threadIdx.x < TR) {
-#pragma unroll
-      for (int j = 0; j < 16; ++j) dDt[threadIdx.x * LDD + j] = cvt<T>(j == 0 ? dDs[threadIdx.x] : 0.f);
-    }
-    Lane L = fresh_lane();
-    {
-      f32x4 Lq[MT][RT];
-      query_logits<G>(L, wt, w, Qs, Lq);
-#pragma unroll
-      for (int tt = 0; tt < RT; ++tt) {
-        const int tr = 16 * tt + L.c;
-        const float qs = qsh[tr];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float x = Lq[mt][tt][r];
-            Lq[mt][tt][r] = tr >= qcount ? 0.f
-                            : (G::KIND == kFavor) ? fast_exp2(x * kLog2e - qs)
-                                                  : plain_feature<G::KIND>(x, a.relu_eps);
-          }
-          store_tile_T<T>(L, Zq, LDF, Lq[mt][tt], 16 * mt, 16 * tt);
-        }
-      }
-    }
-    __syncthreads();  // dDt visible
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const auto qa = frag_tr(L, Zq, LDF, 0, 16 * mt);
-#pragma unroll
-      for (int et = 0; et < ET; ++et) Gp[mt][et] = mma(Gp[mt][et], qa, frag_tr(L, dNs, LDQ, 0, 16 * et));
-      Gp[mt][ET] = mma(Gp[mt][ET], qa, frag_tr(L, dDt, LDD, 0, 0));
-    }
+template <int D, int M>
+hipError_t launch_bwd_dm(int which, const QuadArgs& a, hipStream_t s) {
+  const dim3 g(a.nwg), b(kTH);
+  switch (which) {
+    case kQuadDq:
+      if (a.drop_t != 0) hipLaunchKernelGGL((dq_kernel<D, M, true>), g, b, 0, s, a);
+      else hipLaunchKernelGGL((dq_kernel<D, M, false>), g, b, 0, s, a);
+      break;
+    case kQuadCot: hipLaunchKernelGGL((cot_kernel<D, M>), dim3((M * (D + 1) + 255) / 256, a.H), dim3(256), 0, s, a); break;
+    case kQuadDk:
+      if (a.drop_t != 0) hipLaunchKernelGGL((dk_kernel<D, M, true>), g, b, 0, s, a);
+      else hipLaunchKernelGGL((dk_kernel<D, M, false>), g, b, 0, s, a);
+      break;
+    default: return hipErrorInvalidValue;
   }
-  float* o = a.out + (head * gridDim.x + part) * (size_t)M * (D + 1);
-  const Lane L = this_lane();
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const size_t row = (size_t)(w * FW + 16 * mt + 4 * L.g + r) * (D + 1);
-#pragma unroll
-      for (int et = 0; et < ET; ++et) o[row + 16 * et + L.c] = Gp[mt][et][r];
-      if (L.c == 0) o[row + D] = Gp[mt][ET][r];
-    }
-}
-
-// ---------------------------------------------------------------- launchers
-
-template <class G>
-hipError_t launch_quad_dq(const QuadArgs& a, int nwg, hipStream_t s) {
-  const dim3 grid(nwg, a.H, a.B);
-  if (a.drop_t != 0) hipLaunchKernelGGL((quad_dq_kernel<G, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((quad_dq_kernel<G, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-template <class G>
-hipError_t launch_quad_dk(const QuadArgs& a, int nwg, hipStream_t s) {
-  const dim3 grid(nwg, a.H, a.B);
-  if (a.drop_t != 0) hipLaunchKernelGGL((quad_dk_kernel<G, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((quad_dk_kernel<G, false>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
+}  // namespace quad
 
-template <class G>
-hipError_t launch_quad_gsum(const QuadArgs& a, int nwg, hipStream_t s) {
-  hipLaunchKernelGGL((quad_gsum_kernel<G>), dim3(nwg, a.H, a.B), dim3(256), 0, s, a);
-  return hipGetLastError();
+hipError_t launch_quad_bwd(int which, const QuadArgs& a, int d, int M, hipStream_t s) {
+  if (d == 64) return M == 256 ? quad::launch_bwd_dm<64, 256>(which, a, s) : quad::launch_bwd_dm<64, 128>(which, a, s);
+  return M == 256 ? quad::launch_bwd_dm<32, 256>(which, a, s) : quad::launch_bwd_dm<32, 128>(which, a, s);
 }
-
-template <class G>
-hipError_t launch_state_frag(const float* X0, void* F0, const float* X1, void* F1, int BH, hipStream_t s) {
-  hipLaunchKernelGGL((state_frag_kernel<G>), dim3(StateFragLayout<G>::TOTAL, BH, X1 != nullptr ? 2 : 1), dim3(64), 0, s,
-                     X0, (bf16x8*)F0, X1, (bf16x8*)F1);
-  return hipGetLastError();
-}
-
-template <class G>
-size_t state_frag_bytes() {
-  return (size_t)StateFragLayout<G>::TOTAL * 64 * sizeof(bf16x8);
-}
-
-#define SLIM_INST_QUAD_BWD(T, D, FW, TR, KIND)                                                                  \
-  template hipError_t launch_quad_dq<Cfg<T, D, FW, TR, KIND>>(const QuadArgs&, int, hipStream_t);             \
-  template hipError_t launch_quad_dk<Cfg<T, D, FW, TR, KIND>>(const QuadArgs&, int, hipStream_t);             \
-  template hipError_t launch_quad_gsum<Cfg<T, D, FW, TR, KIND>>(const QuadArgs&, int, hipStream_t);           \
-  template hipError_t launch_state_frag<Cfg<T, D, FW, TR, KIND>>(const float*, void*, const float*, void*, int, \
-                                                                 hipStream_t);                                \
-  template size_t state_frag_bytes<Cfg<T, D, FW, TR, KIND>>();
-SLIM_FOR_EACH_QUAD_CONFIG(SLIM_INST_QUAD_BWD)
 
 }  // namespace slim

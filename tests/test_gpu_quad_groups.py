@@ -1,0 +1,96 @@
+"""The quadratic mode's blocks, groups and head ranges at their edges: rows
+around the 128-row block and the 64- and 32-row tiles, slices of more than one
+part (512 rows), several groups per call with exact and with recovered
+(eq. 17) states before them (SLIM_QUAD_ROWS, SLIM_QUAD_RUNS), fewer workgroups
+than blocks, more heads than a range takes, dropout whose slices are not the
+groups', and the forward on the fixed scratch.
+
+Bar: 2e-2 max-relative, as for every bf16 problem."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth import Workload, make_inputs
+from tests.gpu_common import TOL, dev, host64, mask_w, need_gpu, report
+
+pytestmark = pytest.mark.gpu
+
+# B, H, L, d, M, C, kind, dropout, rows over the heads (0: the plan's), states kept, workgroups
+CASES = [
+    (1, 2, 1, 64, 256, 1, "favor+", 0.0, 0, 0, 0),
+    (1, 1, 31, 32, 128, 31, "relu", 0.0, 0, 0, 0),
+    (2, 1, 129, 64, 128, 200, "favor+", 0.0, 0, 0, 0),
+    (1, 1, 1030, 64, 256, 1030, "favor+", 0.0, 0, 0, 5),
+    (1, 2, 700, 64, 256, 130, "favor+", 0.1, 256, 0, 0),
+    (1, 2, 900, 32, 256, 64, "relu", 0.0, 256, 2, 3),
+    (1, 1, 1300, 64, 128, 600, "favor+", 0.0, 640, 0, 0),
+]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_blocks_and_groups(i, monkeypatch):
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    B, H, L, d, M, C, kind, p, rows, runs, nwg = CASES[i]
+    print(f"[quad groups] case={i} {CASES[i]}", flush=True)
+    for k, v in (("SLIM_QUAD_ROWS", rows), ("SLIM_QUAD_RUNS", runs), ("SLIM_QUAD_WORKGROUPS", nwg)):
+        if v:
+            monkeypatch.setenv(k, str(v))
+    x = make_inputs(Workload(f"qg{i}", 980 + i, B, H, L, d, M, (C,), "bf16", kind))
+    Q, K, V, W, dY = (dev(x[k]) for k in ("Q", "K", "V", "W", "dY"))
+    Y, st, ks = slim.fwd(Q, K, V, W, C, kind, within="quadratic", dropout=p, seed=9)
+    g = slim.bwd(Q, K, V, W, dY, C, ks, kind, within="quadratic", dropout=p, seed=9)
+    torch.cuda.synchronize()
+    tol = TOL["bf16"]
+    Yr = O.dropout_forward(O.attention_forward, x["Q"], x["K"], x["V"], x["W"], kind, C, p, 9)
+    report("Y", host64(Y), Yr, tol)
+    ref = O.dropout_backward(O.attention_backward, x["Q"], x["K"], x["V"], x["W"], x["dY"], kind, C, p, 9, mask_W=mask_w(x))
+    for n, a, r in zip(("dQ", "dK", "dV", "dW"), g[:4], ref):
+        if np.max(np.abs(r)) < 1e-9:  # one row: Y = V whatever Q and K are
+            assert np.max(np.abs(host64(a))) <= 2e-2, n
+            continue
+        report(n, host64(a), r, tol)
+
+
+def test_more_heads_than_a_range():
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    B, H, L, d, M, C, p = 1030, 1, 40, 32, 128, 16, 0.2
+    print("[quad groups] 1030 heads", flush=True)
+    x = make_inputs(Workload("qgh", 990, B, H, L, d, M, (C,), "bf16", "favor+"))
+    Q, K, V, W, dY = (dev(x[k]) for k in ("Q", "K", "V", "W", "dY"))
+    Y, _, ks = slim.fwd(Q, K, V, W, C, within="quadratic", dropout=p, seed=3)
+    g = slim.bwd(Q, K, V, W, dY, C, ks, within="quadratic", dropout=p, seed=3)
+    Yi, _, ksi = slim.fwd(Q, K, V, W, C, dropout=p, seed=3)
+    gi = slim.bwd(Q, K, V, W, dY, C, ksi, dropout=p, seed=3)
+    torch.cuda.synchronize()
+    tol = TOL["bf16"]
+    report("Y vs tile walk", host64(Y), host64(Yi), tol)
+    for n, a, b in zip(("dQ", "dK", "dV", "dW"), g[:4], gi[:4]):
+        report(n + " vs tile walk", host64(a), host64(b), tol)
+
+
+def test_on_the_fixed_scratch():
+    """The preferred plan does not fit the fixed scratch: fewer rows at a time give the same."""
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    B, H, L, d, M, C = 4, 8, 4096, 64, 256, 2048
+    print("[quad groups] fixed scratch", flush=True)
+    x = make_inputs(Workload("qgs", 991, B, H, L, d, M, (C,), "bf16", "favor+"), tensors=("Q", "K", "V", "W"))
+    Q, K, V, W = (dev(x[k]) for k in ("Q", "K", "V", "W"))
+    prob = slim.problem(B, H, L, d, M, C, within="quadratic")
+    assert slim.workspace_bytes(prob, slim.PHASE_FWD) > slim.LIB.slim_noalloc_scratch_bytes()
+    import ctypes
+
+    Y = torch.empty_like(Q)
+    ks = torch.empty(B, H, device="cuda")
+    slim._check(slim.LIB.slim_fwd_noalloc(ctypes.byref(prob), slim._ptr(Q), slim._ptr(K), slim._ptr(V), slim._ptr(W), None,
+                                          None, slim._ptr(Y), None, None, slim._ptr(ks), None, slim._stream()))
+    Yi, _, _ = slim.fwd(Q, K, V, W, 64)
+    torch.cuda.synchronize()
+    report("Y vs tile walk", host64(Y), host64(Yi), TOL["bf16"])
