@@ -1103,6 +1103,20 @@ int fwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V,
   a.P = P;
   a.relu_eps = p->relu_eps;
   hipError_t e = hipSuccess;
+  // A few rows (decoding): one kernel per call, bound by the state's bytes.
+  // (With a context to fill, the tile walk's boundary states are needed.)
+  if (p->dtype == SLIM_BF16 && p->L <= slim::kDecodeRows && ctx == nullptr) {
+    a.seg_state = state_in;
+    a.seg_shift = kshift_in;
+    a.Y = Y;
+    a.logD = logD;
+    a.state_out = state_out;
+    a.kshift_out = kshift_out;
+    const int kind = favor ? slim::kFavor : p->kind == SLIM_RELU ? slim::kRelu : slim::kSquare;
+    e = timed_launch(SLIM_PHASE_FWD, s, [&] { return slim::launch_decode(a, p->d, p->M, kind, s); });
+    if (e != hipSuccess) return hip_fail(e, "forward launch");
+    return ok();
+  }
   if (p->dtype == SLIM_BF16) {
     // W in fragment order, with the low parts of its bf16 split (logits)
     slim::WfragArgs wf;

@@ -1,0 +1,196 @@
+// Forward of a few rows from a carried state (decoding): bf16 problems of at
+// most kDecodeRows rows.
+//
+// Bound: the state, M (d + 1) floats per head, read and written once (133 KB
+// at M = 256, d = 64), and the latency of one kernel.  One workgroup of 1024
+// threads per head; the state's loads are issued before anything else and
+// are in flight while the rows' features are formed.  With S the state
+// before the call, relative to the new key shift,
+//   [N | D]_t = g(q_t)^T S + sum_{s <= t} (g(q_t) . g(k_s)) [v_s | 1],
+//   S' = S + sum_s g(k_s) [v_s | 1]^T,
+// all in float32 from the float32 W (the tile walk rounds features and states
+// to bf16 for the matrix cores: a 32-row tile with one row in it, behind a
+// launch that brings W into fragment order).
+//
+// At B 16, H 8, L 1, M 256, d 64: 10.5 us, where the two launches took 14.1
+// (3.7 + 10.4); a call 15.7 -> 11.6 us, the caller's host work included.
+#include "slim_common.hpp"
+#include "slim_kernels.hpp"
+
+namespace slim {
+
+namespace {
+
+constexpr int kTh = 1024;
+
+template <int D, int M>
+__global__ __launch_bounds__(kTh) void decode_kernel(FwdArgs a, int kind) {
+  constexpr int E = D + 1, SZ = M * E, R = kDecodeRows;
+  constexpr int TPF = kTh / M;        // threads per feature
+  constexpr int EPT = D / TPF;        // columns of W a thread takes
+  constexpr int PER = (SZ + kTh - 1) / kTh;
+  constexpr int PARTS = kTh / D;      // parts of the features in the output sums
+  __shared__ float Ss[SZ];            // S
+  __shared__ float fk[R][M], fq[R][M];
+  __shared__ float xk[R][D], xq[R][D], xv[R][E];
+  __shared__ float red[2 * R + 1][16];
+  __shared__ float A[R][R];
+  __shared__ float part[PARTS][D];
+  __shared__ float dpart[16];
+  const int tid = threadIdx.x, lane = lane_id(), w = wave_id(), L = a.L;
+  const size_t head = blockIdx.x;
+  const float* Sin = a.seg_state != nullptr ? a.seg_state + head * SZ : nullptr;
+  float s[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) s[i] = Sin != nullptr && tid + kTh * i < SZ ? Sin[tid + kTh * i] : 0.f;
+  // W: feature m's columns [e0, e0 + EPT)
+  const int m = tid / TPF, e0 = tid % TPF * EPT;
+  float wr[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) wr[i] = a.W[m * D + e0 + i];
+  const Drop drop{a.drop_seed, a.drop_t, a.C, head};
+  for (int i = tid; i < L * D; i += kTh) {
+    const int t = i / D, e = i % D;
+    const size_t at = (head * a.L + t) * D + e;
+    xk[t][e] = to_f32(((const bf16*)a.K)[at]);
+    xq[t][e] = to_f32(((const bf16*)a.Q)[at]);
+    float v = to_f32(((const bf16*)a.V)[at]);
+    if (a.drop_t != 0 && !(drop_keep_bits<2>(drop, t, e & ~1) >> (e & 1) & 1u)) v = 0.f;
+    xv[t][e] = v;
+    if (e == 0) xv[t][D] = 1.f;
+  }
+  __syncthreads();
+  // logits; the rows' largest ones, and the largest key exponent
+  const bool favor = kind == kFavor;
+  float kmax = -INFINITY;
+  for (int t = 0; t < L; ++t) {
+    float lk = 0.f, lq = 0.f, nk = 0.f;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      lk = fmaf(wr[i], xk[t][e0 + i], lk);
+      lq = fmaf(wr[i], xq[t][e0 + i], lq);
+      nk = fmaf(xk[t][e0 + i], xk[t][e0 + i], nk);
+    }
+    lk = sum_lane_group<TPF>(lk);
+    lq = sum_lane_group<TPF>(lq);
+    if (favor) lk -= 0.5f * sum_lane_group<TPF>(nk);
+    if (tid % TPF == 0) {
+      fk[t][m] = lk;
+      fq[t][m] = lq;
+    }
+    if (favor) {
+      kmax = fmaxf(kmax, lk);
+      const float mq = wave_max(lq);
+      if (lane == 0) red[t][w] = mq;
+    }
+  }
+  float shift = 0.f, ratio = 1.f;
+  if (favor) {
+    kmax = wave_max(kmax);
+    if (lane == 0) red[2 * R][w] = kmax;
+  }
+  __syncthreads();
+  if (favor) {
+    shift = max_lane_group<16>(red[2 * R][tid & 15]);
+    if (Sin != nullptr) {
+      const float old = a.seg_shift[head];
+      shift = fmaxf(shift, old);
+      ratio = exp_f32(old - shift);
+    }
+    if (tid == 0) a.kshift_out[head] = shift;
+  }
+  const float ism = rsqrtf((float)M);
+  for (int i = tid; i < L * M; i += kTh) {
+    const int t = i / M, f = i % M;  // (a wave's features are of one row)
+    const float lk = fk[t][f], lq = fq[t][f];
+    if (favor) {
+      const float mq = max_lane_group<16>(red[t][tid & 15]);
+      fk[t][f] = exp_f32(lk - shift) * ism;
+      fq[t][f] = exp_f32(lq - mq);
+    } else if (kind == kRelu) {
+      fk[t][f] = fmaxf(lk, 0.f) + a.relu_eps;
+      fq[t][f] = fmaxf(lq, 0.f) + a.relu_eps;
+    } else {
+      fk[t][f] = lk * lk;
+      fq[t][f] = lq * lq;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    s[i] *= ratio;
+    if (tid + kTh * i < SZ) Ss[tid + kTh * i] = s[i];
+  }
+  __syncthreads();
+  // scores (one wave per pair), the state after the rows, the outputs
+  for (int p = w; p < L * L; p += 16) {
+    const int t = p / L, u = p - t * L;
+    if (u > t) continue;
+    float x = 0.f;
+#pragma unroll
+    for (int f = lane; f < M; f += 64) x = fmaf(fq[t][f], fk[u][f], x);
+    x = wave_sum_over_c(wave_sum_over_g(x));
+    if (lane == 0) A[t][u] = x;
+  }
+  if (a.state_out != nullptr) {
+    float* So = a.state_out + head * SZ;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int el = tid + kTh * i, f = el / E, e = el - f * E;
+      if (el >= SZ) continue;
+      float x = s[i];
+      for (int u = 0; u < L; ++u) x = fmaf(fk[u][f], xv[u][e], x);
+      So[el] = x;
+    }
+  }
+  const int e = tid % D, q = tid / D;  // column and part of the features
+  constexpr int FP = M / PARTS;
+  for (int t = 0; t < L; ++t) {
+    float x = 0.f;
+#pragma unroll
+    for (int f = q * FP; f < (q + 1) * FP; ++f) x = fmaf(fq[t][f], Ss[f * E + e], x);
+    part[q][e] = x;
+    float z = 0.f;
+    for (int f = tid; f < M; f += kTh) z = fq[t][f] * Ss[f * E + D];
+    z = wave_sum_over_c(wave_sum_over_g(z));
+    if (lane == 0) dpart[w] = z;
+    __syncthreads();  // (and the scores, before the first row)
+    if (tid < D) {
+      float n = part[0][tid], d = 0.f;
+#pragma unroll
+      for (int p = 1; p < PARTS; ++p) n += part[p][tid];
+#pragma unroll
+      for (int p = 0; p < (M + 63) / 64; ++p) d += dpart[p];
+      for (int u = 0; u <= t; ++u) {
+        n = fmaf(A[t][u], xv[u][tid], n);
+        d += A[t][u];
+      }
+      ((bf16*)a.Y)[(head * a.L + t) * D + tid] = (bf16)(n * (a.drop_scale / d));
+      if (tid == 0 && a.logD != nullptr) {
+        float mq = 0.f;
+        if (favor) {
+          mq = red[t][0];
+          for (int p = 1; p < 16; ++p) mq = fmaxf(mq, red[t][p]);
+        }
+        a.logD[head * a.L + t] = __log2f(d) + (mq + shift) * kLog2e;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+template <int D>
+hipError_t launch_d(const FwdArgs& a, int M, int kind, hipStream_t s) {
+  const dim3 g(a.B * a.H), b(kTh);
+  if (M == 256) hipLaunchKernelGGL((decode_kernel<D, 256>), g, b, 0, s, a, kind);
+  else if (M == 128) hipLaunchKernelGGL((decode_kernel<D, 128>), g, b, 0, s, a, kind);
+  else hipLaunchKernelGGL((decode_kernel<D, 64>), g, b, 0, s, a, kind);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_decode(const FwdArgs& a, int d, int M, int kind, hipStream_t s) {
+  return d == 64 ? launch_d<64>(a, M, kind, s) : launch_d<32>(a, M, kind, s);
+}
+
+}  // namespace slim

@@ -1,0 +1,83 @@
+"""The forward of a few rows (decoding: at most 8, one kernel) against the
+oracle and against the rows of one long call: every (d, M), the three maps,
+one row to the limit and one past it (the tile walk), with and without a
+carried state, dropout, the row normalisers, and a NaN query.
+
+Bar: 2e-2 max-relative (bf16 rows); the state, which is float32 throughout
+here, against the tile walk's (bf16 products) within the same."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth import Workload, make_inputs
+from tests.gpu_common import TOL, dev, host64, need_gpu, report
+
+pytestmark = pytest.mark.gpu
+
+# B, H, prefix rows, L, d, M, kind, dropout
+CASES = [
+    (2, 3, 40, 1, 64, 256, "favor+", 0.0),
+    (1, 2, 0, 8, 64, 256, "favor+", 0.0),
+    (1, 2, 33, 9, 64, 256, "favor+", 0.0),
+    (1, 1, 70, 5, 64, 128, "favor+", 0.3),
+    (3, 1, 20, 2, 32, 256, "relu", 0.0),
+    (1, 2, 0, 1, 32, 128, "favor+", 0.0),
+    (1, 2, 50, 7, 32, 64, "relu", 0.2),
+    (2, 1, 64, 3, 64, 64, "square", 0.0),
+]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_a_few_rows(i):
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    B, H, pre, L, d, M, kind, p = CASES[i]
+    print(f"[decode] case={i} {CASES[i]}", flush=True)
+    n = pre + L
+    x = make_inputs(Workload(f"dec{i}", 995 + i, B, H, n, d, M, (n,), "bf16", kind), tensors=("Q", "K", "V", "W"))
+    if kind == "square":
+        x["W"] = torch.eye(64, dtype=torch.float32)
+    Q, K, V, W = (dev(x[k]) for k in ("Q", "K", "V", "W"))
+    cut = lambda t, a, b: t[:, :, a:b].contiguous()
+    st = ks = None
+    if pre:
+        _, st, ks = slim.fwd(cut(Q, 0, pre), cut(K, 0, pre), cut(V, 0, pre), W, 16, kind)
+    logD = torch.empty(B, H, L, device="cuda")
+    q, k, v = (cut(t, pre, n) for t in (Q, K, V))
+    # (slice length 3: the dropout's seeds change inside the call)
+    Y, s1, k1 = slim.fwd(q, k, v, W, 3, kind, state_in=st, kshift_in=ks, dropout=p, seed=5, logD=logD)
+    torch.cuda.synchronize()
+    tol = TOL["bf16"]
+    true = lambda s, sh: host64(s) * (np.exp(host64(sh))[:, :, None, None] if kind == "favor+" else 1.0)
+    mask = O.value_mask(B, H, L, d, 3, p, 5)
+    vm = host64(v) * mask
+    ref, sref = O.slim_forward(host64(q), host64(k), vm, x["W"], L, kind, state_in=None if st is None else true(st, ks),
+                               within="quadratic")
+    report("Y", host64(Y), ref / (1.0 - p), tol)
+    report("state_out", true(s1, k1), sref, tol)
+    # the row normalisers against the tile walk's (16 rows)
+    if L <= 8 and pre == 0:
+        pad = 16 - L
+        qq, kk, vv = (torch.cat([t, t[:, :, -1:].expand(-1, -1, pad, -1)], 2).contiguous() for t in (q, k, v))
+        lw = torch.empty(B, H, 16, device="cuda")
+        slim.fwd(qq, kk, vv, W, 16, kind, logD=lw)
+        torch.cuda.synchronize()
+        assert torch.allclose(logD, lw[:, :, :L], atol=2e-2), (logD - lw[:, :, :L]).abs().max()
+
+
+def test_nan_query_stays_in_its_row():
+    need_gpu()
+    from paper_2012_11346_amd import slim
+
+    x = make_inputs(Workload("decn", 1005, 1, 2, 4, 64, 256, (4,), "bf16", "favor+"), tensors=("Q", "K", "V", "W"))
+    x["Q"][0, 0, 2, 3] = float("nan")
+    Q, K, V, W = (dev(x[k]) for k in ("Q", "K", "V", "W"))
+    print("[decode] NaN query", flush=True)
+    Y, st, _ = slim.fwd(Q, K, V, W, 4)
+    torch.cuda.synchronize()
+    Y = Y.float().cpu()
+    assert torch.isnan(Y[0, 0, 2]).all() and torch.isfinite(Y[0, 0, [0, 1, 3]]).all() and torch.isfinite(Y[0, 1]).all()
+    assert torch.isfinite(st).all()
