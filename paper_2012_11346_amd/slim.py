@@ -146,11 +146,12 @@ def problem(B, H, L, d, M, C, dtype=BF16, kind=FAVOR_PLUS, relu_eps=1e-3, dropou
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # (a c_void_p parameter takes the address as an int, or None)
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _problem_of(Q: torch.Tensor, W: torch.Tensor, C: int, kind, relu_eps: float, dropout=0.0, seed=0,
@@ -162,6 +163,9 @@ def _problem_of(Q: torch.Tensor, W: torch.Tensor, C: int, kind, relu_eps: float,
 
 
 def _need(t: torch.Tensor, name: str, dtype: torch.dtype, shape=None):
+    # (one test where all is well: a decoding call makes about ten of these)
+    if t.is_cuda and t.dtype == dtype and t.is_contiguous() and (shape is None or t.shape == shape):
+        return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype != dtype:
@@ -208,7 +212,7 @@ def time_walk(phase: int, before: "torch.cuda.Event", after: "torch.cuda.Event")
 
 
 def _nbytes(t: torch.Tensor) -> int:
-    return t.numel() * t.element_size()
+    return t.nbytes
 
 
 def _workspace(p: Problem, phase: int, device, ws: Optional[torch.Tensor]):
@@ -252,27 +256,34 @@ def fwd(Q, K, V, W, C: int, kind="favor+", state_in=None, kshift_in=None, relu_e
     dropout / seed: value dropout with per-slice seeds; within: "iter",
     "quadratic" or "ps" (include/slim.h)."""
     p = _problem_of(Q, W, C, kind, relu_eps, dropout, seed, within)
-    shp = (p.B, p.H, p.L, p.d)
-    for n, t in (("Q", Q), ("K", K), ("V", V)):
-        _need(t, n, Q.dtype, shp)
-    _need(W, "W", torch.float32, (p.M, p.d))
-    sshape = (p.B, p.H, p.M, p.d + 1)
+    shp, dt, f32 = Q.shape, Q.dtype, torch.float32
+    B, H, L, d = shp
+    M = W.shape[0]
+    _need(Q, "Q", dt)
+    _need(K, "K", dt, shp)
+    _need(V, "V", dt, shp)
+    _need(W, "W", f32, (M, d))
+    sshape = (B, H, M, d + 1)
     if state_in is not None:
-        _need(state_in, "state_in", torch.float32, sshape)
+        _need(state_in, "state_in", f32, sshape)
     if kshift_in is not None:
-        _need(kshift_in, "kshift_in", torch.float32, (p.B, p.H))
+        _need(kshift_in, "kshift_in", f32, (B, H))
     dev = Q.device
-    Y = torch.empty_like(Q) if Y is None else Y
-    _need(Y, "Y", Q.dtype, shp)
-    state_out = torch.empty(sshape, dtype=torch.float32, device=dev) if state_out is None else state_out
-    _need(state_out, "state_out", torch.float32, sshape)
-    if p.kind == FAVOR_PLUS and kshift_out is None:
-        kshift_out = torch.empty((p.B, p.H), dtype=torch.float32, device=dev)
+    if Y is None:
+        Y = torch.empty_like(Q)
+    else:
+        _need(Y, "Y", dt, shp)
+    if state_out is None:
+        state_out = torch.empty(sshape, dtype=f32, device=dev)
+    else:
+        _need(state_out, "state_out", f32, sshape)
     if kshift_out is not None:
-        _need(kshift_out, "kshift_out", torch.float32, (p.B, p.H))
+        _need(kshift_out, "kshift_out", f32, (B, H))
+    elif p.kind == FAVOR_PLUS:
+        kshift_out = torch.empty((B, H), dtype=f32, device=dev)
     _need_ctx(p, ctx)
     if logD is not None:
-        _need(logD, "logD", torch.float32, (p.B, p.H, p.L))
+        _need(logD, "logD", f32, (B, H, L))
     ws = _workspace(p, PHASE_FWD, dev, ws)
     _check(LIB.slim_fwd(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(state_in), _ptr(kshift_in),
                         _ptr(Y), _ptr(logD), _ptr(state_out), _ptr(kshift_out), _ptr(ctx), _ptr(ws), _nbytes(ws),
