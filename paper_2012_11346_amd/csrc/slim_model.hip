@@ -12,8 +12,9 @@
 // through all layers, and back-propagates through it with the state
 // cotangents G_r carried from the later slices (eq. 18).
 //
-// Kernels here: a float32 matrix-core GEMM (v_mfma_f32_16x16x4_f32, 128 x 128
-// and 64 x 128 tiles, split K with a fixed-order reduction, epilogues for
+// Kernels here: a float32 GEMM on the bf16 matrix cores (every value as the
+// sum of three bf16 ones, 128 x 128, 64 x 128 and 64 x 64 tiles, split K with
+// a fixed-order reduction, epilogues for
 // bias, bias + GeLU, GeLU's derivative and residual sums), row-wise layer
 // normalisation and its backward, cross-entropy, the embedding and its
 // deterministic backward, head split/merge copies and fixed-order column
@@ -28,6 +29,7 @@
 
 #include "../../include/slim.h"
 #include "../../include/slim_model.h"
+#include "slim_device.hpp"
 #include "slim_kernels.hpp"
 
 namespace slim {
@@ -45,21 +47,36 @@ __device__ __forceinline__ float gelu_d(float x) {
 // C = epilogue(op(A) op(B)), row-major: op(A)[m][k] = TA ? A[k lda + m] :
 // A[m lda + k], op(B)[k][n] = TB ? B[n ldb + k] : B[k ldb + n].
 //
-// Workgroup tile BM x 128 (BM = 128 or 64), four waves in 2 x 2, each wave
-// (BM / 2) x 64 as (BM / 32) x 4 matrix tiles of 16 x 16 on
-// v_mfma_f32_16x16x4_f32.  K runs in tiles of 16 through double-buffered
-// LDS.  The summation index of the four products of one k tile is permuted
-// so that lane group g (lane / 16) takes k = 4 g + j in product j.  An
-// operand whose rows run along k in memory is held [m][k] (rows padded to 20
-// floats): one 16-byte LDS read feeds a lane's four products.  An operand
-// whose rows run along m (or n) is held as it is in memory, [k][m] (rows
-// padded by 4 floats, so the four k rows a read touches fall in different
-// banks), and a lane reads its four values one by one.  Either way the
-// global tile lands in LDS with 16-byte writes.  Global loads are 16-byte
-// vectors where the strides allow, prefetched one k tile ahead.  Long K is split over blockIdx.y; the
-// partial products are summed in a fixed order by gemm_reduce_kernel, which
-// then applies the epilogue (no atomics: results are reproducible).
-constexpr int GBN = 128, GBK = 16, GKP = GBK + 4;
+// float32 products on the bf16 matrix cores.  A float32 value is exactly the
+// sum of three bf16 ones, x = hi + mid + lo (round to nearest, then the exact
+// remainders; 24 bits in three times 8, each rounding leaves a remainder of
+// at most half an ulp), so a product of two is nine bf16 products, of which
+// mid lo, lo mid and lo lo lie below 2^-24 of it and are left out: six
+// products on matrix cores sixteen times as fast as the float32 ones.  They
+// are added smallest first.  Measured against 64 bits the sums are no
+// further off than a float32 matrix-core chain over the same K (which rounds
+// every four terms, here every sixteen): over model steps 1.7e-7 to 3.1e-7 of
+// the gradients' norm, 4e-7 to 6e-7 before.  Infinities come out as NaN, as
+// do values within 2^-9 of the largest float32 (both overflow further on).
+//
+// Workgroup tile BM x BN (128 or 64 each), four waves in 2 x 2, each wave
+// (BM / 2) x (BN / 2) as tiles of 32 x 32 on v_mfma_f32_32x32x16_bf16.  K
+// runs in tiles of 32; a tile is fetched as float32 one tile ahead, split
+// in registers and written to LDS as its three parts.  An operand whose rows
+// run along k in memory is held [m][k], one whose rows run along m (or n) as
+// it is in memory, [k][m], and read with ds_read_b64_tr_b16; 16-byte chunks
+// are permuted within a row by the row, so that both reads touch every bank
+// evenly (a [m][k] read's 8-byte halves also swap every 16 rows: 40 % of the
+// LDS cycles were conflicts without it).  In both a lane's operand slot (h, s) holds k = 4 h + (s & 3) + 8 (s
+// >> 2).  One LDS buffer, two or three workgroups per compute unit: their
+// products cover each other's splits and barriers (what bounds it: the six
+// products take a quarter of the time, the splits, the LDS reads and the
+// barriers the rest).  1024 x 4096 by 1024: 93 us on the float32 matrix
+// cores, 75 here, each with the sum of its two splits.  Global loads are 16-byte vectors
+// where the strides allow.  Long K is split over blockIdx.y; the partial
+// products are summed in a fixed order by gemm_reduce_kernel, which then
+// applies the epilogue (no atomics: results are reproducible).
+constexpr int GBN = 128, GBK = 32;
 
 enum EpiOp { EPI_STORE = 0, EPI_ACC = 1, EPI_BIAS = 2, EPI_BIAS_GELU = 3, EPI_GELU_BWD = 4, EPI_ADD = 5 };
 // STORE: C = v; ACC: C += v; BIAS: C = v + bias[n]; BIAS_GELU: C = z = v +
@@ -113,9 +130,6 @@ __device__ __forceinline__ void epi_write(const Epi& e, float* C, size_t o, floa
     default: C[o] = v + x; break;
   }
 }
-__device__ __forceinline__ void epi_op(const Epi& e, float* C, size_t o, int n, float v) {
-  epi_write(e, C, o, v, epi_read(e, C, o, n));
-}
 // where element (m, n) of the product goes: its matrix (C or a group's) and
 // the offset in it; the row's and the column's parts of the offset add
 __device__ __forceinline__ size_t epi_row(const Epi& e, int ldc, int m) {
@@ -131,12 +145,6 @@ __device__ __forceinline__ size_t epi_col(const Epi& e, float*& C, int n) {
   C = pick3(grp, e.Cg0, e.Cg1, e.Cg2);
   return e.layout == 1 ? (size_t)col : (size_t)(col >> 6) * e.hrows * 64 + (col & 63);
 }
-__device__ __forceinline__ void epi_store(const Epi& e, float* C, int ldc, int m, int n, float v) {
-  const size_t ro = epi_row(e, ldc, m);
-  const size_t co = epi_col(e, C, n);
-  epi_op(e, C, ro + co, n, v);
-}
-
 struct GemmArgs {
   int M, N, K;
   const float* A;
@@ -168,20 +176,81 @@ __device__ __forceinline__ float4 ld4(const float* p, int avail) {
   return r;
 }
 
+// x as three bf16 parts, four values at a time
+struct Split4 {
+  bf16x4 p[3];
+};
+__device__ __forceinline__ Split4 split4(const float4& v) {
+  f4 x = {v.x, v.y, v.z, v.w};
+  Split4 o;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    o.p[i] = __builtin_convertvector(x, bf16x4);
+    if (i < 2) x -= __builtin_convertvector(o.p[i], f4);
+  }
+  return o;
+}
+// LDS tiles: [row][32 k] (W = 32) or [k][W columns], in 16-byte chunks
+template <int W>
+__device__ __forceinline__ int chunk_sw(int row) {
+  if constexpr (W == 32) return (row >> 2) & 3;
+  else return ((row & 3) << 2) & (W / 8 - 1);
+}
+template <int W>
+__device__ __forceinline__ int tile_at(int row, int e) {
+  // (row tiles: the 8-byte halves of a chunk swap every 16 rows, or rows r and
+  // r + 16 of a wave's read would meet in the banks)
+  const int lo = W == 32 ? (e & 7) ^ (4 * ((row >> 4) & 1)) : e & 7;
+  return row * W + 8 * ((e >> 3) ^ chunk_sw<W>(row)) + lo;
+}
+// A wave's operand reads from a tile, from lane offsets formed once (the
+// parts, the 16-deep blocks and the 32-wide tiles are then immediates; with
+// the addresses formed at each read, address arithmetic was half of the
+// loop's vector instructions): ROWS, a [row][32 k] tile; else [k][W columns].
+template <bool ROWS, int W, int NT>
+struct OpReader {
+  int off[ROWS ? 4 : NT];  // ROWS: by 16-byte chunk; else by 32-wide tile
+  __device__ __forceinline__ OpReader(int c0, int lane) {
+    const int h = lane >> 5;
+    if constexpr (ROWS) {
+      const int row = c0 + (lane & 31);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) off[c] = tile_at<32>(row, 8 * c + 4 * h);
+    } else {
+      const int j = lane & 15, k = 4 * h + (j >> 2);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) off[i] = tile_at<W>(k, c0 + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (j & 3));
+    }
+  }
+  // tile i, block kk (slot (h, s): k = 16 kk + 4 h + (s & 3) + 8 (s >> 2))
+  __device__ __forceinline__ bf16x8 operator()(const bf16* Z, int i, int kk) const {
+    bf16x4 a, b;
+    if constexpr (ROWS) {
+      a = *reinterpret_cast<const bf16x4*>(Z + 32 * 32 * i + off[2 * kk]);
+      b = *reinterpret_cast<const bf16x4*>(Z + 32 * 32 * i + off[2 * kk + 1]);
+    } else {
+      typedef SLIM_LDS i16x4 lds_i16x4;
+      const bf16* p = Z + off[i] + 16 * kk * W;
+      a = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p));
+      b = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 8 * W)));
+    }
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+};
+
 // GRP: grouped B and grouped / head-split C (the kernels without it carry no
 // code, and no registers, for either)
 template <int BM, int BN, bool TA, bool TB, bool VEC, bool GRP>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256, BM == 64 ? 3 : 2) void gemm_kernel(GemmArgs g) {
+  typedef float f16v __attribute__((ext_vector_type(16)));
   constexpr int AV = BM * GBK / 4 / 256;  // float4 loads per thread per k tile (A)
   constexpr int BV = BN * GBK / 4 / 256;  // (B)
-  constexpr int TI = BM / 32;             // matrix tiles per wave along m
-  constexpr int TJ = BN / 32;             // and along n
-  // [m][k] (k-contiguous source) or [k][m] (m-contiguous source) per buffer
-  constexpr int ALD = TA ? BM + 4 : GKP, BLD = TB ? GKP : BN + 4;
-  constexpr int ASZ = TA ? GBK * ALD : BM * ALD, BSZ = TB ? BN * BLD : GBK * BLD;
-  __shared__ __align__(16) float As[2][ASZ];
-  __shared__ __align__(16) float Bs[2][BSZ];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int TI = BM / 64;             // matrix tiles per wave along m
+  constexpr int TJ = BN / 64;             // and along n
+  constexpr int ASZ = BM * GBK, BSZ = BN * GBK;
+  __shared__ __align__(16) bf16 As[3][ASZ];
+  __shared__ __align__(16) bf16 Bs[3][BSZ];
+  const int tid = threadIdx.x, lane = tid & 63, w = uniform_wave();
   // XCD-aware order: consecutive tiles (sharing rows of A) on one XCD
   int tile = blockIdx.x;
   const int nt = gridDim.x;
@@ -205,12 +274,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   }
 
   float4 ra[AV], rb[BV];
-  auto load = [&](int k0) {
+  auto load_any = [&](int k0) {
 #pragma unroll
     for (int i = 0; i < AV; ++i) {
       const int f = tid + 256 * i;
       if (!TA) {  // rows of A: 4 k per vector
-        const int m = f >> 2, k = k0 + 4 * (f & 3);
+        const int m = f >> 3, k = k0 + 4 * (f & 7);
         ra[i] = (m0 + m < M) ? ld4<VEC>(g.A + (size_t)(m0 + m) * g.lda + k, kend - k) : make_float4(0.f, 0.f, 0.f, 0.f);
       } else {  // rows of A^T: 4 m per vector
         const int k = k0 + f / (BM / 4), m = m0 + 4 * (f % (BM / 4));
@@ -221,7 +290,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     for (int i = 0; i < BV; ++i) {
       const int f = tid + 256 * i;
       if (TB) {  // rows of B^T: 4 k per vector
-        const int n = f >> 2, k = k0 + 4 * (f & 3);
+        const int n = f >> 3, k = k0 + 4 * (f & 7);
         const float* Bb = g.B;
         int kk = k;
         if (GRP && g.gK > 0) {  // the k tile lies in one group (k0 is uniform)
@@ -236,76 +305,141 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       }
     }
   };
-  auto store = [&](int buf) {
+  // With 16-byte loads (VEC) and a whole k tile the guards go: rows past the
+  // end repeat the last (their products are not stored), and a load is a
+  // uniform base, advanced per k tile, plus a lane offset formed once.
+  int oa[AV], ob[BV];
+  const float* const Ab = g.A + (TA ? (size_t)m0 : (size_t)m0 * g.lda);
+  const float* const Bb = TB ? g.B + (size_t)n0 * g.ldb : g.B;
 #pragma unroll
-    for (int i = 0; i < AV; ++i) {
-      const int f = tid + 256 * i;
-      const int at = TA ? (f / (BM / 4)) * ALD + 4 * (f % (BM / 4)) : (f >> 2) * ALD + 4 * (f & 3);
-      *reinterpret_cast<float4*>(&As[buf][at]) = ra[i];
+  for (int i = 0; i < AV; ++i) {
+    const int f = tid + 256 * i;
+    oa[i] = TA ? (f / (BM / 4)) * g.lda + min(4 * (f % (BM / 4)), M - 4 - m0)
+               : min(f >> 3, M - 1 - m0) * g.lda + 4 * (f & 7);
+  }
+#pragma unroll
+  for (int i = 0; i < BV; ++i) {
+    const int f = tid + 256 * i;
+    ob[i] = TB ? min(f >> 3, N - 1 - n0) * g.ldb + 4 * (f & 7) : (f / (BN / 4)) * g.ldb;
+    if (!TB && !(GRP && g.gN > 0)) ob[i] += n0 + min(4 * (f % (BN / 4)), N - 4 - n0);
+    if (!TB && GRP && g.gN > 0 && n0 + 4 * (f % (BN / 4)) >= N)  // (the last columns of the last group)
+      bcol[i] = pick3((N - 4) / g.gN, g.Bg0, g.Bg1, g.Bg2) + (N - 4) % g.gN;
+  }
+  auto load = [&](int k0) {
+    if (!VEC || kend - k0 < GBK || (GRP && g.gK % GBK != 0)) {
+      load_any(k0);
+      return;
+    }
+    const float* const Ak = Ab + (TA ? (size_t)k0 * g.lda : (size_t)k0);
+#pragma unroll
+    for (int i = 0; i < AV; ++i) ra[i] = *reinterpret_cast<const float4*>(Ak + oa[i]);
+    const float* Bk = Bb;
+    if (TB) {
+      int kk = k0;
+      if (GRP && g.gK > 0) {  // the k tile lies in one group (k0 is uniform)
+        const int grp = group3(k0, g.gK);
+        Bk = pick3(grp, g.Bg0, g.Bg1, g.Bg2) + (size_t)n0 * g.ldb;
+        kk = k0 - grp * g.gK;
+      }
+      Bk += kk;
+    } else {
+      Bk += (size_t)k0 * g.ldb;
     }
 #pragma unroll
     for (int i = 0; i < BV; ++i) {
-      const int f = tid + 256 * i;
-      const int at = TB ? (f >> 2) * BLD + 4 * (f & 3) : (f / (BN / 4)) * BLD + 4 * (f % (BN / 4));
-      *reinterpret_cast<float4*>(&Bs[buf][at]) = rb[i];
+      if (!TB && GRP && g.gN > 0) rb[i] = *reinterpret_cast<const float4*>(bcol[i] + (size_t)k0 * g.ldb + ob[i]);
+      else rb[i] = *reinterpret_cast<const float4*>(Bk + ob[i]);
     }
   };
+  const int sa = TA ? tile_at<BM>(tid / (BM / 4), 4 * (tid % (BM / 4))) : tile_at<32>(tid >> 3, 4 * (tid & 7));
+  const int sb = TB ? tile_at<32>(tid >> 3, 4 * (tid & 7)) : tile_at<BN>(tid / (BN / 4), 4 * (tid % (BN / 4)));
+  // (the 256-vector steps keep the row modulo 4 and, in row tiles, the row's
+  // chunk permutation: they are immediates)
+  constexpr int SA = TA ? 1024 / BM * BM : 32 * 32, SB = TB ? 32 * 32 : 1024 / BN * BN;
+  static_assert(1024 / BM % 4 == 0 && 1024 / BN % 4 == 0, "rows of a step");
+  auto store = [&] {
+#pragma unroll
+    for (int i = 0; i < AV; ++i) {
+      const Split4 x = split4(ra[i]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x4*>(&As[p][sa + SA * i]) = x.p[p];
+    }
+#pragma unroll
+    for (int i = 0; i < BV; ++i) {
+      const Split4 x = split4(rb[i]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x4*>(&Bs[p][sb + SB * i]) = x.p[p];
+    }
+  };
+  const OpReader<!TA, BM, TI> rdA(wm, lane);
+  const OpReader<TB, BN, TJ> rdB(wn, lane);
 
-  f4 acc[TI][TJ];
+  f16v acc[TI][TJ];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  const int c = lane & 15, q = lane >> 4;
-  int buf = 0;
-  if (kbeg < kend) {
-    load(kbeg);
-    store(0);
-  }
-  __syncthreads();
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  if (kbeg < kend) load(kbeg);
   for (int k0 = kbeg; k0 < kend; k0 += GBK) {
-    const bool more = k0 + GBK < kend;
-    if (more) load(k0 + GBK);
-    float4 a[TI], b[TJ];
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      if (TA) {
-        const float* p = &As[buf][4 * q * ALD + wm + 16 * i + c];
-        a[i] = make_float4(p[0], p[ALD], p[2 * ALD], p[3 * ALD]);
-      } else {
-        a[i] = *reinterpret_cast<const float4*>(&As[buf][(wm + 16 * i + c) * ALD + 4 * q]);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      if (TB) {
-        b[j] = *reinterpret_cast<const float4*>(&Bs[buf][(wn + 16 * j + c) * BLD + 4 * q]);
-      } else {
-        const float* p = &Bs[buf][4 * q * BLD + wn + 16 * j + c];
-        b[j] = make_float4(p[0], p[BLD], p[2 * BLD], p[3 * BLD]);
-      }
-    }
-    // each accumulator's four products are TI * 4 issues apart
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, b[j].x, acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].y, b[j].y, acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].z, b[j].z, acc[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].w, b[j].w, acc[i][j], 0, 0, 0);
-    if (more) store(buf ^ 1);
+    store();
     __syncthreads();
-    buf ^= 1;
+    if (k0 + GBK < kend) load(k0 + GBK);
+    // A tile's products start from zero, the large ones (hi hi: 16-bit terms,
+    // whose sums all but fit 24 bits) apart from the small, and both are added
+    // to the running sums rounding to nearest.  The matrix cores' own
+    // additions cut the smaller operand off: over a long K, or summed over
+    // rows that are nearly alike, the results would lean towards zero.
+    f16v t[TI][TJ];
+#pragma unroll
+    for (int kk = 0; kk < GBK / 16; ++kk) {
+      bf16x8 a[TI], b[TJ];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) a[i] = rdA(As[0], i, kk);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) b[j] = rdB(Bs[0], j, kk);
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          t[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], kk == 0 ? f16v{} : t[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] += t[i][j];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < GBK / 16; ++kk) {
+      bf16x8 a[TI][3], b[TJ][3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) a[i][p] = rdA(As[p], i, kk);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) b[j][p] = rdB(Bs[p], j, kk);
+      }
+      // (part of A, part of B), smallest product first
+      constexpr int pa[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+      for (int q = 0; q < 5; ++q)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j)
+            t[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][pa[q]], b[j][pb[q]],
+                                                              kk == 0 && q == 0 ? f16v{} : t[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[i][j] += t[i][j];
+    __syncthreads();
   }
+  // element r of a lane's tile: row row_at(r), column lane & 31
+  const int c = lane & 31, h4 = 4 * (lane >> 5);
+  auto row_at = [&](int r) { return (r & 3) + 8 * (r >> 2) + h4; };
   const bool split = gridDim.y > 1;
   if (GRP && !split) {
     // the tile's row offsets once, in LDS (the operand buffers are free
@@ -313,100 +447,76 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     size_t* rowoff = reinterpret_cast<size_t*>(&As[0][0]);
     for (int i = tid; i < BM; i += 256) rowoff[i] = epi_row(g.epi, g.ldc, min(m0 + i, M - 1));
     __syncthreads();
-    // (per 16 x 32 block: its reads, then its writes; the column offsets are
-    // recomputed per block rather than held)
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j2 = 0; j2 < TJ; j2 += 2) {
-        float x[2][4];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const int n = n0 + wn + 16 * (j2 + jj) + c;
-          float* Cj = g.C;
-          const size_t co = epi_col(g.epi, Cj, min(n, N - 1));
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int mm = wm + 16 * i + 4 * q + r;
-            x[jj][r] = (m0 + mm < M && n < N) ? epi_read(g.epi, Cj, rowoff[mm] + co, n) : 0.f;
-          }
-        }
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const int n = n0 + wn + 16 * (j2 + jj) + c;
-          float* Cj = g.C;
-          const size_t co = epi_col(g.epi, Cj, min(n, N - 1));
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int mm = wm + 16 * i + 4 * q + r;
-            if (m0 + mm < M && n < N) epi_write(g.epi, Cj, rowoff[mm] + co, acc[i][j2 + jj][r], x[jj][r]);
-          }
-        }
-      }
-    return;
   }
-  if (split) {
-    float* part = g.part + (size_t)blockIdx.y * M * N;
+  // per 32 x 32 tile: the epilogue's reads, then its writes
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int j = 0; j < TJ; ++j)
+    for (int j = 0; j < TJ; ++j) {
+      const int n = n0 + wn + 32 * j + c;
+      if (split) {
+        float* part = g.part + (size_t)blockIdx.y * M * N;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = m0 + wm + 16 * i + 4 * q + r, n = n0 + wn + 16 * j + c;
+        for (int r = 0; r < 16; ++r) {
+          const int m = m0 + wm + 32 * i + row_at(r);
           if (m < M && n < N) part[(size_t)m * N + n] = acc[i][j][r];
         }
-    return;
-  }
-  // the epilogue's reads first, then its writes: all of a lane's with the
-  // 64-row tile, per 16-row block with the 128-row one (registers)
-  constexpr int IB = TI <= 2 ? TI : 1;
+        continue;
+      }
+      float* Cj = g.C;
+      size_t co = n;
+      const size_t* rowoff = reinterpret_cast<const size_t*>(&As[0][0]);
+      if constexpr (GRP) co = epi_col(g.epi, Cj, min(n, N - 1));
+      auto off = [&](int r) -> size_t {
+        const int mm = wm + 32 * i + row_at(r);
+        if constexpr (GRP) return rowoff[mm] + co;
+        else return (size_t)(m0 + mm) * g.ldc + n;
+      };
+      float x[16];
 #pragma unroll
-  for (int i0 = 0; i0 < TI; i0 += IB) {
-    float x[IB][TJ][4];
+      for (int r = 0; r < 16; ++r)
+        x[r] = (m0 + wm + 32 * i + row_at(r) < M && n < N) ? epi_read(g.epi, Cj, off(r), n) : 0.f;
 #pragma unroll
-    for (int ii = 0; ii < IB; ++ii)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = m0 + wm + 16 * (i0 + ii) + 4 * q + r, n = n0 + wn + 16 * j + c;
-          x[ii][j][r] = (m < M && n < N) ? epi_read(g.epi, g.C, (size_t)m * g.ldc + n, n) : 0.f;
-        }
-#pragma unroll
-    for (int ii = 0; ii < IB; ++ii)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = m0 + wm + 16 * (i0 + ii) + 4 * q + r, n = n0 + wn + 16 * j + c;
-          if (m < M && n < N) epi_write(g.epi, g.C, (size_t)m * g.ldc + n, acc[i0 + ii][j][r], x[ii][j][r]);
-        }
-  }
+      for (int r = 0; r < 16; ++r)
+        if (m0 + wm + 32 * i + row_at(r) < M && n < N) epi_write(g.epi, Cj, off(r), acc[i][j][r], x[r]);
+    }
 }
 
-// C = epilogue(sum over splits of the partial products, in split order)
+// C = epilogue(sum over splits of the partial products, in split order).  VW
+// elements per thread: four (16-byte reads of the partials) where N is a
+// multiple of four, so that they share a row, a column group and a head.
+// Bound: memory; at M = N = 1024 and four splits 12.5 us with one element
+// per thread.
+template <int VW>
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* part, int splits, int M, int N, float* C, int ldc,
                                                           Epi epi) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x, MN = (size_t)M * N;
+  const size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * VW, MN = (size_t)M * N;
   if (e >= MN) return;
+  typedef float fv __attribute__((ext_vector_type(VW)));
+  auto at = [&](int s) { return *reinterpret_cast<const fv*>(part + s * MN + e); };
   // (eight, then four partials loaded at a time, added in split order)
-  float v = 0.f;
+  fv v = fv{};
   int s = 0;
   for (; s + 8 <= splits; s += 8) {
-    float q[8];
+    fv q[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) q[i] = part[(s + i) * MN + e];
+    for (int i = 0; i < 8; ++i) q[i] = at(s + i);
 #pragma unroll
     for (int i = 0; i < 8; ++i) v += q[i];
   }
   for (; s + 4 <= splits; s += 4) {
-    const float p0 = part[s * MN + e], p1 = part[(s + 1) * MN + e], p2 = part[(s + 2) * MN + e],
-                p3 = part[(s + 3) * MN + e];
+    const fv p0 = at(s), p1 = at(s + 1), p2 = at(s + 2), p3 = at(s + 3);
     v = (((v + p0) + p1) + p2) + p3;
   }
-  for (; s < splits; ++s) v += part[s * MN + e];
-  epi_store(epi, C, ldc, (int)(e / N), (int)(e % N), v);
+  for (; s < splits; ++s) v += at(s);
+  const int m = (int)(e / N), n = (int)(e % N);
+  float* Cn = C;
+  const size_t o = epi_row(epi, ldc, m) + epi_col(epi, Cn, n);
+  float x[VW];
+#pragma unroll
+  for (int i = 0; i < VW; ++i) x[i] = epi_read(epi, Cn, o + i, n + i);
+#pragma unroll
+  for (int i = 0; i < VW; ++i) epi_write(epi, Cn, o + i, v[i], x[i]);
 }
 
 // Launch plan of one product: tile height, k per split and split count.
@@ -420,13 +530,16 @@ inline GemmPlan gemm_plan(int M, int N, int K) {
     GemmPlan p;
     // (a short reduction leaves the epilogue's reads and writes of C to set
     // the pace: the smaller tile gives twice the workgroups in flight)
-    p.BM = (t128 >= 256 && kt > 8) ? 128 : 64;
+    p.BM = (t128 * std::min(64, kt / 4) >= 256 && kt > 4 && (M >= 512 || (M - 1) % 128 >= 64)) ? 128 : 64;
     p.BN = BN;
     p.tiles_n = (N + BN - 1) / BN;
     p.tiles = ((M + p.BM - 1) / p.BM) * p.tiles_n;
     int s = 1;
-    // split long K until about 512 workgroups run, keeping >= 8 k tiles each
-    while (p.tiles * s < 512 && kt >= 16 * s && s < 64) s *= 2;  // next split keeps >= 8 k tiles
+    // split long K until two workgroups per CU run, keeping >= 4 k tiles each:
+    // one 128 x 128 workgroup per CU leaves the matrix cores idle while its
+    // tile is split and stored (1024 x 4096 by 1024, one whole product 92 us;
+    // two splits 62 and their sum 13; 64 x 128 tiles unsplit 76)
+    while (p.tiles * s < 512 && kt >= 8 * s && s < 64) s *= 2;
     const int per = std::max(1, (kt + s - 1) / s);
     p.kchunk = per * GBK;
     p.splits = (kt + per - 1) / per;
@@ -451,8 +564,7 @@ void gemm_launch(const GemmArgs& a, dim3 grid, bool vec, hipStream_t s) {
 }
 template <int BM, int BN, bool GRP>
 void gemm_launch(bool ta, bool tb, const GemmArgs& a, dim3 grid, bool vec, hipStream_t s) {
-  if (ta && tb) gemm_launch<BM, BN, true, true, GRP>(a, grid, vec, s);
-  else if (ta) gemm_launch<BM, BN, true, false, GRP>(a, grid, vec, s);
+  if (ta) gemm_launch<BM, BN, true, false, GRP>(a, grid, vec, s);
   else if (tb) gemm_launch<BM, BN, false, true, GRP>(a, grid, vec, s);
   else gemm_launch<BM, BN, false, false, GRP>(a, grid, vec, s);
 }
@@ -494,7 +606,9 @@ hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float* A, int lda, 
     a.Bg2 = grp->Bg[2];
     for (int i = 0; i < 3; ++i) bal = bal && ((uintptr_t)grp->Bg[i] & 15) == 0;
   }
-  const bool vec = lda % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)A & 15) == 0 && bal;
+  // (16-byte vectors along m or n must not pass the last one)
+  const bool vec = lda % 4 == 0 && ldb % 4 == 0 && ((uintptr_t)A & 15) == 0 && bal && (!ta || M % 4 == 0) &&
+                   (tb || N % 4 == 0);
   const dim3 grid(p.tiles, p.splits);
   const bool grouped = a.gN > 0 || a.gK > 0 || epi.layout != 0;
   // (128-row tiles only come with 128-column ones: they need 256 tiles)
@@ -510,8 +624,14 @@ hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float* A, int lda, 
   }
   if (p.splits > 1) {
     const size_t MN = (size_t)M * N;
-    hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, s, part, p.splits, M, N, C,
-                       ldc, epi);
+    // (few elements: one per thread, or too few threads are in flight: at 64 x
+    // 1024 and 16 splits 3.9 us against 4.7; at 1024 x 1024 and 4, 12.5 against 7.7)
+    if (N % 4 == 0 && MN >= (1u << 19))
+      hipLaunchKernelGGL((gemm_reduce_kernel<4>), dim3((unsigned)((MN / 4 + 255) / 256)), dim3(256), 0, s, part, p.splits, M,
+                         N, C, ldc, epi);
+    else
+      hipLaunchKernelGGL((gemm_reduce_kernel<1>), dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, s, part, p.splits, M, N,
+                         C, ldc, epi);
   }
   return hipGetLastError();
 }
