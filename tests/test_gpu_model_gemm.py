@@ -3,8 +3,8 @@ matrix cores) at the edges of their tiles, against the fp64 oracle.
 
 Row counts around the 64- and 128-row tiles, an alphabet just past a 128-column
 tile with 16-byte loads (132) and without (131), reductions with a last k tile
-of 1 to 31 (row counts, in the weight gradients) and the 128-row plan with two
-rows in its last tile.
+of 1 to 31 (row counts, in the weight gradients) and the 128-row plan (at least
+512 tiles) with two rows in its last tile.
 
 Bar: a product of K terms rounds its sum every 16 terms, 2^-24 of the partial
 sum each time, and leaves out parts of terms below 2^-24 of them: 2e-6 of the
@@ -27,7 +27,7 @@ CASES = [
     ModelConfig("gemm65", L=65, D=128, s=1, vocab=132, B=1),
     ModelConfig("gemm129", L=129, D=192, s=1, vocab=128, B=1),
     ModelConfig("gemm127x2", L=127, D=64, s=1, vocab=4, B=2),
-    ModelConfig("gemm1154", L=577, D=512, s=1, vocab=129, B=2),
+    ModelConfig("gemm4098", L=2049, D=512, s=1, vocab=129, B=2),
 ]
 
 
