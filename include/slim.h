@@ -74,9 +74,9 @@ typedef enum { SLIM_QUERY = 0, SLIM_KEY = 1 } slim_role;
 typedef enum { SLIM_PHASE_FWD = 0, SLIM_PHASE_BWD = 1 } slim_phase;
 /* How the prefix sums inside a slice are evaluated (Sec. 3.2, Appendix B):
  *   SLIM_WITHIN_ITER       block-iteratively, the state carried from one
- *                          32-row tile to the next (the tiles of a slice never
- *                          leave the chip; the work per row does not depend
- *                          on C)
+ *                          32-row tile to the next (tiles run on across slices
+ *                          and never leave the chip; neither the work per row
+ *                          nor, without dropout, the result depends on C)
  *   SLIM_WITHIN_QUADRATIC  the slice as one masked quadratic form (eq. 2
  *                          inside the slice): the work per row grows with C.
  *                          The slices of a group run in parallel, groups one

@@ -148,7 +148,7 @@ constexpr int kTargetWorkgroupsForward = 512;
 constexpr int kMinTilesPerSegment = 4;
 
 int count_tiles(const slim_problem* p) {
-  return slim::TileMap((int)p->L, clamp_C(p), kTileRows).count_tiles();
+  return slim::TileMap((int)p->L, kTileRows).count_tiles();
 }
 
 // Segments per head.  The walk inside a segment is sequential; segments run
@@ -286,7 +286,7 @@ bool has_carry8(const slim_problem* p);
 // heads.
 int carry8_workgroups(const slim_problem* p, int P) {
   if (P < 2) return 0;
-  const int64_t chunks = p->B * p->H * (int64_t)slim::carry8_chunks_per_head((int)p->L, clamp_C(p), P);
+  const int64_t chunks = p->B * p->H * (int64_t)slim::carry8_chunks_per_head((int)p->L, P);
   int64_t n = std::min<int64_t>(kTargetWorkgroups, chunks);
   const char* env = getenv("SLIM_CARRY_WORKGROUPS");
   if (env != nullptr && atoi(env) >= 1) n = std::min<int64_t>(n, atoi(env));
@@ -1510,7 +1510,7 @@ int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V,
     ca.CS = plan_carry_split(p, P);
     ca.relu_eps = p->relu_eps;
     if (dp.carry8 != nullptr) {
-      ca.nch_head = slim::carry8_chunks_per_head(a.L, a.C, P);
+      ca.nch_head = slim::carry8_chunks_per_head(a.L, P);
       ca.NWG = carry8_workgroups(p, P);
       e = dp.carry8(ca, s);
     } else {

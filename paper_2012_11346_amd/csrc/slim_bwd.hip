@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256, 1) void bwd_walk_kernel(BwdArgs a) {
   // this wave's buffers start at zero: pad rows of Zk must read as zero
   for (size_t i = lane_id() * 16; i < Lay::WAVE; i += 64 * 16) *reinterpret_cast<uint4*>(wz + i) = uint4{0, 0, 0, 0};
 
-  const TileMap tm(a.L, a.C, TR);
+  const TileMap tm(a.L, TR);
   const int n_tiles = tm.count_tiles();
   const int j0 = (int)((int64_t)p * n_tiles / a.P), j1 = (int)((int64_t)(p + 1) * n_tiles / a.P);
   // exact states at the starts of the sub-segments inside this segment: the

@@ -244,7 +244,7 @@ __global__ __launch_bounds__(512, 1) void bwd_walk8_kernel(BwdArgs a) {
   for (size_t i = (size_t)threadIdx.x * 16; i < Lay::TOTAL; i += (size_t)NT * 16)
     *reinterpret_cast<uint4*>(arena + i) = uint4{0, 0, 0, 0};
 
-  const TileMap tm(a.L, a.C, TR);
+  const TileMap tm(a.L, TR);
   const int n_tiles = tm.count_tiles();
   const int j0 = (int)((int64_t)p * n_tiles / a.P), j1 = (int)((int64_t)(p + 1) * n_tiles / a.P);
   // exact states at the starts of the sub-segments inside this segment: the

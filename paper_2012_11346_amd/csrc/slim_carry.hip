@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void carry_kernel(CarryArgs a) {
     for (int et = 0; et < ET; ++et) dWacc[mt][et] = zero4();
 
   // rows of this part of segment p
-  const TileMap tm(a.L, a.C, TR);
+  const TileMap tm(a.L, TR);
   const int n_tiles = tm.count_tiles();
   const int s0 = (int)((int64_t)p * n_tiles / a.P), s1 = (int)((int64_t)(p + 1) * n_tiles / a.P);
   const int j0 = s0 + (s1 - s0) * part / a.CS, j1 = s0 + (s1 - s0) * (part + 1) / a.CS;

@@ -83,8 +83,8 @@ struct ChunkPos {
 
 }  // namespace
 
-int carry8_chunks_per_head(int L, int C, int P) {
-  const TileMap tm(L, C, 32);
+int carry8_chunks_per_head(int L, int P) {
+  const TileMap tm(L, 32);
   const int n_tiles = tm.count_tiles();
   int n = 0;
   for (int p = 0; p < P - 1; ++p) {
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(512, 1) void carry8_kernel(CarryArgs a) {
   const OR oR(L);
   const OK oK(L);
   const int BH = a.B * a.H;
-  const TileMap tm(a.L, a.C, 32);
+  const TileMap tm(a.L, 32);
   const int n_tiles = tm.count_tiles();
 
   // this workgroup's run of chunks [i0, i0 + n_run)

@@ -1,8 +1,8 @@
 // Forward sweep (Algorithm 1, one layer) and the stand-alone feature map.
 //
 // fwd_walk: one workgroup per (batch, head, segment) walks its tiles in
-// order.  Per tile of C_t <= TR rows (never straddling a slice), with the
-// state B = (S, z) of everything before the tile held in registers:
+// order.  Per tile of at most TR rows, with the state B = (S, z) of everything
+// before the tile held in registers:
 //   a1  logits of Q and K against W on the matrix cores, with -|x|^2/2 folded
 //       into the accumulator start; FAVOR+ features are exp2 of the shifted
 //       logits (one shift per query row, one running shift per head for keys;
@@ -12,9 +12,9 @@
 //   a3+a4  N^T = [V|1]^T A^T + [S|z]^T Q~^T, per wave over its features
 //   a5  cross-wave sum of N, then Y = N / D
 //   a6  [S|z] += K~^T [V|1]                       (eqs. 14-16, carried state)
-// For slices longer than TR rows the tiles of a slice are chained through
-// the same running state, which is the block-iterative evaluation of the
-// in-slice prefix sum (Appendix B) with block TR.
+// The tiles are chained through the running state whatever the slice length
+// (see TileMap): the block-iterative evaluation of the prefix sum (Appendix
+// B) with block TR, whose result does not depend on the slices.
 #include "slim_common.hpp"
 #include "slim_kernels.hpp"
 
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256, 2) void fwd_walk_kernel(FwdArgs a) {
   if constexpr (QSIDE)
     for (int i = FW * LDZ + lane_id(); i < ZR * LDZ; i += 64) Zk[w][i] = cvt<T>(0.f);
 
-  const TileMap tm(a.L, a.C, TR);
+  const TileMap tm(a.L, TR);
   const int n_tiles = tm.count_tiles();
   const int j0 = (int)((int64_t)p * n_tiles / a.P), j1 = (int)((int64_t)(p + 1) * n_tiles / a.P);
   const float half_log2M = 0.5f * __log2f((float)M);

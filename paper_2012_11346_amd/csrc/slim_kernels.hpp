@@ -254,7 +254,7 @@ hipError_t launch_carry(const CarryArgs& a, hipStream_t s);
 // workgroup; bf16 problems with 32 or 64 features per 4-wave slice
 template <class G>
 hipError_t launch_carry8(const CarryArgs& a, hipStream_t s);
-int carry8_chunks_per_head(int L, int C, int P);
+int carry8_chunks_per_head(int L, int P);
 // dW = sum of the n_parts partials [n_parts][n], in a fixed order
 hipError_t launch_dw_reduce(const float* part, int n_parts, int n, float* dW, hipStream_t s);
 

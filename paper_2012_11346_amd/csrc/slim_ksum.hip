@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256, 2) void ksum_kernel(KsumArgs a) {
   }
 
   // rows of this part
-  const TileMap tm(a.L, a.C, 32);
+  const TileMap tm(a.L, 32);
   const int tb = a.tile_end > a.tile_begin ? a.tile_begin : 0;
   const int n_tiles = (a.tile_end > a.tile_begin ? a.tile_end : tm.count_tiles()) - tb;
   int j0, j1;
