@@ -72,7 +72,7 @@ __device__ __forceinline__ float gelu_d(float x) {
 // products cover each other's splits and barriers (what bounds it: the six
 // products take a quarter of the time, the splits, the LDS reads and the
 // barriers the rest).  1024 x 4096 by 1024: 93 us on the float32 matrix
-// cores with the sum of its two splits, 77 here, unsplit.  Global loads are 16-byte vectors
+// cores, 78 here, each with the sum of its two splits.  Global loads are 16-byte vectors
 // where the strides allow.  Long K is split over blockIdx.y; the partial
 // products are summed in a fixed order by gemm_reduce_kernel, which then
 // applies the epilogue (no atomics: results are reproducible).
@@ -528,13 +528,18 @@ inline GemmPlan gemm_plan(int M, int N, int K) {
   const int t128 = ((M + 127) / 128) * ((N + GBN - 1) / GBN);
   auto plan = [&](int BN) {
     GemmPlan p;
-    // 128-row tiles only where they give two workgroups per CU unsplit: one
-    // leaves the matrix cores idle while its tile is split and stored (1024 x
-    // 4096 by 1024 in 128-row tiles 92 us, and 75 in two splits with their
-    // sum, at twice the workspace; in 64-row tiles 77).  (A short reduction
-    // leaves the epilogue's reads and writes of C to set the pace: the smaller
-    // tile gives twice the workgroups in flight.)
-    p.BM = (t128 >= 512 && kt > 4) ? 128 : 64;
+    // 128-row tiles do a third more per cycle, but one workgroup per CU leaves
+    // the matrix cores idle while its tile is split and stored: they are taken
+    // where they give two, unsplit or in splits of at least 16 k tiles, which
+    // pay for their sum (1024 x 4096 by 1024: 128 rows in two splits 60 us and
+    // 18 for the sum, unsplit 92, 64 rows 85; 1024 x 1024 by 4096: 128 rows in
+    // eight splits 53 + 8, 64 rows in four 72 + 6; 1024 x 3072 by 1024, splits
+    // of eight: 57 + 13, 64 rows 54 + 11).  (A short reduction leaves the
+    // epilogue's reads and writes of C to set the pace: the smaller tile gives
+    // twice the workgroups in flight.)
+    int s128 = 1;
+    while (t128 * s128 < 512 && s128 < 64) s128 *= 2;
+    p.BM = t128 * s128 >= 512 && (s128 > 1 ? kt >= 16 * s128 : kt > 4) ? 128 : 64;
     p.BN = BN;
     p.tiles_n = (N + BN - 1) / BN;
     p.tiles = ((M + p.BM - 1) / p.BM) * p.tiles_n;
@@ -549,7 +554,7 @@ inline GemmPlan gemm_plan(int M, int N, int K) {
   const GemmPlan p = plan(GBN);
   // fewer workgroups than the split aims for (a short row count, or a
   // reduction too short to split further): 64-column tiles double them
-  // (64-row tiles; 128-row ones only come with at least 512 tiles)
+  // (64-row tiles; 128-row ones only come with at least 512)
   if (p.BM == 64 && p.tiles * p.splits < 512) return plan(64);
   return p;
 }
@@ -612,7 +617,7 @@ hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float* A, int lda, 
                    (tb || N % 4 == 0);
   const dim3 grid(p.tiles, p.splits);
   const bool grouped = a.gN > 0 || a.gK > 0 || epi.layout != 0;
-  // (128-row tiles only come with 128-column ones: they need 512 tiles)
+  // (128-row tiles only come with 128-column ones)
   if (p.BM == 128) {
     if (grouped) gemm_launch<128, 128, true>(ta, tb, a, grid, vec, s);
     else gemm_launch<128, 128, false>(ta, tb, a, grid, vec, s);
