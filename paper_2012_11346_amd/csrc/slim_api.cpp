@@ -1259,6 +1259,36 @@ int scratch_address(void** out) {
 
 }  // namespace
 
+namespace slim {
+
+// one run of tiles per workgroup, two workgroups per compute unit
+int sum_parts(const slim_problem* p, size_t state_bytes, size_t bytes) {
+  const int64_t want = std::min<int64_t>(count_tiles(p), kTargetWorkgroupsForward / (p->B * p->H));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)(bytes / state_bytes)));
+}
+int part_sums(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W, float* out, int parts,
+              hipStream_t s) {
+  FwdArgs a;
+  std::memset(&a, 0, sizeof(a));
+  set_drop(a, drop_plan(p));
+  a.Q = Q;
+  a.K = K;
+  a.V = V;
+  a.W = W;
+  a.B = (int)p->B;
+  a.H = (int)p->H;
+  a.L = (int)p->L;
+  a.C = clamp_C(p);
+  a.P = parts;
+  a.relu_eps = p->relu_eps;
+  a.seg_out = out;
+  const hipError_t e = dispatch(p).fwd(a, kWalkSums, s);
+  if (e != hipSuccess) return hip_fail(e, "part-sum launch");
+  return ok();
+}
+
+}  // namespace slim
+
 extern "C" {
 
 int slim_fwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/slim.h"
+
 namespace slim {
 
 // Sets the calling thread's slim_last_error() text (cleared for SLIM_OK)
@@ -255,6 +257,12 @@ hipError_t launch_carry(const CarryArgs& a, hipStream_t s);
 template <class G>
 hipError_t launch_carry8(const CarryArgs& a, hipStream_t s);
 int carry8_chunks_per_head(int L, int P);
+// What the rows add to the state (eqs. 14-16 summed; square map, float32), as
+// the sums of `parts` runs of tiles: out [B H][parts][M (d + 1)].  sum_parts:
+// how many to take, at most what `bytes` hold at state_bytes for each.
+int sum_parts(const slim_problem* p, size_t state_bytes, size_t bytes);
+int part_sums(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W, float* out, int parts,
+              hipStream_t s);
 // dW = sum of the n_parts partials [n_parts][n], in a fixed order
 hipError_t launch_dw_reduce(const float* part, int n_parts, int n, float* dW, hipStream_t s);
 

@@ -17,7 +17,7 @@
 // a fixed-order reduction, epilogues for
 // bias, bias + GeLU, GeLU's derivative and residual sums), row-wise layer
 // normalisation and its backward, cross-entropy, the embedding and its
-// deterministic backward, head split/merge copies and fixed-order column
+// deterministic backward, copies between heads and rows and fixed-order column
 // sums.
 #include <hip/hip_runtime.h>
 
@@ -25,6 +25,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/slim.h"
@@ -705,23 +708,46 @@ __global__ __launch_bounds__(256) void embed_kernel(const int* tokens, int64_t L
   }
 }
 
-// out[i] = LN(x[i]) * g + b + res[i] (res may be null); stats[i] = (mean, rstd)
+// offset of element (row i, column j) in the per-head layout [B, k, n, 64]
+__device__ __forceinline__ size_t head_at(int i, int j, int k, int n) {
+  const int b = i / n, t = i - b * n;
+  return (((size_t)b * k + (j >> 6)) * n + t) * 64 + (j & 63);
+}
+
+// out[i] = LN(x[i]) * g + b + res[i]; stats[i] = (mean, rstd).  HEADS: x is
+// per head, [B, k, n, 64], and its rows are written to xr on the way.  A
+// thread keeps its NV values of the row (D <= 256 NV) from the first pass on.
+// Bound by latency and launches: 64 rows of 1024, read three times, took 5.5 us
+// and a copy to rows before it 4.4; in one launch 4.3.
+template <int NV, bool HEADS>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* x, const float* g, const float* b, const float* res,
-                                                     float* out, float* stats, int D, float eps) {
+                                                     float* out, float* stats, int D, float eps, float* xr, int k, int n) {
   __shared__ float red[4];
   const size_t row = (size_t)blockIdx.x * D;
+  float v[NV];
   float s = 0.f;
-  for (int j = threadIdx.x; j < D; j += 256) s += x[row + j];
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int j = threadIdx.x + 256 * u;
+    v[u] = j < D ? x[HEADS ? head_at(blockIdx.x, j, k, n) : row + j] : 0.f;
+  }
+#pragma unroll
+  for (int u = 0; u < NV; ++u) s += v[u];
   const float mu = block_sum(s, red) / (float)D;
   float q = 0.f;
-  for (int j = threadIdx.x; j < D; j += 256) {
-    const float c = x[row + j] - mu;
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const float c = (int)threadIdx.x + 256 * u < D ? v[u] - mu : 0.f;
     q += c * c;
   }
   const float rstd = 1.f / sqrtf(block_sum(q, red) / (float)D + eps);
-  for (int j = threadIdx.x; j < D; j += 256) {
-    const float y = (x[row + j] - mu) * rstd * g[j] + b[j];
-    out[row + j] = res ? y + res[row + j] : y;
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int j = threadIdx.x + 256 * u;
+    if (j < D) {
+      if (HEADS) xr[row + j] = v[u];
+      out[row + j] = (v[u] - mu) * rstd * g[j] + b[j] + res[row + j];
+    }
   }
   if (threadIdx.x == 0) {
     stats[2 * blockIdx.x] = mu;
@@ -729,27 +755,38 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* x, const float
   }
 }
 
-// dx[i] = rstd / D (D dxh - sum dxh - xhat sum(dxh xhat)) + add[i], dxh = dy g;
-// P[i] = dy xhat (for the gain's gradient)
+// dx[i] = rstd / D (D dxh - sum dxh - xhat sum(dxh xhat)), dxh = dy g (HEADS:
+// stored per head, [B, k, n, 64]); P[i] = dy xhat (for the gain's gradient)
+template <int NV, bool HEADS>
 __global__ __launch_bounds__(256) void ln_bwd_kernel(const float* x, const float* stats, const float* g, const float* dy,
-                                                     const float* add, float* dx, float* P, int D) {
+                                                     float* dx, float* P, int D, int k, int n) {
   __shared__ float red[4];
   const size_t row = (size_t)blockIdx.x * D;
   const float mu = stats[2 * blockIdx.x], rstd = stats[2 * blockIdx.x + 1];
+  float xh[NV], d[NV], y[NV];
   float s1 = 0.f, s2 = 0.f;
-  for (int j = threadIdx.x; j < D; j += 256) {
-    const float xh = (x[row + j] - mu) * rstd, d = dy[row + j] * g[j];
-    s1 += d;
-    s2 += d * xh;
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int j = threadIdx.x + 256 * u;
+    const bool in = j < D;
+    xh[u] = in ? (x[row + j] - mu) * rstd : 0.f;
+    y[u] = in ? dy[row + j] : 0.f;
+    d[u] = in ? y[u] * g[j] : 0.f;
+  }
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    s1 += d[u];
+    s2 += d[u] * xh[u];
   }
   s1 = block_sum(s1, red);
   s2 = block_sum(s2, red);
-  for (int j = threadIdx.x; j < D; j += 256) {
-    const float xh = (x[row + j] - mu) * rstd, d = dy[row + j] * g[j];
-    float v = rstd / (float)D * ((float)D * d - s1 - xh * s2);
-    if (add) v += add[row + j];
-    dx[row + j] = v;
-    P[row + j] = dy[row + j] * xh;
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    const int j = threadIdx.x + 256 * u;
+    if (j < D) {
+      dx[HEADS ? head_at(blockIdx.x, j, k, n) : row + j] = rstd / (float)D * ((float)D * d[u] - s1 - xh[u] * s2);
+      P[row + j] = y[u] * xh[u];
+    }
   }
 }
 
@@ -759,11 +796,11 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const float* x, const float
 // are added in wave order through LDS.  One stage when the rows fit one
 // chunk of 64 (out_z[j] += the sum); else part[z][c][j] = the sum of chunk c
 // and a second stage adds the chunks the same way (wave q: chunks q, q + 4,
-// ...).  z selects one of two independent sums.
+// ...).  z selects one of up to three independent sums.
 constexpr int kColChunk = 64;
 struct ColsumArgs {
-  const float* src[2];
-  float* out[2];
+  const float* src[3];
+  float* out[3];
 };
 // sum of rows r0, r0 + 4, r0 + 8, ... < r1 of column j (stride n), in order
 __device__ __forceinline__ float colsum_strided(const float* src, int r0, int r1, size_t n, int j) {
@@ -806,10 +843,6 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(ColsumArgs a, int chu
   if (q == 0 && j < n) a.out[z][j] += t;
 }
 
-__global__ __launch_bounds__(256) void copy_kernel(float* dst, const float* src, size_t total) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e < total) dst[e] = src[e];
-}
 __global__ __launch_bounds__(256) void identity_kernel(float* I, int n) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e < n * n) I[e] = (e / n == e % n) ? 1.f : 0.f;
@@ -818,10 +851,27 @@ __global__ __launch_bounds__(256) void fill_kernel(float* dst, float v, size_t t
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (e < total) dst[e] = v;
 }
-// out = a - b
-__global__ __launch_bounds__(256) void sub_kernel(float* out, const float* a, const float* b, size_t total) {
+// out = a - (the sum of the parts [heads][P][per], in order), per element:
+// the state before a slice (eq. 17).  The rows' sums come from a pass over
+// keys and values alone (16 heads of 64 rows: 5.4 us; the whole forward, whose
+// outputs were not needed, 15.2).
+__global__ __launch_bounds__(256) void sub_parts_kernel(float* out, const float* a, const float* parts, int P, size_t per,
+                                                        size_t total) {
   const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e < total) out[e] = a[e] - b[e];
+  if (e >= total) return;
+  const size_t head = e / per;
+  const float* q = parts + (head * P) * per + (e - head * per);
+  float d = 0.f;
+  int i = 0;
+  for (; i + 8 <= P; i += 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = q[(size_t)(i + k) * per];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d += v[k];
+  }
+  for (; i < P; ++i) d += q[(size_t)i * per];
+  out[e] = a[e] - d;
 }
 
 // Cross-entropy of row i = (b, t) against the next token (eq. 10): weight
@@ -861,20 +911,7 @@ __global__ __launch_bounds__(256) void sum_kernel(const float* v, int n, float* 
   if (threadIdx.x == 0) out[0] = accumulate ? out[0] + s : s;
 }
 
-// heads [B, k, n, 64] <-> rows [B n, ld] at column offset col0 (head h at
-// columns col0 + 64 h)
-__global__ __launch_bounds__(256) void rows_to_heads_kernel(const float* src, int ld, int col0, float* dst, int k, int n,
-                                                            size_t total) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= total) return;
-  const int c = (int)(e % kHead);
-  size_t r = e / kHead;
-  const int t = (int)(r % n);
-  r /= n;
-  const int h = (int)(r % k);
-  const int b = (int)(r / k);
-  dst[e] = src[((size_t)b * n + t) * ld + col0 + h * kHead + c];
-}
+// heads [B, k, n, 64] to rows [B n, ld] (head h at columns col0 + 64 h):
 // parts consecutive head tensors of `per` floats each: part p goes to the
 // columns from col0 + p colstep
 __global__ __launch_bounds__(256) void heads_to_rows_kernel(const float* src, float* dst, int ld, int col0, int colstep,
@@ -957,9 +994,9 @@ slim_problem att_problem(const Dims& m, int n) {
 
 // workspace regions (byte offsets)
 struct Layout {
-  size_t ident, attws, attws_bytes, states, gstates, bprev, delta, snew, wd;
+  size_t ident, attws, attws_bytes, states, gstates, bprev, snew, wd;
   size_t X, Qh, Yh, A, st1, H, Z1, G1, Fo, st2;
-  size_t logits, rowloss, dX, dH, dF, dG1, dA, dYh, dQh, dQKV, P, part, part_bytes, red;
+  size_t logits, rowloss, dX, dH, dF, dG1, dYh, dQh, dQKV, P, part, part_bytes, red;
   size_t total;
 };
 
@@ -980,12 +1017,11 @@ Layout layout(const Dims& m) {
     const slim_problem p = att_problem(m, n);
     aw = std::max(aw, std::max(slim_workspace_bytes(&p, SLIM_PHASE_FWD), slim_workspace_bytes(&p, SLIM_PHASE_BWD)));
   }
-  l.attws_bytes = std::max<size_t>(aw, 256);
+  l.attws_bytes = std::max<size_t>(aw, S * 4);  // (it also holds part sums: at least one state)
   take(l.attws, l.attws_bytes);
   take(l.states, s * S * 4);
   take(l.gstates, 2 * s * S * 4);
   take(l.bprev, s * S * 4);
-  take(l.delta, S * 4);
   take(l.snew, S * 4);
   take(l.wd, kHead * kHead * 4);
   take(l.X, (s + 1) * R * D * 4);
@@ -1004,7 +1040,6 @@ Layout layout(const Dims& m) {
   take(l.dH, R * D * 4);
   take(l.dF, R * D * 4);
   take(l.dG1, R * F * 4);
-  take(l.dA, R * D * 4);
   take(l.dYh, HF * 4);
   take(l.dQh, 3 * HF * 4);
   take(l.dQKV, R * 3 * D * 4);
@@ -1020,7 +1055,7 @@ Layout layout(const Dims& m) {
   }
   l.part_bytes = pb;
   take(l.part, std::max<size_t>(pb, 256));
-  take(l.red, 2 * ((R + kColChunk - 1) / kColChunk) * std::max(D, std::max(F, (size_t)m.V)) * 4);
+  take(l.red, 3 * ((R + kColChunk - 1) / kColChunk) * std::max(D, std::max(F, (size_t)m.V)) * 4);
   l.total = off;
   return l;
 }
@@ -1099,7 +1134,6 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
   float* states = (float*)(w + lay.states);
   float* gst = (float*)(w + lay.gstates);
   float* bprev = (float*)(w + lay.bprev);
-  float* delta = (float*)(w + lay.delta);
   float* snew = (float*)(w + lay.snew);
   float* wd = (float*)(w + lay.wd);
   auto f = [&](size_t off) { return (float*)(w + off); };
@@ -1116,7 +1150,7 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
   float* Yh = f(lay.Yh);
   float* logits = f(lay.logits);
   float* rowloss = f(lay.rowloss);
-  float *dX = f(lay.dX), *dH = f(lay.dH), *dF = f(lay.dF), *dG1 = f(lay.dG1), *dA = f(lay.dA);
+  float *dX = f(lay.dX), *dH = f(lay.dH), *dF = f(lay.dF), *dG1 = f(lay.dG1);
   float *dYh = f(lay.dYh), *dQh = f(lay.dQh), *dQKV = f(lay.dQKV), *Pp = f(lay.P);
   float* part = f(lay.part);
   float* red = f(lay.red);
@@ -1135,18 +1169,30 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
     gb.gK = along_k ? D : 0;
     return gb;
   };
-  // out0 += column sums of src0 (and out1 += those of src1), rows in order
-  auto colsum = [&](int rows, int n, const float* src0, float* out0, const float* src1 = nullptr,
-                    float* out1 = nullptr) {
-    ColsumArgs ca;
-    ca.src[0] = src0;
-    ca.out[0] = out0;
-    ca.src[1] = src1;
-    ca.out[1] = out1;
-    const int nz = src1 ? 2 : 1, chunks = (rows + kColChunk - 1) / kColChunk;
+  // out += column sums of src for up to three pairs, rows in order
+  auto colsum = [&](int rows, int n, std::initializer_list<std::pair<const float*, float*>> sums) {
+    ColsumArgs ca = {};
+    int nz = 0;
+    for (const auto& x : sums) {
+      ca.src[nz] = x.first;
+      ca.out[nz++] = x.second;
+    }
+    const int chunks = (rows + kColChunk - 1) / kColChunk;
     hipLaunchKernelGGL(colsum_part_kernel, dim3((n + 63) / 64, chunks, nz), dim3(256), 0, s, ca, rows, n, red);
     if (chunks > 1)
       hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 63) / 64, nz), dim3(256), 0, s, ca, chunks, n, red);
+  };
+  auto ln_fwd = [&](auto heads, int rows, int n, const float* x, const float* g, const float* b, const float* res, float* out,
+                    float* stats, float* xr) {
+    constexpr bool HEADS = decltype(heads)::value;
+    if (D <= 1024) hipLaunchKernelGGL((ln_fwd_kernel<4, HEADS>), dim3(rows), dim3(256), 0, s, x, g, b, res, out, stats, D, m.eps, xr, k, n);
+    else hipLaunchKernelGGL((ln_fwd_kernel<16, HEADS>), dim3(rows), dim3(256), 0, s, x, g, b, res, out, stats, D, m.eps, xr, k, n);
+  };
+  auto ln_bwd = [&](auto heads, int rows, int n, const float* x, const float* stats, const float* g, const float* dy, float* dx,
+                    float* P_) {
+    constexpr bool HEADS = decltype(heads)::value;
+    if (D <= 1024) hipLaunchKernelGGL((ln_bwd_kernel<4, HEADS>), dim3(rows), dim3(256), 0, s, x, stats, g, dy, dx, P_, D, k, n);
+    else hipLaunchKernelGGL((ln_bwd_kernel<16, HEADS>), dim3(rows), dim3(256), 0, s, x, stats, g, dy, dx, P_, D, k, n);
   };
 
   // identity W of the square map: g(x) = (x_i^2)
@@ -1166,18 +1212,14 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
   // the rest of layer r (eqs. 5-9) from the state before the slice
   auto layer_fwd = [&](int r, int a, int n, const float* state_in, float* state_out) -> int {
     const int rows = (int)(m.B * n);
-    const size_t hf = (size_t)m.B * k * n * kHead;
     const float* X = Xr(r);
     const slim_problem p = att_problem(m, n);
     CHECK_SLIM(slim_fwd(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, state_in, nullptr, Yh, nullptr, state_out, nullptr,
                         nullptr, attws, lay.attws_bytes, s));
-    hipLaunchKernelGGL(heads_to_rows_kernel, grid1(hf), dim3(256), 0, s, Yh, Ar(r), D, 0, 0, k, n, hf, hf);
-    hipLaunchKernelGGL(ln_fwd_kernel, dim3(rows), dim3(256), 0, s, Ar(r), P.l[r].g1, P.l[r].b1n, X, Hr(r), s1r(r), D,
-                       m.eps);
+    ln_fwd(std::true_type(), rows, n, Yh, P.l[r].g1, P.l[r].b1n, X, Hr(r), s1r(r), Ar(r));
     CHECK_HIP(mm(false, false, rows, F, D, Hr(r), D, P.l[r].W1, F, Z1r(r), F, epi(EPI_BIAS_GELU, P.l[r].b1, nullptr, G1r(r))));
     CHECK_HIP(mm(false, false, rows, D, F, G1r(r), F, P.l[r].W2, D, For(r), D, epi(EPI_BIAS, P.l[r].b2)));
-    hipLaunchKernelGGL(ln_fwd_kernel, dim3(rows), dim3(256), 0, s, For(r), P.l[r].g2, P.l[r].b2n, Hr(r), Xr(r + 1),
-                       s2r(r), D, m.eps);
+    ln_fwd(std::false_type(), rows, n, For(r), P.l[r].g2, P.l[r].b2n, Hr(r), Xr(r + 1), s2r(r), nullptr);
     CHECK_HIP(hipGetLastError());
     return SLIM_OK;
   };
@@ -1198,9 +1240,9 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
     hipLaunchKernelGGL(embed_kernel, dim3((unsigned)(m.B * n)), dim3(256), 0, s, tokens, m.L, a, n, P.emb, D, V, Xr(0));
     for (int r = 0; r < m.s; ++r) {
       CHECK_SLIM(layer_qkv(r, n));
-      CHECK_SLIM(layer_fwd(r, a, n, states + r * S, snew));
-      hipLaunchKernelGGL(copy_kernel, grid1(S), dim3(256), 0, s, states + r * S, snew, S);
+      CHECK_SLIM(layer_fwd(r, a, n, states + r * S, bprev + r * S));
     }
+    std::swap(states, bprev);
     CHECK_SLIM(head_logits(a, n));
     hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, s, rowloss, (int)(m.B * n), loss, 1);
     CHECK_HIP(hipGetLastError());
@@ -1230,38 +1272,41 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
     hipLaunchKernelGGL(embed_kernel, dim3((unsigned)rows), dim3(256), 0, s, tokens, m.L, a, n, P.emb, D, V, Xr(0));
     for (int r = 0; r < m.s; ++r) {
       CHECK_SLIM(layer_qkv(r, n));
-      CHECK_SLIM(slim_fwd(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, nullptr, nullptr, Yh, nullptr, delta, nullptr,
-                          nullptr, attws, lay.attws_bytes, s));
-      hipLaunchKernelGGL(sub_kernel, grid1(S), dim3(256), 0, s, bprev + r * S, states + r * S, delta, S);
+      if (q == 0) {  // before the first slice: exactly nothing
+        hipLaunchKernelGGL(fill_kernel, grid1(S), dim3(256), 0, s, bprev + r * S, 0.f, S);
+      } else {
+        const int parts = slim::sum_parts(&p, S * sizeof(float), lay.attws_bytes);
+        CHECK_SLIM(slim::part_sums(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, (float*)attws, parts, s));
+        hipLaunchKernelGGL(sub_parts_kernel, grid1(S), dim3(256), 0, s, bprev + r * S, states + r * S, (const float*)attws,
+                           parts, S / ((size_t)m.B * k), S);
+      }
       CHECK_HIP(hipGetLastError());
       CHECK_SLIM(layer_fwd(r, a, n, bprev + r * S, snew));
     }
     CHECK_SLIM(head_logits(a, n));
     // output layer
     CHECK_HIP(mm(true, false, D, V, rows, Xr(m.s), D, logits, V, G.Wout, V, epi(EPI_ACC)));
-    colsum(rows, V, logits, G.bout);
+    colsum(rows, V, {{logits, G.bout}});
     CHECK_HIP(mm(false, true, rows, D, V, logits, V, P.Wout, V, dX, D, epi(EPI_STORE)));
     for (int r = m.s - 1; r >= 0; --r) {
       const Params::Layer& pl = P.l[r];
       const Grads::Layer& gl = G.l[r];
       // X_{r+1} = LN2(Fo) + H
-      hipLaunchKernelGGL(ln_bwd_kernel, dim3(rows), dim3(256), 0, s, For(r), s2r(r), pl.g2, dX, nullptr, dF, Pp, D);
-      colsum(rows, D, Pp, gl.g2, dX, gl.b2n);
+      ln_bwd(std::false_type(), rows, n, For(r), s2r(r), pl.g2, dX, dF, Pp);
+      colsum(rows, D, {{Pp, gl.g2}, {dX, gl.b2n}, {dF, gl.b2}});  // (b2: Fo = GeLU(Z1) W2 + b2)
       // Fo = GeLU(Z1) W2 + b2
       CHECK_HIP(mm(true, false, F, D, rows, G1r(r), F, dF, D, gl.W2, D, epi(EPI_ACC)));
-      colsum(rows, D, dF, gl.b2);
       CHECK_HIP(mm(false, true, rows, F, D, dF, D, pl.W2, D, dG1, F, epi(EPI_GELU_BWD, nullptr, Z1r(r))));
       // Z1 = H W1 + b1; dH = dX (residual) + dZ1 W1^T
       CHECK_HIP(mm(true, false, D, F, rows, Hr(r), D, dG1, F, gl.W1, F, epi(EPI_ACC)));
-      colsum(rows, F, dG1, gl.b1);
+      colsum(rows, F, {{dG1, gl.b1}});
       CHECK_HIP(mm(false, true, rows, D, F, dG1, F, pl.W1, F, dH, D, epi(EPI_ADD, nullptr, dX)));
       // H = LN1(A) + X
-      hipLaunchKernelGGL(ln_bwd_kernel, dim3(rows), dim3(256), 0, s, Ar(r), s1r(r), pl.g1, dH, nullptr, dA, Pp, D);
-      colsum(rows, D, Pp, gl.g1, dH, gl.b1n);
+      ln_bwd(std::true_type(), rows, n, Ar(r), s1r(r), pl.g1, dH, dYh, Pp);
+      colsum(rows, D, {{Pp, gl.g1}, {dH, gl.b1n}});
       CHECK_HIP(hipGetLastError());
       // attention: the slice's gradient with the state cotangent after it
       // (eq. 18 gives the one before it)
-      hipLaunchKernelGGL(rows_to_heads_kernel, grid1(hf), dim3(256), 0, s, dA, D, 0, dYh, k, n, hf);
       float* gin = gst + ((size_t)gcur * m.s + r) * S;
       float* gout = gst + ((size_t)(1 - gcur) * m.s + r) * S;
       CHECK_SLIM(slim_bwd(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, bprev + r * S, nullptr, nullptr, dYh, nullptr,
@@ -1277,7 +1322,7 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
     }
     hipLaunchKernelGGL(embed_bwd_kernel, dim3(V, (D + 255) / 256), dim3(256), 0, s, tokens, m.L, a, n, rows, dX, D, G.emb);
     // the states before this slice become the states after the earlier one
-    hipLaunchKernelGGL(copy_kernel, grid1(m.s * S), dim3(256), 0, s, states, bprev, (size_t)m.s * S);
+    std::swap(states, bprev);
     CHECK_HIP(hipGetLastError());
     gcur = 1 - gcur;
   }
