@@ -30,7 +30,8 @@
  * the workspace: the activations of one slice plus the states, so it grows
  * with C and not with L.
  *
- * Everything is float32.  Matrix products run on the float32 matrix cores
+ * Everything is float32.  Matrix products run on the matrix cores, each value
+ * as the exact sum of three bf16 ones (infinities come out as NaN),
  * in the library's own kernels (long reductions split over workgroups and
  * summed in a fixed order); every call is asynchronous on `stream`; the
  * library allocates nothing; results are deterministic (fixed summation

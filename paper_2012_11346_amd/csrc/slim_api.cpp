@@ -1319,14 +1319,19 @@ int slim_fwd_noalloc(const slim_problem* p, const void* Q, const void* K, const 
                   need, stream);
 }
 
-int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
+}  // extern "C"
+
+namespace {
+
+// slim_bwd; without want_dw the tile walk's dW partials are left unsummed (dW is not read)
+int bwd_impl(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
              const float* state_in, const float* kshift_in, const float* kshift, const void* dY, const void* Y,
              const float* logD, const float* dstate_out, void* dQ, void* dK, void* dV, float* dW, float* dstate_in,
-             const float* ctx, void* ws, size_t ws_bytes, void* stream) {
+             const float* ctx, void* ws, size_t ws_bytes, void* stream, bool want_dw) {
   int st = check_problem(p);
   if (st != SLIM_OK) return st;
   if (Q == nullptr || K == nullptr || V == nullptr || W == nullptr || dY == nullptr || dQ == nullptr ||
-      dK == nullptr || dV == nullptr || dW == nullptr)
+      dK == nullptr || dV == nullptr || (want_dw && dW == nullptr))
     return fail(SLIM_EINVAL, "Q, K, V, W, dY, dQ, dK, dV and dW must be non-NULL");
   const bool favor = p->kind == SLIM_FAVOR_PLUS;
   if (favor) {
@@ -1551,9 +1556,29 @@ int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V,
   // (5) dW: the workgroups' partials summed in a fixed order (the walks'
   //     only, without the carry pass)
   const int slots = direct ? BH * P : (int)dw_slots(p, P);
+  if (!want_dw) return ok();
   e = slim::launch_dw_reduce(a.dW_part, slots, (int)(p->M * p->d), dW, s);
   if (e != hipSuccess) return hip_fail(e, "dW-reduction launch");
   return ok();
 }
 
-}  // extern "C"
+}  // namespace
+
+extern "C" int slim_bwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W,
+             const float* state_in, const float* kshift_in, const float* kshift, const void* dY, const void* Y,
+             const float* logD, const float* dstate_out, void* dQ, void* dK, void* dV, float* dW, float* dstate_in,
+             const float* ctx, void* ws, size_t ws_bytes, void* stream) {
+  return bwd_impl(p, Q, K, V, W, state_in, kshift_in, kshift, dY, Y, logD, dstate_out, dQ, dK, dV, dW, dstate_in, ctx, ws, ws_bytes,
+                  stream, true);
+}
+
+namespace slim {
+
+int attention_bwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W, const float* state_in,
+                  const void* dY, const float* dstate_out, void* dQ, void* dK, void* dV, float* dstate_in, void* ws,
+                  size_t ws_bytes, hipStream_t s) {
+  return bwd_impl(p, Q, K, V, W, state_in, nullptr, nullptr, dY, nullptr, nullptr, dstate_out, dQ, dK, dV, nullptr, dstate_in,
+                  nullptr, ws, ws_bytes, s, false);
+}
+
+}  // namespace slim

@@ -263,6 +263,10 @@ int carry8_chunks_per_head(int L, int P);
 int sum_parts(const slim_problem* p, size_t state_bytes, size_t bytes);
 int part_sums(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W, float* out, int parts,
               hipStream_t s);
+// slim_bwd of the tile walk without dW (the square map's W is fixed)
+int attention_bwd(const slim_problem* p, const void* Q, const void* K, const void* V, const float* W, const float* state_in,
+                  const void* dY, const float* dstate_out, void* dQ, void* dK, void* dV, float* dstate_in, void* ws,
+                  size_t ws_bytes, hipStream_t s);
 // dW = sum of the n_parts partials [n_parts][n], in a fixed order
 hipError_t launch_dw_reduce(const float* part, int n_parts, int n, float* dW, hipStream_t s);
 

@@ -579,13 +579,14 @@ void gemm_launch(bool ta, bool tb, const GemmArgs& a, dim3 grid, bool vec, hipSt
 }
 
 // part: workspace for the partial products (gemm_part_bytes of the shape);
+// sum: false leaves a split product's parts there, without the epilogue;
 // grp: grouped B (Bg, gN, gK of GemmArgs), or nullptr
 struct GroupB {
   const float* Bg[3];
   int gN, gK;
 };
 hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C,
-                int ldc, Epi epi, float* part, hipStream_t s, const GroupB* grp = nullptr) {
+                int ldc, Epi epi, float* part, hipStream_t s, const GroupB* grp = nullptr, bool sum = true) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const GemmPlan p = gemm_plan(M, N, K);
   GemmArgs a;
@@ -631,7 +632,7 @@ hipError_t gemm(bool ta, bool tb, int M, int N, int K, const float* A, int lda, 
     if (grouped) gemm_launch<64, 64, true>(ta, tb, a, grid, vec, s);
     else gemm_launch<64, 64, false>(ta, tb, a, grid, vec, s);
   }
-  if (p.splits > 1) {
+  if (p.splits > 1 && sum) {
     const size_t MN = (size_t)M * N;
     // (few elements: one per thread, or too few threads are in flight: at 64 x
     // 1024 and 16 splits 3.9 us against 4.7; at 1024 x 1024 and 4, 12.5 against 7.7)
@@ -714,22 +715,52 @@ __device__ __forceinline__ size_t head_at(int i, int j, int k, int n) {
   return (((size_t)b * k + (j >> 6)) * n + t) * 64 + (j & 63);
 }
 
-// out[i] = LN(x[i]) * g + b + res[i]; stats[i] = (mean, rstd).  HEADS: x is
-// per head, [B, k, n, 64], and its rows are written to xr on the way.  A
-// thread keeps its NV values of the row (D <= 256 NV) from the first pass on.
-// Bound by latency and launches: 64 rows of 1024, read three times, took 5.5 us
-// and a copy to rows before it 4.4; in one launch 4.3.
-template <int NV, bool HEADS>
+// out[i] = LN(x[i]) * g + b + res[i]; stats[i] = (mean, rstd).  Where x comes
+// from: LnRows, as it is; LnHeads, per head, [B, k, n, 64]; LnParts, the k
+// partial products of a split GEMM and its bias (gemm_reduce_kernel's sum, in
+// its order).  The last two write the rows to xr on the way.  A thread keeps
+// its NV values of the row (D <= 256 NV) from the first pass on.  Bound by
+// latency and launches: 64 rows of 1024, read three times, took 5.5 us and the
+// copy to rows before it 4.4; in one launch 4.3.
+enum LnSource { LnRows = 0, LnHeads = 1, LnParts = 2 };
+template <int NV, int SRC>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* x, const float* g, const float* b, const float* res,
-                                                     float* out, float* stats, int D, float eps, float* xr, int k, int n) {
+                                                     float* out, float* stats, int D, float eps, float* xr, int k, int n,
+                                                     const float* bias) {
   __shared__ float red[4];
   const size_t row = (size_t)blockIdx.x * D;
   float v[NV];
   float s = 0.f;
+  if constexpr (SRC == LnParts) {
+    // (PB parts of all the thread's values loaded at a time: with few rows the
+    // loads' latency sets the pace; past the row or the parts they repeat the
+    // last one and are not added)
+    constexpr int PB = 32 / NV;
+    const size_t MN = (size_t)gridDim.x * D;
 #pragma unroll
-  for (int u = 0; u < NV; ++u) {
-    const int j = threadIdx.x + 256 * u;
-    v[u] = j < D ? x[HEADS ? head_at(blockIdx.x, j, k, n) : row + j] : 0.f;
+    for (int u = 0; u < NV; ++u) v[u] = 0.f;
+    for (int i = 0; i < k; i += PB) {
+      float y[PB][NV];
+#pragma unroll
+      for (int t = 0; t < PB; ++t)
+#pragma unroll
+        for (int u = 0; u < NV; ++u) y[t][u] = x[(size_t)min(i + t, k - 1) * MN + row + min((int)threadIdx.x + 256 * u, D - 1)];
+#pragma unroll
+      for (int t = 0; t < PB; ++t)
+#pragma unroll
+        for (int u = 0; u < NV; ++u) v[u] = i + t < k ? v[u] + y[t][u] : v[u];
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int j = threadIdx.x + 256 * u;
+      v[u] = j < D ? v[u] + bias[j] : 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int j = threadIdx.x + 256 * u;
+      v[u] = j < D ? x[SRC == LnHeads ? head_at(blockIdx.x, j, k, n) : row + j] : 0.f;
+    }
   }
 #pragma unroll
   for (int u = 0; u < NV; ++u) s += v[u];
@@ -745,7 +776,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const float* x, const float
   for (int u = 0; u < NV; ++u) {
     const int j = threadIdx.x + 256 * u;
     if (j < D) {
-      if (HEADS) xr[row + j] = v[u];
+      if (SRC != LnRows) xr[row + j] = v[u];
       out[row + j] = (v[u] - mu) * rstd * g[j] + b[j] + res[row + j];
     }
   }
@@ -994,7 +1025,7 @@ slim_problem att_problem(const Dims& m, int n) {
 
 // workspace regions (byte offsets)
 struct Layout {
-  size_t ident, attws, attws_bytes, states, gstates, bprev, snew, wd;
+  size_t ident, attws, attws_bytes, states, gstates, bprev, snew;
   size_t X, Qh, Yh, A, st1, H, Z1, G1, Fo, st2;
   size_t logits, rowloss, dX, dH, dF, dG1, dYh, dQh, dQKV, P, part, part_bytes, red;
   size_t total;
@@ -1023,7 +1054,6 @@ Layout layout(const Dims& m) {
   take(l.gstates, 2 * s * S * 4);
   take(l.bprev, s * S * 4);
   take(l.snew, S * 4);
-  take(l.wd, kHead * kHead * 4);
   take(l.X, (s + 1) * R * D * 4);
   take(l.Qh, s * 3 * HF * 4);
   take(l.Yh, HF * 4);
@@ -1135,7 +1165,6 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
   float* gst = (float*)(w + lay.gstates);
   float* bprev = (float*)(w + lay.bprev);
   float* snew = (float*)(w + lay.snew);
-  float* wd = (float*)(w + lay.wd);
   auto f = [&](size_t off) { return (float*)(w + off); };
   const size_t R = m.rows_max(), HF = (size_t)m.B * k * m.nmax * kHead;
   auto Xr = [&](int r) { return f(lay.X) + (size_t)r * R * D; };
@@ -1182,11 +1211,11 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
     if (chunks > 1)
       hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 63) / 64, nz), dim3(256), 0, s, ca, chunks, n, red);
   };
-  auto ln_fwd = [&](auto heads, int rows, int n, const float* x, const float* g, const float* b, const float* res, float* out,
-                    float* stats, float* xr) {
-    constexpr bool HEADS = decltype(heads)::value;
-    if (D <= 1024) hipLaunchKernelGGL((ln_fwd_kernel<4, HEADS>), dim3(rows), dim3(256), 0, s, x, g, b, res, out, stats, D, m.eps, xr, k, n);
-    else hipLaunchKernelGGL((ln_fwd_kernel<16, HEADS>), dim3(rows), dim3(256), 0, s, x, g, b, res, out, stats, D, m.eps, xr, k, n);
+  auto ln_fwd = [&](auto src, int rows, int k_, int n, const float* x, const float* g, const float* b, const float* res,
+                    float* out, float* stats, float* xr, const float* bias) {
+    constexpr int SRC = decltype(src)::value;
+    const auto kernel = D <= 1024 ? ln_fwd_kernel<4, SRC> : ln_fwd_kernel<16, SRC>;
+    hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, s, x, g, b, res, out, stats, D, m.eps, xr, k_, n, bias);
   };
   auto ln_bwd = [&](auto heads, int rows, int n, const float* x, const float* stats, const float* g, const float* dy, float* dx,
                     float* P_) {
@@ -1216,10 +1245,21 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
     const slim_problem p = att_problem(m, n);
     CHECK_SLIM(slim_fwd(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, state_in, nullptr, Yh, nullptr, state_out, nullptr,
                         nullptr, attws, lay.attws_bytes, s));
-    ln_fwd(std::true_type(), rows, n, Yh, P.l[r].g1, P.l[r].b1n, X, Hr(r), s1r(r), Ar(r));
+    ln_fwd(std::integral_constant<int, LnHeads>(), rows, k, n, Yh, P.l[r].g1, P.l[r].b1n, X, Hr(r), s1r(r), Ar(r), nullptr);
     CHECK_HIP(mm(false, false, rows, F, D, Hr(r), D, P.l[r].W1, F, Z1r(r), F, epi(EPI_BIAS_GELU, P.l[r].b1, nullptr, G1r(r))));
-    CHECK_HIP(mm(false, false, rows, D, F, G1r(r), F, P.l[r].W2, D, For(r), D, epi(EPI_BIAS, P.l[r].b2)));
-    ln_fwd(std::false_type(), rows, n, For(r), P.l[r].g2, P.l[r].b2n, Hr(r), Xr(r + 1), s2r(r), nullptr);
+    // A split product's parts are summed by the normalisation that reads them,
+    // given a workgroup (a row) for every compute unit: at 1024 rows of 1024
+    // and 8 parts a step of 24 such pairs gains 0.3 ms, at 64 rows and 16 parts
+    // the pair takes 8.8 us in one launch and 8.2 in two.
+    const int parts = rows >= 256 ? gemm_plan(rows, D, F).splits : 1;
+    CHECK_HIP(gemm(false, false, rows, D, F, G1r(r), F, P.l[r].W2, D, For(r), D, epi(EPI_BIAS, P.l[r].b2), part, s, nullptr,
+                   parts == 1));
+    if (parts > 1)
+      ln_fwd(std::integral_constant<int, LnParts>(), rows, parts, n, part, P.l[r].g2, P.l[r].b2n, Hr(r), Xr(r + 1), s2r(r),
+             For(r), P.l[r].b2);
+    else
+      ln_fwd(std::integral_constant<int, LnRows>(), rows, k, n, For(r), P.l[r].g2, P.l[r].b2n, Hr(r), Xr(r + 1), s2r(r),
+             nullptr, nullptr);
     CHECK_HIP(hipGetLastError());
     return SLIM_OK;
   };
@@ -1309,8 +1349,8 @@ int step(const Dims& m, const int* tokens, const Params& P, const Grads& G, floa
       // (eq. 18 gives the one before it)
       float* gin = gst + ((size_t)gcur * m.s + r) * S;
       float* gout = gst + ((size_t)(1 - gcur) * m.s + r) * S;
-      CHECK_SLIM(slim_bwd(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, bprev + r * S, nullptr, nullptr, dYh, nullptr,
-                          nullptr, gin, dQh, dQh + hf, dQh + 2 * hf, wd, gout, nullptr, attws, lay.attws_bytes, s));
+      CHECK_SLIM(slim::attention_bwd(&p, Qhr(r, 0), Qhr(r, 1), Qhr(r, 2), ident, bprev + r * S, dYh, gin, dQh, dQh + hf,
+                                     dQh + 2 * hf, gout, attws, lay.attws_bytes, s));
       hipLaunchKernelGGL(heads_to_rows_kernel, grid1(3 * hf), dim3(256), 0, s, dQh, dQKV, 3 * D, 0, D, k, n, hf, 3 * hf);
       CHECK_HIP(hipGetLastError());
       // [Q K V] = X [Wq Wk Wv]: [dWq dWk dWv] += X^T [dQ dK dV];
