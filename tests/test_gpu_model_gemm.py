@@ -32,6 +32,9 @@ CASES = [
     # layer normalisation with 4 values per thread, full, and with 16
     ModelConfig("ln1024", L=20, D=1024, s=1, vocab=64, B=2),
     ModelConfig("ln1088", L=33, D=1088, s=1, vocab=64, B=1),
+    # rows enough for the normalisation to sum a split product's parts
+    ModelConfig("parts1088", L=300, D=1088, s=1, vocab=64, B=1),
+    ModelConfig("parts256", L=259, D=256, s=1, vocab=64, B=1),
 ]
 
 
